@@ -62,12 +62,14 @@ constexpr uint32_t kLutLdsCap = 32 * 1024;  // decode tables kept in LDS when th
 constexpr uint32_t kPalFast = 252;       // u8 indices 0..251; 252 marks an invalid reference, 253..255 open ones
 constexpr uint32_t kRingWords = 1024;    // word ring of the entropy decoder
 constexpr int kWavesLeaf = 8;            // waves of a leaf workgroup (LDS arena)
+constexpr int kWavesGen = 4;             // waves of a front workgroup for other brick edges and raw nibbles
 constexpr int kWavesLeafG = 4;           // waves of a leaf workgroup with a global-memory arena
 
 // level m (1..4) offsets (entries) inside the Morton-ordered level arrays
 __device__ constexpr uint32_t kLvOff[5] = {0, 0, 4096, 4608, 4672};
 // expanded-node bit arrays (bytes, one per parent) for levels 1..4
 __device__ constexpr uint32_t kBmOff[5] = {0, 0, 512, 576, 584};
+constexpr uint32_t kLvOffH[5] = {0, 0, 4096, 4608, 4672};  // (for host code)
 // lists of expanded nodes (u16 entries) for levels 2..4; level 1 has its own
 __device__ constexpr uint32_t kLstOff[5] = {0, 0, 72, 8, 0};
 
@@ -110,6 +112,7 @@ struct DecodeArgs {
     // code in req_err[rq]; successful requests leave their entry untouched
     int *req_err;
     uint32_t rq_base;  // index of request 0 in the caller's whole batch (errors name requests by it)
+    const uint8_t *vol_raw;  // per volume: symbols stored as raw nibbles (only read by kernels for such pools)
 };
 
 // What the leaf kernel needs of a full-LOD request, written by the front
@@ -303,6 +306,7 @@ struct Hdr {
     uint32_t pdw;         // word dwords in the device record (0xFFFFFFFF: all)
     bool up;              // full LOD requested, level 1 decoded and written upsampled
     uint32_t P, W, nw, t, vol, rq, id;
+    bool raw;             // symbols stored as raw nibbles (pools that may hold such volumes)
     // cumulative symbol counts (scalars: a run-time level never indexes a private array)
     uint32_t c0, c1, c2, c3, c4;
     __device__ __forceinline__ uint32_t c(uint32_t m) const {
@@ -317,7 +321,21 @@ struct NoHook {
 
 enum ReqKind { kReqBadLod, kReqBadId, kReqCorrupt, kReqFill, kReqDecode };
 
+// A brick of edge 32 >> SH has the levels SH .. 5 of a 32^3 brick: its level
+// t is level t + SH here, in Hdr::t, in Hdr::c() and in every function of
+// the replay, and its finest level is level SH.
+template <int SH>
+constexpr uint32_t header_words() { return csv::record_header_words(kLog2 - SH); }
+
+// symbols before the segment of the finest level (coded with the other table)
+template <int SH>
+__device__ __forceinline__ uint32_t leaf_start(const Hdr &h) {
+    return SH == 0 ? h.c1 : SH == 1 ? h.c2 : SH == 2 ? h.c3 : SH == 3 ? h.c4 : 0u;
+}
+
 // read and check request rq; for kReqFill, fill is the value of every output label
+// kGen: pools with bricks of edge 32 >> SH that may hold raw-nibble volumes
+template <int SH = 0, bool kGen = false>
 __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq, Hdr &h, uint32_t *&dst,
                                                 uint32_t &count, uint32_t &fill) {
     h.rq = rq;
@@ -325,7 +343,7 @@ __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq
     h.pdw = 0xFFFFFFFFu;
     h.up = false;
     h.id = ld_s(a.ids + rq);
-    h.t = a.lods ? ld_s_u8(a.lods + rq) : a.lod_scalar;
+    h.t = (a.lods ? ld_s_u8(a.lods + rq) : a.lod_scalar) + (uint32_t)SH;
     dst = nullptr;
     count = 0;
     fill = 0;
@@ -340,22 +358,28 @@ __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq
     h.P = ld_s(h.rec + 0);
     h.W = ld_s(h.rec + 1);
     h.nw = ld_s(h.rec + 2);
+    // the counts of levels finer than the brick's finest one (SH) are that one's
     h.c0 = ld_s(h.rec + 3);
-    h.c1 = ld_s(h.rec + 4);
-    h.c2 = ld_s(h.rec + 5);
-    h.c3 = ld_s(h.rec + 6);
-    h.c4 = ld_s(h.rec + 7);
-    if (a.pfx_dw) {
+    h.c1 = h.c2 = h.c3 = h.c4 = h.c0;
+    if constexpr (SH < 1) h.c1 = ld_s(h.rec + 4 - SH);
+    if constexpr (SH < 2) h.c2 = ld_s(h.rec + 5 - SH);
+    if constexpr (SH < 3) h.c3 = ld_s(h.rec + 6 - SH);
+    if constexpr (SH < 4) h.c4 = ld_s(h.rec + 7 - SH);
+    h.raw = false;
+    if constexpr (kGen) h.raw = ld_s_u8(a.vol_raw + h.vol) != 0;
+    if (!kGen && a.pfx_dw) {
         h.pdw = ld_s(a.pfx_dw + h.id);
         if (h.pdw != 0xFFFFFFFFu) {
             const uint64_t s = ld_s(a.sfx + h.id);
             h.sfx = s ? rec_at(s) : nullptr;
         }
     }
-    const uint32_t hdr = csv::record_header_words(kLog2);
+    const uint32_t hdr = header_words<SH>();
     // the record holds its words up to pdw dwords (the rest is staged)
-    bool ok = h.P >= 1 && h.W <= 64 && (h.W & (h.W - 1)) == 0 && ((h.c0 > 0) == (h.W > 0)) && h.c0 <= kMaxSym &&
+    bool ok = h.P >= 1 && h.W <= 64 && (h.W & (h.W - 1)) == 0 && ((h.c0 > 0) == (h.W > 0) || (kGen && h.raw)) &&
+              h.c0 <= kMaxSym &&
               4ull * ((uint64_t)hdr + h.P + h.W) + std::min<uint64_t>(2ull * h.nw, 4ull * h.pdw) <= size;
+    if constexpr (kGen) ok = ok && (!h.raw || (h.W == 0 && h.nw == (h.c0 + 3) / 4));
     ok = ok && h.c0 >= h.c1 && h.c1 >= h.c2 && h.c2 >= h.c3 && h.c3 >= h.c4;
     if (ok) ok = (h.c0 == 0) ? (h.P == 1) : (h.P >= 2);
     if (!ok) return kReqCorrupt;
@@ -363,7 +387,7 @@ __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq
         fill = ld_s(h.rec + hdr);
         return kReqFill;
     }
-    if (h.t == 0 && h.pdw != 0xFFFFFFFFu && !h.sfx) {  // level 0 not on the device: level 1, upsampled
+    if (!kGen && h.t == 0 && h.pdw != 0xFFFFFFFFu && !h.sfx) {  // level 0 not on the device: level 1, upsampled
         h.t = 1;
         h.up = true;
     }
@@ -599,7 +623,12 @@ __device__ __forceinline__ void wave_sync() {
 // at_upper (with the paired front kernel) is called once, in wave-uniform
 // control flow, as soon as the nibble dwords of the first c_1 symbols (the
 // levels above L_0) are written, else at the end
-template <bool kLutLds, class Hook = NoHook>
+// kNarrow: blocks of 8 steps also for bricks of 8, 16 or 32 states, the rule
+// for bricks of a smaller edge (16^3 bricks have 16 or 32 states; decoding
+// 32,768 of them takes 0.39 ms).  The kernels for 32^3 rANS pools leave it
+// out: their bricks mostly have 64 states, and the added code made the front
+// kernel 1 % slower (32,768 and 4,096 bricks at full LOD).
+template <bool kLutLds, int SH = 0, bool kNarrow = false, class Hook = NoHook>
 __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h, const uint32_t *slut,
                                                uint32_t *ring32, uint32_t *out, uint32_t *lcopy, uint32_t n,
                                                uint32_t &words, Hook at_upper = Hook{}) {
@@ -615,11 +644,11 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
         }
     };
     const uint32_t L = lane();
-    const uint32_t hdr = csv::record_header_words(kLog2);
+    const uint32_t hdr = header_words<SH>();
     const uint16_t *ring = reinterpret_cast<const uint16_t *>(ring32);
     const uint32_t sbits = ld_s(a.vol_bits + h.vol), lutn = 1u << sbits, mask = lutn - 1u;
     const uint32_t *lut = (kLutLds ? slut : glob(a.luts)) + ld_s(a.lut_off + h.vol);
-    const uint32_t W = h.W, lw = 31u - (uint32_t)__builtin_clz(W), leaf = h.c1;
+    const uint32_t W = h.W, lw = 31u - (uint32_t)__builtin_clz(W), leaf = leaf_start<SH>(h);
     const uint32_t *wg = h.rec + hdr + h.P + W;
     const uint32_t ndw = (h.nw + 1) / 2;  // word dwords in the record (the last one padded)
     // dword d of the word stream: from the record below pdw, then from the
@@ -731,6 +760,47 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
         // words past the end of the stream came from stale ring entries
         bad = cursor > h.nw;
         if (bad) s = steps;
+    } else if (kNarrow && W >= 8) {
+        // 8, 16 or 32 states: the same blocks of 8 steps, lanes from W on left out of the ballot.
+        // What those lanes write behind a step's W symbol bytes is
+        // overwritten by the next step (the last step's ends below byte
+        // 7 * 32 + 64 of the 512).
+        uint8_t *sb = reinterpret_cast<uint8_t *>(ring32) + 2 * kRingWords + 128;
+        const uint64_t lanes = (1ull << W) - 1ull;
+        auto block8w = [&](auto leaf_select) {
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const uint32_t i = ((s + (uint32_t)j) << lw) + L;
+                const uint32_t tb = decltype(leaf_select)::value ? (i >= leaf ? lutn : 0u) : 0u;
+                const uint32_t e = lut[tb + (x & mask)];
+                x = __umul24(e >> 20, x >> sbits) + ((e >> 8) & 0xFFFu);
+                const bool need = x < csv::kRansLower;
+                const uint64_t bal = __ballot(need) & lanes;
+                uint32_t wd = (ring + (cursor & (kRingWords - 1)))[mbcnt(bal)];
+                __asm__ volatile("" : "+v"(wd));
+                x = need ? ((x << 16) | wd) : x;
+                cursor += (uint32_t)__popcll(bal);
+                sb[((uint32_t)j << lw) + L] = (uint8_t)e;
+                if (cursor >= ring_lo + 512) refill();
+            }
+            wsync();
+            const uint2 b = *reinterpret_cast<const uint2 *>(sb + 8 * L);
+            const uint32_t lo = (b.x | (b.x >> 4)) & 0x00FF00FFu, hi = (b.y | (b.y >> 4)) & 0x00FF00FFu;
+            const uint32_t packed = ((lo | (lo >> 8)) & 0xFFFFu) | (((hi | (hi >> 8)) & 0xFFFFu) << 16);
+            const uint32_t at = ((s << lw) >> 3) + L;
+            if (L < W) {
+                out[at] = packed;
+                if (at < kWDeltaDw) lcopy[at] = packed;
+            }
+            wsync();
+            s += 8;
+            upper_done(s << lw);
+        };
+        const uint32_t full = n >> lw, s_int = min(leaf >> lw, full);
+        while (s + 8 <= s_int) block8w(std::false_type{});
+        while (s + 8 <= full) block8w(std::true_type{});
+        bad = cursor > h.nw;
+        if (bad) s = steps;
     }
     for (; s < steps; s++) {
         const uint32_t i = (s << lw) + L;
@@ -776,9 +846,27 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
         if (!fired) at_upper();
     }
     // a complete decode ends in the encoder's initial states with every word read
-    if (!bad && h.t == 0) bad = (__ballot(L < W && x != csv::kRansLower) != 0) || cursor != h.nw;
+    if (!bad && h.t == (uint32_t)SH) bad = (__ballot(L < W && x != csv::kRansLower) != 0) || cursor != h.nw;
     words = cursor;
     return !bad;
+}
+
+// The first n symbols of a raw-nibble brick: its words are the packed
+// nibbles already (symbol i in bits 4 (i mod 8) of dword i / 8, from a dword
+// boundary on), copied to where entropy_decode leaves them.
+template <int SH>
+__device__ __forceinline__ bool raw_nibbles(const Hdr &h, uint32_t *out, uint32_t *lcopy, uint32_t n) {
+    const uint32_t L = lane(), c = h.c0;
+    const uint32_t *wg = h.rec + header_words<SH>() + h.P;
+    for (uint32_t d = L; d < (n + 7) / 8; d += 64) {
+        const uint32_t v = wg[d];
+        out[d] = v;
+        if (d < kWDeltaDw) lcopy[d] = v;
+    }
+    // a complete decode finds the last word's unused nibbles zero
+    if (h.t != (uint32_t)SH || (c & 3u) == 0) return true;
+    const uint32_t last = (ld_s(wg + (h.nw - 1) / 2) >> (16 * ((h.nw - 1) & 1u))) & 0xFFFFu;
+    return (last >> (4 * (c & 3u))) == 0;
 }
 
 // Replay of levels 4 .. max(t, 1) by one wave (Alg. 1).  lv: the level
@@ -786,7 +874,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
 // levels 2..4 in LDS; nib: the brick's nibbles (global).  On return E and
 // ipl hold the number of expanded L_1 nodes and the P_a operations so far.
 // False on a malformed stream.
-template <class IdxT, bool kG>
+template <class IdxT, bool kG, int SH = 0>
 __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, IdxT *lv, uint8_t *bm, uint16_t *lst,
                                              uint32_t *dstage, uint32_t &E_out, uint32_t &ipl_out) {
     using V = Vec8<IdxT>;
@@ -804,7 +892,7 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
         uint8_t *cbm = bm + kBmOff[m];
         const uint8_t *pbm = (m + 1 <= 4) ? bm + kBmOff[m + 1] : nullptr;
         const uint16_t *plist = (m + 1 <= 4) ? lst + kLstOff[m + 1] : nullptr;
-        const bool want_list = m >= 2;  // L_1's list is rebuilt from its bits by the leaf kernel
+        const bool want_list = m >= 2 && !(SH > 0 && m == SH);  // L_1's list is rebuilt from its bits by the leaf kernel
         uint16_t *clist = lst + kLstOff[m];
         const uint32_t list_cap = 1u << (3 * (kLog2 - m));
         // children of parents that are not expanded inherit the parent's index
@@ -864,7 +952,8 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
                     }
                     const VT vals = replay8<IdxT>(wd, pv, nb, nbok, lowok, ipl + bpa + (exc & 1023u),
                                                           compact_nibble_bits(pam), compact_nibble_bits(pdm), src,
-                                                          seg - off + bpd + ((exc >> 10) & 1023u), P, false, bad);
+                                                          seg - off + bpd + ((exc >> 10) & 1023u), P,
+                                                          SH > 0 && m == SH, bad);
                     *reinterpret_cast<VT *>(cur + 8 * q) = vals;
                     uint32_t ex8 = compact_nibble_bits(exm);
                     cbm[q] = (uint8_t)ex8;
@@ -1058,19 +1147,20 @@ __device__ __forceinline__ void hand_off(const Hdr &h, const LaunchA &l, uint32_
     }
 }
 
-template <class IdxT, bool kG>
+template <class IdxT, bool kG, int SH = 0>
 __device__ __forceinline__ bool front_replay(const Hdr &h, const LaunchA &l, const uint32_t *nib, uint8_t *slot,
                                              uint8_t *wl, uint32_t *dst, uint32_t *e1_ipl = nullptr) {
     const uint32_t L = lane();
-    const uint32_t hdr = csv::record_header_words(kLog2);
+    const uint32_t hdr = header_words<SH>();
     uint8_t *slv = slot + 4 * l.slot_dw;
     uint8_t *sbm = slv + kSlotLv;
-    IdxT *lv = kG ? reinterpret_cast<IdxT *>(slv) : reinterpret_cast<IdxT *>(wl + kWLv);
+    // (a slot for smaller bricks holds levels SH .. 4 only)
+    IdxT *lv = kG ? reinterpret_cast<IdxT *>(slv) - (SH > 0 ? kLvOff[SH] : 0u) : reinterpret_cast<IdxT *>(wl + kWLv);
     uint8_t *bm = wl + kWBm;
     uint16_t *lst = reinterpret_cast<uint16_t *>(wl + kWLst);
     uint32_t E1 = 0, ipl = 0;
-    if (!upper_replay<IdxT, kG>(h, nib, lv, bm, lst, reinterpret_cast<uint32_t *>(wl + kWPal), E1, ipl)) return false;
-    if (h.t >= 1) {
+    if (!upper_replay<IdxT, kG, SH>(h, nib, lv, bm, lst, reinterpret_cast<uint32_t *>(wl + kWPal), E1, ipl)) return false;
+    if (SH > 0 || h.t >= 1) {
         const uint32_t *pal = h.rec + hdr;
         if (!kG) {  // stage the palette next to the levels
             uint32_t *sp = reinterpret_cast<uint32_t *>(wl + kWPal);
@@ -1100,7 +1190,16 @@ __device__ __forceinline__ bool front_replay(const Hdr &h, const LaunchA &l, con
 
 // kLutLds: the decode tables of every volume are copied to LDS (else read
 // from global memory)
-template <int WPG, bool kLutLds>
+// SH, kGen: bricks of edge 32 >> SH, rANS or raw nibbles.  SH > 0 decodes a
+// brick whole (its levels are the upper levels of a 32^3 brick, level SH
+// last), so a slot serves a wave, not a request, and nothing reaches the
+// leaf kernel.
+// Bricks of edge 16 are bound as the 32^3 front kernel is (a serial chain
+// per brick at 16 waves per CU, set by 8 KB of LDS each); a wave per brick
+// keeps the levels in LDS and needs no barrier: all 32,768 bricks of a 512^3
+// cells volume, full LOD, 0.391 ms (1.41 TB/s of labels and records); a
+// workgroup per brick with its levels in global scratch took 2.59 ms.
+template <int WPG, bool kLutLds, int SH = 0, bool kGen = false>
 // 16 waves per CU at most (LDS); registers for 4 per SIMD
 __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) void front_kernel(DecodeArgs a, LaunchA l) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -1135,7 +1234,7 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         phase_mark(rq, 0);
         Hdr h;
         uint32_t *dst, count, fill;
-        const ReqKind kind = load_request(a, rq, h, dst, count, fill);
+        const ReqKind kind = load_request<SH, kGen>(a, rq, h, dst, count, fill);
         if (l.words_out && kind != kReqDecode) {
             if (L == 0) l.words_out[rq] = kind == kReqFill ? 0u : 0xFFFFFFFFu;
             continue;
@@ -1152,7 +1251,7 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         }
         if (h.up && L == 0) fail(a, rq, CSV_EDETAIL, h.id);
         const uint32_t n = h.c(h.t);
-        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+        uint8_t *slot = glob(l.slots) + (size_t)(SH > 0 ? wid : rq) * l.slot_bytes;
         uint32_t *nib = reinterpret_cast<uint32_t *>(slot);
         if (n + 16 > 8 * l.slot_dw) {  // the slots are sized for the pool's largest brick
             if (L == 0) fail(a, rq, CSV_EINVAL, h.id);
@@ -1166,8 +1265,12 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         // the packed nibbles go to the slot, and their first kWDeltaDw dwords
         // also to the wave's staging area (the upper levels read them there)
         uint32_t words = 0;
-        bool ok = entropy_decode<kLutLds>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
-                                          nib, reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
+        bool ok;
+        if (kGen && h.raw)
+            ok = raw_nibbles<SH>(h, nib, reinterpret_cast<uint32_t *>(wl + kWPal), n);
+        else
+            ok = entropy_decode<kLutLds, SH, kGen>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
+                                             nib, reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
         if (l.words_out) {
             if (L == 0) l.words_out[rq] = ok ? words : 0xFFFFFFFFu;
             wsync();
@@ -1178,8 +1281,8 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         wsync();  // the ring is reused for the levels
-        if (ok) ok = h.P <= kPalFast ? front_replay<uint8_t, false>(h, l, nib, slot, wl, dst)
-                                     : front_replay<uint16_t, true>(h, l, nib, slot, wl, dst);
+        if (ok) ok = h.P <= kPalFast ? front_replay<uint8_t, false, SH>(h, l, nib, slot, wl, dst)
+                                     : front_replay<uint16_t, true, SH>(h, l, nib, slot, wl, dst);
         if (!ok) {
             if (L == 0) fail(a, rq, CSV_ECORRUPT, h.id);
             fill_labels<64>(dst, count, 0u, L);
@@ -2107,11 +2210,11 @@ struct LaunchBufs {
         arena_groups = groups;
         return CSV_OK;
     }
-    // room for n requests with slot_dw nibble dwords each
-    int reserve(uint32_t n, uint32_t dw) {
+    // room for n requests with slot_dw nibble dwords each (at least `least`)
+    int reserve(uint32_t n, uint32_t dw, uint32_t least = 1024u) {
         if (slots && n <= cap_n && dw == slot_dw) return CSV_OK;
         release();
-        const uint32_t cap = std::max(n, 1024u);
+        const uint32_t cap = std::max(n, least);
         slot_dw = dw;
         if (hipMalloc(reinterpret_cast<void **>(&slots), (size_t)cap * slot_bytes()) != hipSuccess ||
             hipMalloc(reinterpret_cast<void **>(&order), 4ull * cap) != hipSuccess ||
@@ -2173,8 +2276,7 @@ struct csv_pool {
     int *d_err = nullptr;
     std::vector<LaunchBufs> bufs;             // per stream, at most kMaxStreamBufs
     uint32_t brick_log2 = 0;                  // brick edge 2^brick_log2 of every volume (0: none yet)
-    bool generic = false;                     // a volume of another brick size or with raw nibbles:
-                                              // every decode takes the generic decoder
+    bool generic = false;                     // a volume of another brick size or with raw nibbles
     std::vector<uint8_t> vol_raw;             // per volume: symbols stored as raw nibbles
     uint8_t *d_vol_raw = nullptr;
     uint64_t use_clock = 0;
@@ -2387,9 +2489,14 @@ int stream_bufs(csv_pool *pool, hipStream_t s, uint32_t n, LaunchBufs **out) {
         if (cap) return CSV_EBUSY;  // buffers cannot be re-sized inside a capture
         if (b->slots && hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
         const uint64_t now = b->slots ? LaunchBufs::sized(b->cap_n, b->slot_dw) : 0;
-        const uint64_t want = LaunchBufs::sized(std::max(n, 1024u), dw);
+        uint64_t want = LaunchBufs::sized(std::max(n, 1024u), dw);
+        uint32_t least = 1024u;
+        if (pool->generic && want > now && over_budget(pool, want - now)) {  // no more than this batch needs
+            want = LaunchBufs::sized(n, dw);
+            least = 1u;
+        }
         if (want > now && over_budget(pool, want - now)) return CSV_ENOMEM;
-        const int rc = b->reserve(n, dw);
+        const int rc = b->reserve(n, dw, least);
         if (rc) return rc;
     }
     *out = b;
@@ -2415,6 +2522,21 @@ void launch_a(const DecodeArgs &a, const LaunchA &l, uint32_t grid, size_t lds, 
         hipLaunchKernelGGL((front_kernel<WPG, false>), dim3(grid), dim3(64 * WPG), lds, s, a, l);
 }
 
+// the front kernel for pools with other brick edges or raw nibbles, 4 waves
+// per workgroup (4 workgroups fill a CU's LDS with tables up to 8 KB)
+template <int SH>
+void launch_gen(const DecodeArgs &a, const LaunchA &l, uint32_t grid, size_t lds, hipStream_t s) {
+    static std::once_flag once;
+    std::call_once(once, [] {
+        (void)set_lds_attr(front_kernel<kWavesGen, true, SH, true>);
+        (void)set_lds_attr(front_kernel<kWavesGen, false, SH, true>);
+    });
+    if (l.lut_lds_words)
+        hipLaunchKernelGGL((front_kernel<kWavesGen, true, SH, true>), dim3(grid), dim3(64 * kWavesGen), lds, s, a, l);
+    else
+        hipLaunchKernelGGL((front_kernel<kWavesGen, false, SH, true>), dim3(grid), dim3(64 * kWavesGen), lds, s, a, l);
+}
+
 void launch_pair(const DecodeArgs &a, const LaunchA &l, uint32_t grid, size_t lds, hipStream_t s) {
     static std::once_flag once;
     std::call_once(once, [] {
@@ -2425,6 +2547,123 @@ void launch_pair(const DecodeArgs &a, const LaunchA &l, uint32_t grid, size_t ld
         hipLaunchKernelGGL((front_pair_kernel<true>), dim3(grid), dim3(128), lds, s, a, l);
     else
         hipLaunchKernelGGL((front_pair_kernel<false>), dim3(grid), dim3(128), lds, s, a, l);
+}
+
+DecodeArgs decode_args(const csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_t lod_scalar,
+                       const uint64_t *out_off, uint32_t n, uint32_t *out, int *req_err, uint32_t rq_base,
+                       const uint32_t *n_dev = nullptr) {
+    DecodeArgs a;
+    a.rec_ptr = pool->d_rec_ptr;
+    a.rec_size = pool->d_rec_size;
+    a.rec_vol = pool->d_rec_vol;
+    a.luts = pool->d_luts;
+    a.lut_off = pool->d_lut_off;
+    a.vol_bits = pool->d_bits;
+    a.n_bricks = (uint32_t)pool->rec_ptr.size();
+    a.ids = ids;
+    a.lods = lods;
+    a.lod_scalar = lod_scalar;
+    a.out_off = out_off;
+    a.out = out;
+    a.n = n;
+    a.n_dev = n_dev;
+    a.err = pool->d_err;
+    a.pfx_dw = pool->any_split ? pool->d_pfx_dw : nullptr;
+    a.sfx = pool->any_split ? pool->d_sfx : nullptr;
+    a.req_err = req_err;
+    a.rq_base = rq_base;
+    a.vol_raw = pool->d_vol_raw;
+    return a;
+}
+
+// A decode on a pool of bricks of another edge than 32 (pool->mu held).
+// Edges 2..16: the front kernel alone, one wave per brick, the wave's slot
+// in the scratch of the stream's buffer set (packed nibbles, then the u16
+// levels of big palettes).  Edge 64: the generic decoder.
+int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_t lod_scalar,
+                 const uint64_t *out_off, uint32_t n, uint32_t *out, hipStream_t s, bool plain, int *req_err,
+                 uint32_t rq_base) {
+    const uint32_t cu = (uint32_t)std::max(1, pool->n_cu);
+    LaunchBufs *G = nullptr;
+    if (pool->brick_log2 < (uint32_t)kLog2) {
+        const uint32_t sh = (uint32_t)kLog2 - pool->brick_log2;
+        LaunchA la{};
+        la.lut_lds_words = lut_lds_words(pool);
+        la.slot_dw = slot_dw(pool);
+        la.slot_bytes = (4 * la.slot_dw + 2 * (4680u - kLvOffH[sh]) + 15u) & ~15u;
+        const uint32_t lds = align16(4 * la.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
+        const uint32_t most = cu * std::max(1u, kLdsBytes / lds);
+        // from half of the waves that fit on, scratch for all of them, so
+        // that it does not grow with larger batches
+        const uint32_t grid = plain ? 1u : std::min(most, (n + kWavesGen - 1) / kWavesGen);
+        const uint32_t waves = n >= most * kWavesGen / 2 ? most * kWavesGen : std::min(n, grid * kWavesGen);
+        const int rc = generic_bufs(pool, s, (uint64_t)la.slot_bytes * (plain ? 1u : waves), &G);
+        if (rc) return rc;
+        la.slots = G->gen;
+        DecodeArgs a = decode_args(pool, ids, lods, lod_scalar, out_off, n, out, req_err, rq_base);
+        auto go = [&](uint32_t g) {
+            switch (sh) {
+                case 1: launch_gen<1>(a, la, g, lds, s); break;
+                case 2: launch_gen<2>(a, la, g, lds, s); break;
+                case 3: launch_gen<3>(a, la, g, lds, s); break;
+                default: launch_gen<4>(a, la, g, lds, s); break;
+            }
+        };
+        if (plain) {
+            for (uint32_t i = 0; i < n; i++) {
+                la.base = i;
+                a.n = i + 1;
+                go(1);
+            }
+        } else {
+            go(grid);
+        }
+        return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
+    }
+    // 8 workgroups per CU (few registers and 112 bytes of LDS each), 4 for
+    // 64^3 bricks (1.9 MB of scratch per workgroup)
+    const uint32_t groups = plain ? 1u : std::min(n, (pool->brick_log2 >= 6 ? 4u : 8u) * cu);
+    csv::GenericArgs ga{};
+    ga.sym_cap = pool->max_c0 + 16;
+    ga.scratch_per_group = csv::generic_scratch_bytes(pool->brick_log2, ga.sym_cap);
+    const int rc = generic_bufs(pool, s, ga.scratch_per_group * groups, &G);
+    if (rc) return rc;
+    ga.rec_ptr = pool->d_rec_ptr;
+    ga.rec_size = pool->d_rec_size;
+    ga.rec_vol = pool->d_rec_vol;
+    ga.luts = pool->d_luts;
+    ga.lut_off = pool->d_lut_off;
+    // the tables in LDS when 8 workgroups per CU still fit
+    ga.lut_lds_words = 4 * pool->luts.size() <= 16 * 1024 ? (uint32_t)pool->luts.size() : 0u;
+    ga.vol_bits = pool->d_bits;
+    ga.vol_raw = pool->d_vol_raw;
+    ga.n_bricks = (uint32_t)pool->rec_ptr.size();
+    ga.log2 = pool->brick_log2;
+    ga.ids = ids;
+    ga.lods = lods;
+    ga.lod_scalar = lod_scalar;
+    ga.out_off = out_off;
+    ga.out = reinterpret_cast<uint64_t>(out);
+    ga.n = n;
+    ga.err = pool->d_err;
+    ga.req_err = req_err;
+    ga.rq_base = rq_base;
+    ga.scratch = reinterpret_cast<uint64_t>(G->gen);
+    if (!plain) return csv::generic_launch(ga, groups, s) == hipSuccess ? CSV_OK : CSV_EHIP;
+    // one launch per brick
+    const uint64_t g1 = (1u << pool->brick_log2) >> (lods ? 0u : lod_scalar);
+    for (uint32_t i = 0; i < n; i++) {
+        csv::GenericArgs gi = ga;
+        gi.ids = ids + i;
+        gi.lods = lods ? lods + i : nullptr;
+        gi.out_off = out_off ? out_off + i : nullptr;
+        gi.out = reinterpret_cast<uint64_t>(out_off ? out : out + (uint64_t)i * g1 * g1 * g1);
+        gi.n = 1;
+        gi.req_err = req_err ? req_err + i : nullptr;
+        gi.rq_base = rq_base + i;
+        if (csv::generic_launch(gi, 1, s) != hipSuccess) return CSV_EHIP;
+    }
+    return CSV_OK;
 }
 
 // waves_a: front-kernel waves per workgroup (2: the paired kernel, two
@@ -2464,56 +2703,16 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     std::call_once(once_b, [] { attr_b = set_lds_attr(leaf_kernel<kWavesLeaf, false>); });
     if (attr_b != hipSuccess) return CSV_EHIP;
     std::lock_guard<std::mutex> lk(pool->mu);
-    if (pool->generic) {
-        // other brick sizes and raw nibbles: the generic decoder, one
-        // workgroup per brick (no launch shape, no fixed buffers)
+    const bool gen = pool->generic;
+    if (gen) {
+        // no launch shape, no fixed buffers; 32^3 raw nibbles take the
+        // kernels below, other brick edges their own launch
         if (fixed || words_out || n_dev) return CSV_EINVAL;
-        // 8 workgroups per CU (few registers and 112 bytes of LDS each), 4 for
-        // 64^3 bricks (1.9 MB of scratch per workgroup)
-        const uint32_t cu = (uint32_t)std::max(1, pool->n_cu);
-        const uint32_t groups = plain ? 1u : std::min(n, (pool->brick_log2 >= 6 ? 4u : 8u) * cu);
-        csv::GenericArgs ga{};
-        ga.sym_cap = pool->max_c0 + 16;
-        ga.scratch_per_group = csv::generic_scratch_bytes(pool->brick_log2, ga.sym_cap);
-        LaunchBufs *G = nullptr;
-        const int rc = generic_bufs(pool, s, ga.scratch_per_group * groups, &G);
-        if (rc) return rc;
-        ga.rec_ptr = pool->d_rec_ptr;
-        ga.rec_size = pool->d_rec_size;
-        ga.rec_vol = pool->d_rec_vol;
-        ga.luts = pool->d_luts;
-        ga.lut_off = pool->d_lut_off;
-        // the tables in LDS when 8 workgroups per CU still fit
-        ga.lut_lds_words = 4 * pool->luts.size() <= 16 * 1024 ? (uint32_t)pool->luts.size() : 0u;
-        ga.vol_bits = pool->d_bits;
-        ga.vol_raw = pool->d_vol_raw;
-        ga.n_bricks = (uint32_t)pool->rec_ptr.size();
-        ga.log2 = pool->brick_log2;
-        ga.ids = ids;
-        ga.lods = lods;
-        ga.lod_scalar = lod_scalar;
-        ga.out_off = out_off;
-        ga.out = reinterpret_cast<uint64_t>(out);
-        ga.n = n;
-        ga.err = pool->d_err;
-        ga.req_err = req_err;
-        ga.rq_base = rq_base;
-        ga.scratch = reinterpret_cast<uint64_t>(G->gen);
-        if (!plain) return csv::generic_launch(ga, groups, s) == hipSuccess ? CSV_OK : CSV_EHIP;
-        // one launch per brick
-        const uint64_t g1 = (1u << pool->brick_log2) >> (lods ? 0u : lod_scalar);
-        for (uint32_t i = 0; i < n; i++) {
-            csv::GenericArgs gi = ga;
-            gi.ids = ids + i;
-            gi.lods = lods ? lods + i : nullptr;
-            gi.out_off = out_off ? out_off + i : nullptr;
-            gi.out = reinterpret_cast<uint64_t>(out_off ? out : out + (uint64_t)i * g1 * g1 * g1);
-            gi.n = 1;
-            gi.req_err = req_err ? req_err + i : nullptr;
-            gi.rq_base = rq_base + i;
-            if (csv::generic_launch(gi, 1, s) != hipSuccess) return CSV_EHIP;
-        }
-        return CSV_OK;
+        if (pool->brick_log2 != (uint32_t)kLog2)
+            return launch_edges(pool, ids, lods, lod_scalar, out_off, n, out, s, plain, req_err, rq_base);
+        waves_a = kWavesGen;
+        groups_b = 3;
+        queue = lpt = false;
     }
     LaunchBufs *B = fixed;
     if (!B) {
@@ -2522,26 +2721,7 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     } else if (n > B->cap_n) {
         return CSV_EINVAL;
     }
-    DecodeArgs a;
-    a.rec_ptr = pool->d_rec_ptr;
-    a.rec_size = pool->d_rec_size;
-    a.rec_vol = pool->d_rec_vol;
-    a.luts = pool->d_luts;
-    a.lut_off = pool->d_lut_off;
-    a.vol_bits = pool->d_bits;
-    a.n_bricks = (uint32_t)pool->rec_ptr.size();
-    a.ids = ids;
-    a.lods = lods;
-    a.lod_scalar = lod_scalar;
-    a.out_off = out_off;
-    a.out = out;
-    a.n = n;
-    a.n_dev = n_dev;
-    a.err = pool->d_err;
-    a.pfx_dw = pool->any_split ? pool->d_pfx_dw : nullptr;
-    a.sfx = pool->any_split ? pool->d_sfx : nullptr;
-    a.req_err = req_err;
-    a.rq_base = rq_base;
+    const DecodeArgs a = decode_args(pool, ids, lods, lod_scalar, out_off, n, out, req_err, rq_base, n_dev);
     const uint32_t cu = (uint32_t)std::max(1, pool->n_cu);
     // the global-arena variant runs only for pools with bricks that may not fit the LDS arena;
     // its arenas belong to this buffer set, so launches on other streams never share them
@@ -2551,8 +2731,13 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const uint32_t grid_g = std::min(B->owned ? slow_groups(cu) : B->arena_groups, n);
     if (slow && (!B->arenas || B->arena_groups < grid_g)) {
         if (!B->owned || capturing(s)) return CSV_EBUSY;  // fixed buffers cannot grow
-        if (over_budget(pool, (uint64_t)slow_groups(cu) * kArenaBytes)) return CSV_ENOMEM;
-        const int rc = B->reserve_arenas(slow_groups(cu));
+        uint32_t groups = slow_groups(cu);
+        if (over_budget(pool, (uint64_t)groups * kArenaBytes)) {
+            groups = grid_g;  // raw nibbles: no more than this batch needs
+            if (!gen || over_budget(pool, (uint64_t)groups * kArenaBytes)) return CSV_ENOMEM;
+        }
+        if (B->arenas && hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
+        const int rc = B->reserve_arenas(groups);
         if (rc) return rc;
     }
     // counters: 0 front queue, 1 leaf queue, 2 leaf count, 3 slow count,
@@ -2605,6 +2790,10 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const uint32_t bricks_a = grid_a * per_wg;
     const uint32_t grid_b = std::min(cu * groups_b, n);
     auto go_a = [&](const DecodeArgs &aa, const LaunchA &L, uint32_t grid) {
+        if (gen) {
+            launch_gen<0>(aa, L, grid, lds_a, s);
+            return;
+        }
         switch (waves_a) {
             case 2: launch_pair(aa, L, grid, lds_a, s); break;
             case 4: launch_a<4>(aa, L, grid, lds_a, s); break;
@@ -2647,6 +2836,9 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
 // Requests per chunk below which a decode is not split (a chunk should
 // still fill the machine for a while).
 constexpr uint32_t kMinChunk = 2048;
+// Requests of a raw 32^3 pool decoded per launch pair: a slot takes 10 KB
+// plus half a byte per symbol, so 8192 hold 0.1 to 0.4 GB.
+constexpr uint32_t kRawChunk = 8192;
 constexpr size_t kMaxCompanions = kMaxStreamBufs / 2;
 
 // The companion stream of caller stream s, created on first use (nullptr
@@ -2683,7 +2875,28 @@ int launch(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_t lo
            uint32_t chunks = 1) {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     chunks = std::min(chunks, n / kMinChunk);
-    if (pool && pool->generic) chunks = 1;  // the generic decoder runs as one launch
+    if (pool && pool->generic) {
+        chunks = 1;  // (no launch shape)
+        if (pool->brick_log2 == (uint32_t)kLog2 && !plain && !fixed && !words_out && n > kRawChunk / 4 && ids &&
+            out && (!lods || out_off) && (lods || lod_scalar <= (uint32_t)kLog2)) {
+            // 32^3 raw nibbles: slots for at most kRawChunk requests; a
+            // stream capture, where they cannot grow, uses those there are
+            uint32_t per = kRawChunk;
+            if (capturing(s)) {
+                std::lock_guard<std::mutex> lk(pool->mu);
+                for (auto &e : pool->bufs)
+                    if (e.stream == s && e.cap_n >= kRawChunk / 4) per = std::min(per, e.cap_n);
+            }
+            const uint64_t G = 32u >> (lods ? 0u : lod_scalar), cnt = lods ? 0 : G * G * G;
+            int rc = CSV_OK;
+            for (uint32_t at = 0; at < n && rc == CSV_OK; at += per)
+                rc = launch_one(pool, ids + at, lods ? lods + at : nullptr, lod_scalar,
+                                out_off ? out_off + at : nullptr, std::min(per, n - at),
+                                out_off ? out : out + at * cnt, stream, false, waves_a, groups_b, queue, lpt, nullptr,
+                                nullptr, req_err ? req_err + at : nullptr, at);
+            return rc;
+        }
+    }
     if (chunks <= 1 || !pool || plain || fixed || words_out || !ids || !out || (lods && !out_off) ||
         (!lods && lod_scalar > (uint32_t)kLog2) || capturing(s))
         return launch_one(pool, ids, lods, lod_scalar, out_off, n, out, stream, plain, waves_a, groups_b, queue,
@@ -2844,7 +3057,7 @@ int csv_pool_add_volume(csv_pool *p, const uint8_t *blob, size_t blob_bytes, uin
     int rc = csv_blob_info(blob, blob_bytes, &info);
     if (rc) return rc;
     if (info.scale_bits > (uint32_t)kLutMaxBits || info.coding > 1) return CSV_EINVAL;
-    // one brick size per pool; other sizes and raw nibbles take the generic decoder
+    // one brick size per pool
     if (p->brick_log2 && info.brick_log2 != p->brick_log2) return CSV_EINVAL;
     const bool gen = info.brick_log2 != (uint32_t)kLog2 || info.coding != 0;
     if (gen && p->any_split) return CSV_EINVAL;  // detail separation needs the 32^3 rANS path

@@ -1,8 +1,7 @@
-// The decoder for every brick edge 2^N (N = 1..6) and both codings (rANS
-// and raw nibbles): one workgroup per brick, levels replayed one after
-// another in a global-memory scratch area of the workgroup.  The 32^3
-// rANS path of csv_decode.hip is the tuned one; this one serves the other
-// brick sizes and the coding without rANS (Table 1's variants).
+// The decoder for bricks of edge 64 with both codings (rANS and raw
+// nibbles): one workgroup per brick, levels replayed one after another in a
+// global-memory scratch area of the workgroup.  Smaller edges decode with
+// the kernels of csv_decode.hip.
 #pragma once
 #include <hip/hip_runtime.h>
 
