@@ -1,0 +1,660 @@
+// Decoder for 64^3 bricks with palettes of fewer than k64PalMax entries,
+// rANS or raw nibbles; part of csv_decode.hip, whose helpers it uses.  A
+// decode is up to three launches:
+//   entropy64_kernel  (pools with rANS volumes) one wave per brick: the
+//                     symbols as packed nibbles in the request's slot; raw
+//                     bricks are read where they lie in the record;
+//   upper64_kernel    a workgroup per brick: levels 5 .. max(t, 1) in LDS
+//                     (u16 palette indices, Morton order), one lane per
+//                     parent; t >= 1: the output.  t = 0: level 1, its
+//                     expansion bits and, per expanded level-1 node, the P_a
+//                     and P_delta operations before it go to the slot, and
+//                     everything that could be malformed in level 0 is
+//                     checked here;
+//   leaf64_kernel     one wave per block of 32 x 16 x 8 voxels: its expanded
+//                     parents 64 at a time, in no order that matters (each
+//                     has its own counts), the block in LDS, the output in
+//                     rows of 128 bytes.  References out of the block are
+//                     evaluated on the other block's operations.
+// The finest level of a 64^3 brick (512 KB of u16) does not fit LDS; blocks
+// that need nothing of each other's results keep it out of global memory
+// and give 64 waves of work per brick.
+
+constexpr uint32_t k64PalMax = 1u << 14;  // P_a counts of a slot have 14 bits
+constexpr int k64Threads = 512;           // of an upper workgroup
+constexpr uint32_t k64Waves = k64Threads / 64;
+
+// The slot of a request (bytes): level 1, its expansion bits, the expanded
+// nodes before each 64 of them, Head64, per expanded node its counts, the
+// nibbles (pools with rANS volumes)
+constexpr uint32_t k64Bits = 2 * 32768, k64Pre = k64Bits + 4096, k64Head = k64Pre + 1024, k64Info = k64Head + 256;
+
+struct Head64 {
+    uint32_t leaf;  // 1: a full-LOD request for leaf64_kernel
+    uint32_t bad;   // 1: the entropy decode failed
+    uint32_t P, ops0, seg, ipl;
+    uint64_t pal, nib, dst;
+};
+static_assert(sizeof(Head64) <= 256, "slot layout");
+
+struct Launch64 {
+    uint8_t *slots;
+    uint64_t slot_bytes;
+    uint32_t nib_off;        // nibbles in a slot
+    uint32_t nib_dw;         // dwords they may take
+    uint32_t lut_lds_words;  // decode-table words in LDS (entropy kernel; 0: read from global memory)
+};
+
+struct Hdr64 {
+    const uint32_t *rec;
+    uint32_t P, W, nw, t, vol, id;
+    bool raw;
+    uint32_t c[6];  // c[m]: symbols in the segments of child levels 5 .. m
+};
+
+__device__ __forceinline__ ReqKind load_request64(const DecodeArgs &a, uint32_t rq, Hdr64 &h, uint32_t *&dst,
+                                                  uint32_t &count, uint32_t &fill) {
+    h.id = ld_s(a.ids + rq);
+    h.t = a.lods ? ld_s_u8(a.lods + rq) : a.lod_scalar;
+    dst = nullptr;
+    count = 0;
+    fill = 0;
+    if (h.t > 6u) return kReqBadLod;
+    const uint32_t G = 64u >> h.t;
+    count = G * G * G;
+    dst = a.out + (a.out_off ? ld_s(a.out_off + rq) : (uint64_t)rq * count);
+    if (h.id >= a.n_bricks) return kReqBadId;
+    h.rec = rec_at(ld_s(a.rec_ptr + h.id));
+    const uint32_t size = ld_s(a.rec_size + h.id);
+    h.vol = ld_s_u16(a.rec_vol + h.id);
+    h.raw = ld_s_u8(a.vol_raw + h.vol) != 0;
+    h.P = ld_s(h.rec + 0);
+    h.W = ld_s(h.rec + 1);
+    h.nw = ld_s(h.rec + 2);
+    bool ok = true;
+#pragma unroll
+    for (int m = 0; m < 6; m++) {
+        h.c[m] = ld_s(h.rec + 3 + m);
+        if (m > 0) ok = ok && h.c[m] <= h.c[m - 1];
+    }
+    const uint32_t c0 = h.c[0], hdr = csv::record_header_words(6);
+    ok = ok && h.P < k64PalMax && (c0 == 0 ? h.P == 1 : h.P >= 2);
+    ok = ok && (h.raw ? (h.W == 0 && h.nw == (c0 + 3) / 4)
+                      : (h.W <= 64 && (h.W & (h.W - 1)) == 0 && (c0 > 0) == (h.W > 0)));
+    ok = ok && 4ull * ((uint64_t)hdr + h.P + h.W) + 2ull * h.nw <= size;
+    if (!ok) return kReqCorrupt;
+    if (h.t == 6u || c0 == 0) {
+        fill = ld_s(h.rec + hdr);
+        return kReqFill;
+    }
+    return kReqDecode;
+}
+
+// 5-bit coordinate -> Morton bit positions 0, 3, .., 12, and back
+__device__ __forceinline__ uint32_t spread5(uint32_t v) { return spread4(v) | ((v & 16u) << 8); }
+__device__ __forceinline__ uint32_t coord5(uint32_t p) {
+    return (p & 1u) | ((p >> 2) & 2u) | ((p >> 4) & 4u) | ((p >> 6) & 8u) | ((p >> 8) & 16u);
+}
+
+// One wave per rANS request; a serial chain of c_t / 64 steps (a brick of
+// the 512^3 cells volume has 100,000 symbols), so a launch of 512 bricks is
+// bound by that chain's latency, not by the machine.
+template <bool kLutLds>
+__global__ __launch_bounds__(64 * kWavesGen) void entropy64_kernel(DecodeArgs a, Launch64 l) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    uint32_t *slut = reinterpret_cast<uint32_t *>(smem);
+    if (kLutLds)
+        for (uint32_t e = threadIdx.x; e < l.lut_lds_words; e += blockDim.x) slut[e] = a.luts[e];
+    __syncthreads();
+    const uint32_t wave = uniform(threadIdx.x >> 6);
+    uint8_t *wl = smem + align16(4 * l.lut_lds_words) + wave * kWaveLds;
+    for (uint32_t rq = blockIdx.x * kWavesGen + wave; rq < a.n; rq += gridDim.x * kWavesGen) {
+        Hdr64 g;
+        uint32_t *dst, count, fill;
+        const ReqKind kind = load_request64(a, rq, g, dst, count, fill);
+        if (kind != kReqDecode || g.raw) continue;
+        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+        const uint32_t n = g.t == 0   ? g.c[0]
+                           : g.t == 1 ? g.c[1]
+                           : g.t == 2 ? g.c[2]
+                           : g.t == 3 ? g.c[3]
+                           : g.t == 4 ? g.c[4]
+                                      : g.c[5];
+        bool ok = n + 16 <= 8 * l.nib_dw;
+        if (ok) {
+            Hdr h;
+            h.rec = g.rec;
+            h.sfx = nullptr;
+            h.pdw = 0xFFFFFFFFu;
+            h.P = g.P;
+            h.W = g.W;
+            h.nw = g.nw;
+            h.vol = g.vol;
+            h.t = g.t - 1u;  // (levels of a 64^3 brick are one above those of Hdr)
+            h.c0 = g.c[1];
+            h.c1 = 0;
+            uint32_t words = 0;
+            ok = entropy_decode<kLutLds, -1>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
+                                             reinterpret_cast<uint32_t *>(slot + l.nib_off),
+                                             reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
+            wsync();
+        }
+        if (lane() == 0) reinterpret_cast<Head64 *>(slot + k64Head)->bad = ok ? 0u : 1u;
+    }
+}
+
+// LDS of an upper workgroup: levels 2..5 and the root (u16), level 1, the
+// expansion bits of levels 1..5 and of the root (64-bit words), expanded
+// nodes before each word of the parent level, per-wave counts
+__device__ constexpr uint32_t k64Lv[7] = {0, 0, 0, 4096, 4608, 4672, 4680};
+__device__ constexpr uint32_t k64Bm[7] = {0, 0, 512, 576, 584, 585, 586};  // words of level m
+constexpr uint32_t kU64L1 = 2 * 4688, kU64Bm = kU64L1 + 65536, kU64Pre = kU64Bm + 8 * 588, kU64Sm = kU64Pre + 1024,
+                   kU64Lds = kU64Sm + 96;
+
+// What bounds it: latency (a chain of six levels with a few barriers each,
+// at the two workgroups per CU that 80 KB of LDS allow).
+__global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4))) void upper64_kernel(DecodeArgs a,
+                                                                                                   Launch64 l) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    uint16_t *lv = reinterpret_cast<uint16_t *>(smem);
+    uint16_t *l1 = reinterpret_cast<uint16_t *>(smem + kU64L1);
+    uint64_t *bmw = reinterpret_cast<uint64_t *>(smem + kU64Bm);
+    uint16_t *pre = reinterpret_cast<uint16_t *>(smem + kU64Pre);
+    uint32_t *wt = reinterpret_cast<uint32_t *>(smem + kU64Sm);  // per wave: P_a, P_delta counts
+    uint32_t *tot = wt + 2 * k64Waves;                           // expanded parents
+    uint32_t *bad = tot + 1;
+    const uint32_t tid = threadIdx.x, L = lane(), w = uniform(tid >> 6), hdr = csv::record_header_words(6);
+    constexpr uint32_t kMark = 65533u;
+    using V = Vec8<uint16_t>;
+    for (uint32_t rq = blockIdx.x; rq < a.n; rq += gridDim.x) {
+        Hdr64 h;
+        uint32_t *dst, count, fill;
+        const ReqKind kind = load_request64(a, rq, h, dst, count, fill);
+        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+        Head64 *head = reinterpret_cast<Head64 *>(slot + k64Head);
+        __syncthreads();  // LDS of the request before
+        if (tid == 0) {
+            head->leaf = 0;
+            *bad = (kind == kReqDecode && !h.raw) ? head->bad : 0u;
+            bmw[k64Bm[6]] = 1;
+            bmw[k64Bm[5]] = 0;  // (8 of the word's bits are nodes)
+            lv[k64Lv[6]] = 0;
+        }
+        if (kind == kReqBadLod) {
+            if (tid == 0) fail(a, rq, CSV_ERANGE, a.rq_base + rq);
+            continue;
+        }
+        if (kind != kReqDecode) {
+            if (kind != kReqFill && tid == 0)
+                fail(a, rq, kind == kReqBadId ? CSV_ERANGE : CSV_ECORRUPT, kind == kReqBadId ? a.rq_base + rq : h.id);
+            fill_labels<k64Threads>(dst, count, kind == kReqFill ? fill : 0u, tid);
+            continue;
+        }
+        const uint32_t t = h.t, P = h.P;
+        const uint32_t *nib = h.raw ? h.rec + hdr + P : reinterpret_cast<const uint32_t *>(slot + l.nib_off);
+        if (h.raw && t == 0 && (h.c[0] & 3u) && tid == 0) {
+            // a complete decode finds the last word's unused nibbles zero
+            const uint32_t last = (nib[(h.nw - 1) / 2] >> (16 * ((h.nw - 1) & 1u))) & 0xFFFFu;
+            if ((last >> (4 * (h.c[0] & 3u))) != 0) *bad = 1;
+        }
+        uint32_t ipl = 0;
+        bool ok = true;
+        __syncthreads();
+        if (*bad) ok = false;
+        // child level m from the 8^(5 - m) nodes of level m + 1: wave w takes
+        // K words of 64 parents from word w K on, a lane per parent
+        auto level = [&](int m, uint32_t K, uint32_t seg, uint32_t seg_end) __attribute__((always_inline)) -> bool {
+            const uint32_t Bp = (uint32_t)(5 - m), np = 1u << (3 * Bp), nw = np < 64 ? 1u : np / 64;
+            const uint64_t *pb = bmw + k64Bm[m + 1];
+            const uint16_t *up = lv + k64Lv[m + 1];
+            uint16_t *cur = m == 1 ? l1 : lv + k64Lv[m];
+            uint8_t *cb = reinterpret_cast<uint8_t *>(bmw + k64Bm[m]);
+            if (w == 0) {
+                const uint32_t c = L < nw ? (uint32_t)__popcll(pb[L]) : 0u;
+                const uint32_t inc = wave_incl_scan(c);
+                pre[L] = (uint16_t)(inc - c);
+                if (L == 63) *tot = inc;
+            }
+            __syncthreads();
+            const uint32_t E = *tot;
+            if ((uint64_t)seg + 8ull * E > seg_end) return false;
+            const uint32_t D = seg_end - seg - 8 * E, ops0 = seg + D;  // deltas precede the operations
+            auto ops_of = [&](uint32_t j, uint64_t &b) -> uint32_t {  // the lane's operations (0: not expanded)
+                const uint32_t word = w * K + j;
+                b = word < nw ? pb[word] : 0ull;
+                return ((b >> L) & 1u) ? nib8(nib, ops0 + 8 * (pre[word & 511u] + mbcnt(b))) : 0u;
+            };
+            uint32_t sum = 0;
+#pragma unroll 4
+            for (uint32_t j = 0; j < K; j++) {
+                uint64_t b;
+                const uint32_t y = ops_of(j, b) & 0x77777777u;
+                sum += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u)) |
+                       ((uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u)) << 16);
+            }
+            sum = uniform(__builtin_amdgcn_readlane(wave_incl_scan(sum), 63));
+            if (L == 0) wt[w] = sum;
+            __syncthreads();
+            uint32_t bpa = 0, bpd = 0, tpa = 0, tpd = 0;
+#pragma unroll
+            for (uint32_t v = 0; v < k64Waves; v++) {
+                const uint32_t s = wt[v];
+                if (v < w) {
+                    bpa += s & 0xFFFFu;
+                    bpd += s >> 16;
+                }
+                tpa += s & 0xFFFFu;
+                tpd += s >> 16;
+            }
+            if (tpd != D) return false;
+            const uint32_t pm = axis_mask(0, Bp);
+            bool wrong = false;
+#pragma unroll 1
+            for (uint32_t j = 0; j < K; j++) {
+                const uint32_t q = 64 * (w * K + j) + L;
+                uint64_t b;
+                const uint32_t wd = ops_of(j, b);
+                const bool act = (b >> L) & 1u;
+                uint32_t pam, pdm, exm, cnt;
+                nibble_counts(wd, act, pam, pdm, exm, cnt);
+                const uint32_t inc = wave_incl_scan(cnt & 0xFFFFFu), exc = inc - (cnt & 0xFFFFFu);
+                const uint32_t all = uniform(__builtin_amdgcn_readlane(inc, 63));
+                if (q < np) {
+                    const uint32_t pv = up[q];
+                    typename V::T vals = V::splat(pv);
+                    if (act) {
+                        uint32_t nb[3], nbok = 0, lowok = 0;
+#pragma unroll
+                        for (int x = 0; x < 3; x++) {
+                            const uint32_t am = pm << x;
+                            const bool hi = (q & am) != am;
+                            nb[x] = hi ? (uint32_t)up[morton_inc(q, am)] : 0u;
+                            nbok |= hi ? (1u << x) : 0u;
+                            lowok |= (q & am) ? (1u << x) : 0u;
+                        }
+                        vals = replay_children<uint16_t>(wd, pv, nb, nbok, lowok, ipl + bpa + (exc & 1023u),
+                                                         compact_nibble_bits(pam), compact_nibble_bits(pdm), nib,
+                                                         seg + bpd + (exc >> 10), P, false, wrong);
+                    }
+                    *reinterpret_cast<typename V::T *>(cur + 8 * q) = vals;
+                    cb[q] = act ? (uint8_t)compact_nibble_bits(exm) : 0;
+                }
+                bpa += all & 1023u;
+                bpd += all >> 10;
+            }
+            if (__ballot(wrong) && L == 0) atomicOr(bad, 1u);
+            __syncthreads();
+            if (*bad) return false;
+            // references to the same-level node at -1, followed to their
+            // values (at most three links; a reader sees a reference or its
+            // final value, and both lead to the value)
+#pragma unroll 1
+            for (uint32_t j = 0; j < K; j++) {
+                const uint32_t word = w * K + j, q = 64 * word + L;
+                const uint64_t b = word < nw ? pb[word] : 0ull;
+                if (!((b >> L) & 1u)) continue;
+                const typename V::T vals = *reinterpret_cast<const typename V::T *>(cur + 8 * q);
+                uint32_t open = 0;
+#pragma unroll
+                for (int k = 0; k < 7; k++) open |= V::get(vals, k) >= kMark ? 1u << k : 0u;
+                while (open) {
+                    uint32_t kk = (uint32_t)__builtin_ctz(open), qq = q;
+                    const uint32_t at = 8 * q + kk;
+                    open &= open - 1u;
+                    uint32_t v = cur[at];
+                    while (v >= kMark) {
+                        const uint32_t x = v - kMark;
+                        qq = morton_dec(qq, pm << x);
+                        kk |= 1u << x;
+                        v = cur[8 * qq + kk];
+                    }
+                    cur[at] = (uint16_t)v;
+                }
+            }
+            ipl += tpa;
+            __syncthreads();
+            return true;
+        };
+        const uint32_t tl = t > 1 ? t : 1u;
+        auto cum = [&](uint32_t m) -> uint32_t {
+            return m == 5 ? h.c[5] : m == 4 ? h.c[4] : m == 3 ? h.c[3] : m == 2 ? h.c[2] : m == 1 ? h.c[1] : 0u;
+        };
+#pragma unroll 1
+        for (uint32_t m = 5; ok && m >= tl; m--) ok = level((int)m, m == 1 ? 8u : 1u, cum(m + 1), cum(m));
+        const uint32_t *pal = h.rec + hdr;
+        if (ok && t >= 1) {  // level t to the output (every index has been checked against P)
+            const uint32_t lg = 6 - t, G = 1u << lg;
+            const uint16_t *res = t == 1 ? l1 : lv + (t == 2 ? 0u : t == 3 ? 4096u : t == 4 ? 4608u : 4672u);
+            if (t == 5) {
+                if (tid < 8) dst[tid] = pal[res[tid]];  // Morton order equals dense order on 2^3
+            } else {
+                const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+                for (uint32_t e = 4 * tid; e < count; e += 4 * k64Threads) {
+                    const uint32_t x = e & (G - 1), y = (e >> lg) & (G - 1), z = e >> (2 * lg);
+                    const uint32_t m0 = spread5(x) | (spread5(y) << 1) | (spread5(z) << 2);
+                    const uint4 o = make_uint4(pal[res[m0]], pal[res[m0 | 1u]], pal[res[m0 | 8u]], pal[res[m0 | 9u]]);
+                    if (al) store4<true>(dst + e, o);
+                    else store4<false>(dst + e, o);
+                }
+            }
+            continue;
+        }
+        // t = 0: what leaf64_kernel needs of the levels above
+        const uint64_t *b1 = bmw + k64Bm[1];
+        uint32_t ops0 = 0;
+        const uint32_t seg = h.c[1], seg_end = h.c[0];
+        if (ok) {
+            const uint32_t c = (uint32_t)__popcll(b1[tid]), inc = wave_incl_scan(c);
+            if (L == 63) wt[w] = inc;
+            __syncthreads();
+            uint32_t before = 0, E = 0;
+#pragma unroll
+            for (uint32_t v = 0; v < k64Waves; v++) {
+                before += v < w ? wt[v] : 0u;
+                E += wt[v];
+            }
+            pre[tid] = (uint16_t)(before + inc - c);
+            __syncthreads();
+            ok = (uint64_t)seg + 8ull * E <= seg_end;
+            if (ok) {
+                // per expanded node the P_a and P_delta operations before it:
+                // a wave takes a run of nodes in stream order, its totals
+                // first.  The same operations are checked: no stop bit, no
+                // code 7, deltas and palette positions in range.
+                const uint32_t D = seg_end - seg - 8 * E;
+                ops0 = seg + D;
+                const uint32_t nch = (E + 63) / 64, cpw = (nch + k64Waves - 1) / k64Waves;
+                const uint32_t cb = min(w * cpw, nch), ce = min(cb + cpw, nch);
+                uint32_t spa = 0, spd = 0;
+                bool wrong = false;
+#pragma unroll 4
+                for (uint32_t ch = cb; ch < ce; ch++) {
+                    const uint32_t r = 64 * ch + L;
+                    const uint32_t wd = r < E ? nib8(nib, ops0 + 8 * r) : 0u, y = wd & 0x77777777u;
+                    spa += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u));
+                    spd += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u));
+                    wrong |= (wd & 0x88888888u) != 0 || zero_nibbles(y ^ 0x77777777u) != 0;
+                }
+                spa = uniform(__builtin_amdgcn_readlane(wave_incl_scan(spa), 63));
+                spd = uniform(__builtin_amdgcn_readlane(wave_incl_scan(spd), 63));
+                if (L == 0) {
+                    wt[2 * w] = spa;
+                    wt[2 * w + 1] = spd;
+                }
+                __syncthreads();
+                uint32_t bpa = 0, bpd = 0, tpa = 0, tpd = 0;
+#pragma unroll
+                for (uint32_t v = 0; v < k64Waves; v++) {
+                    const uint32_t s0 = wt[2 * v], s1 = wt[2 * v + 1];
+                    if (v < w) {
+                        bpa += s0;
+                        bpd += s1;
+                    }
+                    tpa += s0;
+                    tpd += s1;
+                }
+                ok = tpd == D && ipl + tpa < P;
+                if (ok) {
+                    uint32_t *info = reinterpret_cast<uint32_t *>(slot + k64Info);
+                    for (uint32_t ch = cb; ch < ce; ch++) {
+                        const uint32_t r = 64 * ch + L;
+                        const bool act = r < E;
+                        const uint32_t wd = act ? nib8(nib, ops0 + 8 * r) : 0u;
+                        uint32_t pam, pdm, exm, cnt;
+                        nibble_counts(wd, act, pam, pdm, exm, cnt);
+                        const uint32_t inc2 = wave_incl_scan(cnt & 0xFFFFFu), exc = inc2 - (cnt & 0xFFFFFu);
+                        const uint32_t all = uniform(__builtin_amdgcn_readlane(inc2, 63));
+                        const uint32_t pa = bpa + (exc & 1023u);
+                        uint32_t pd = bpd + (exc >> 10);
+                        if (act) info[r] = pa | (pd << 14);
+                        while (pdm) {  // delta d names the entry d + 1 before the last one used
+                            const uint32_t k4 = (uint32_t)__builtin_ctz(pdm);
+                            pdm &= pdm - 1u;
+                            const uint32_t ip =
+                                ipl + pa + (uint32_t)__builtin_popcount(pam & ((1u << k4) - 1u));
+                            wrong |= ip < nib1(nib, seg + pd) + 1u;
+                            pd++;
+                        }
+                        bpa += all & 1023u;
+                        bpd += all >> 10;
+                    }
+                    // references of nodes on the brick's faces must stay inside
+                    for (uint32_t word = w; word < 512; word += k64Waves) {
+                        const uint32_t q = 64 * word + L;
+                        const uint64_t b = b1[word];
+                        const uint32_t side[3] = {0x01010101u, 0x00110011u, 0x00001111u};  // children at 0 on the axis
+                        uint32_t face[3];  // nibbles whose reference along the axis would leave the brick
+                        bool any = false;
+#pragma unroll
+                        for (int x = 0; x < 3; x++) {
+                            const uint32_t am = 0x1249u << x, v = q & am;
+                            face[x] = (v == 0 ? side[x] : 0u) | (v == am ? 0x11111111u ^ side[x] : 0u);
+                            any |= face[x] != 0;
+                        }
+                        if (!__ballot(any && ((b >> L) & 1u))) continue;
+                        if (any && ((b >> L) & 1u)) {
+                            const uint32_t y = nib8(nib, ops0 + 8 * (pre[word] + mbcnt(b))) & 0x77777777u;
+                            wrong |= ((zero_nibbles(y ^ 0x11111111u) & face[0]) | (zero_nibbles(y ^ 0x22222222u) & face[1]) |
+                                      (zero_nibbles(y ^ 0x33333333u) & face[2])) != 0;
+                        }
+                    }
+                }
+                if (__ballot(wrong) && L == 0) atomicOr(bad, 1u);
+            }
+            __syncthreads();
+            if (*bad) ok = false;
+        }
+        if (!ok) {
+            if (tid == 0) fail(a, rq, CSV_ECORRUPT, h.id);
+            fill_labels<k64Threads>(dst, count, 0u, tid);
+            continue;
+        }
+        uint4 *s4 = reinterpret_cast<uint4 *>(slot);
+        const uint4 *l4 = reinterpret_cast<const uint4 *>(l1);
+#pragma unroll
+        for (int q = 0; q < 8; q++) s4[tid + k64Threads * q] = l4[tid + k64Threads * q];
+        reinterpret_cast<uint64_t *>(slot + k64Bits)[tid] = b1[tid];
+        reinterpret_cast<uint16_t *>(slot + k64Pre)[tid] = pre[tid];
+        if (tid == 0) {
+            head->P = P;
+            head->ops0 = ops0;
+            head->seg = seg;
+            head->ipl = ipl;
+            head->pal = reinterpret_cast<uintptr_t>(pal);
+            head->nib = reinterpret_cast<uintptr_t>(nib);
+            head->dst = reinterpret_cast<uintptr_t>(dst);
+            head->leaf = 1;
+        }
+    }
+}
+
+// LDS of a leaf wave: the block's 32 x 16 x 8 voxels as u16 (8 planes of 264
+// dwords), its expanded parents (word and lane), per word the rank of its
+// first one less its place in that list, voxels with a reference out of the
+// block
+constexpr uint32_t kV64Plane = 264, kV64List = 4 * 8 * kV64Plane, kV64Delta = kV64List + 1024, kV64Out = kV64Delta + 32,
+                   kV64OutCap = 256, kV64Wave = kV64Out + 2 * kV64OutCap;
+constexpr int k64LeafWaves = 4;
+constexpr uint32_t k64PalLds = 896;  // palette entries kept in LDS
+
+// Dword of voxels (x, x + 1), x even, of a block row.  The exclusive or
+// spreads the four y-rows of parents that a store touches over the banks, the
+// planes' 8 extra dwords spread z.
+__device__ __forceinline__ uint32_t v64_dw(uint32_t x, uint32_t y, uint32_t z) {
+    return kV64Plane * z + 16 * y + ((x >> 1) ^ (((y >> 1) & 3u) << 2));
+}
+
+struct Leaf64 {
+    const uint16_t *l1;
+    const uint64_t *bits;
+    const uint16_t *pre;
+    const uint32_t *info, *nib;
+    uint32_t ops0, seg, ipl;
+};
+
+// value of child k of level-1 node q, from the brick's operations
+__device__ __forceinline__ uint32_t eval64(const Leaf64 &f, uint32_t q, uint32_t k) {
+    for (;;) {
+        const uint64_t b = f.bits[q >> 6];
+        if (!((b >> (q & 63u)) & 1u)) return f.l1[q];
+        const uint32_t r = f.pre[q >> 6] + (uint32_t)__popcll(b & ((1ull << (q & 63u)) - 1ull));
+        const uint32_t wd = nib8(f.nib, f.ops0 + 8 * r), op = (wd >> (4 * k)) & 7u;
+        if (op == csv::kRp) return f.l1[q];
+        if (op <= csv::kRz) {
+            const uint32_t x = op - 1u, am = 0x1249u << x;
+            if ((k >> x) & 1u) return f.l1[morton_inc(q, am)];
+            q = morton_dec(q, am);
+            k |= 1u << x;
+            continue;
+        }
+        const uint32_t in = f.info[r], y = wd & 0x77777777u, below = (1u << (4 * k)) - 1u;
+        const uint32_t ip =
+            f.ipl + (in & (k64PalMax - 1u)) + (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u) & below);
+        if (op == csv::kP0) return ip;
+        if (op == csv::kPa) return ip + 1u;
+        const uint32_t d =
+            nib1(f.nib, f.seg + (in >> 14) + (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u) & below));
+        return ip - 1u - d;
+    }
+}
+
+__global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_eu(3))) void leaf64_kernel(DecodeArgs a,
+                                                                                                           Launch64 l) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    uint32_t *spal = reinterpret_cast<uint32_t *>(smem);
+    const uint32_t L = lane(), w = uniform(threadIdx.x >> 6);
+    uint8_t *wl = smem + 4 * k64PalLds + w * kV64Wave;
+    uint32_t *D32 = reinterpret_cast<uint32_t *>(wl);
+    uint16_t *D = reinterpret_cast<uint16_t *>(wl);
+    uint16_t *list = reinterpret_cast<uint16_t *>(wl + kV64List);
+    uint32_t *delta = reinterpret_cast<uint32_t *>(wl + kV64Delta);
+    uint16_t *out = reinterpret_cast<uint16_t *>(wl + kV64Out);
+    constexpr uint32_t kMark = 65533u;
+    // workgroups go to the 8 XCDs in turn: the 16 workgroups of a brick on
+    // the XCD of its upper workgroup, whose L2 holds the slot
+    const uint32_t g = blockIdx.x >> 3, rq = (g >> 4) * 8 + (blockIdx.x & 7u);
+    if (rq >= a.n) return;
+    const uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+    const Head64 *head = reinterpret_cast<const Head64 *>(slot + k64Head);
+    if (!ld_s(&head->leaf)) return;
+    const uint32_t P = ld_s(&head->P);
+    const uint32_t *pal = rec_at(ld_s(&head->pal));
+    uint32_t *dst = reinterpret_cast<uint32_t *>(ld_s(&head->dst));
+    Leaf64 f;
+    f.l1 = reinterpret_cast<const uint16_t *>(slot);
+    f.bits = reinterpret_cast<const uint64_t *>(slot + k64Bits);
+    f.pre = reinterpret_cast<const uint16_t *>(slot + k64Pre);
+    f.info = reinterpret_cast<const uint32_t *>(slot + k64Info);
+    f.nib = rec_at(ld_s(&head->nib));
+    f.ops0 = ld_s(&head->ops0);
+    f.seg = ld_s(&head->seg);
+    f.ipl = ld_s(&head->ipl);
+    const bool plds = P <= k64PalLds;
+    if (plds)
+        for (uint32_t e = threadIdx.x; e < P; e += 64 * k64LeafWaves) spal[e] = pal[e];
+    __syncthreads();
+    // the block: 16 x 8 x 4 parents, 2 x 4 x 8 of them in a brick
+    const uint32_t blk = (g & 15u) * k64LeafWaves + w;
+    const uint32_t PX = 16 * (blk & 1u), PY = 8 * ((blk >> 1) & 3u), PZ = 4 * (blk >> 3);
+    const uint32_t lx = coord5(L), ly = coord5(L >> 1), lz = coord5(L >> 2);  // of a parent in its word (0 .. 3)
+    // every voxel its parent's value; the expanded parents listed
+    uint32_t E = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 8; j++) {
+        const uint32_t wx = j & 3u, wy = j >> 2;
+        const uint32_t word = spread5((PX >> 2) + wx) | (spread5((PY >> 2) + wy) << 1) | (spread5(PZ >> 2) << 2);
+        const uint64_t b = ld_s(f.bits + word);
+        const uint32_t pv = f.l1[64 * word + L] * 0x00010001u;
+        const uint32_t d = v64_dw(2 * (4 * wx + lx), 2 * (4 * wy + ly), 2 * lz);  // (the rows y and y + 1 share it)
+        D32[d] = pv;
+        D32[d + 16] = pv;
+        D32[d + kV64Plane] = pv;
+        D32[d + kV64Plane + 16] = pv;
+        if ((b >> L) & 1u) list[E + mbcnt(b)] = (uint16_t)(64 * j + L);
+        if (L == 0) delta[j] = ld_s_u16(f.pre + word) - E;
+        E += (uint32_t)__popcll(b);
+    }
+    wsync();
+    // the children of the expanded parents
+    uint32_t nout = 0;
+    for (uint32_t c = 0; c < (E + 63) / 64; c++) {
+        const uint32_t pos = 64 * c + L;
+        const bool act = pos < E;
+        const uint32_t idx = act ? (uint32_t)list[pos] : 0u, j = idx >> 6, i = idx & 63u;
+        const uint32_t bx = 4 * (j & 3u) + coord5(i), by = 4 * (j >> 2) + coord5(i >> 1), bz = coord5(i >> 2);
+        const uint32_t q = spread5(PX + bx) | (spread5(PY + by) << 1) | (spread5(PZ + bz) << 2);
+        uint32_t open = 0, v0 = 0;
+        if (act) {
+            const uint32_t r = pos + delta[j], wd = nib8(f.nib, f.ops0 + 8 * r), in = f.info[r];
+            uint32_t nb[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const uint32_t am = 0x1249u << x;
+                nb[x] = (q & am) != am ? (uint32_t)f.l1[morton_inc(q, am)] : 0u;
+            }
+            uint32_t pam, pdm, exm, cnt;
+            nibble_counts(wd, true, pam, pdm, exm, cnt);
+            bool bad = false;  // (the upper kernel has checked the level)
+            const uint4 v = replay_children<uint16_t>(wd, f.l1[q], nb, 7u, 7u, f.ipl + (in & (k64PalMax - 1u)),
+                                                      compact_nibble_bits(pam), compact_nibble_bits(pdm), f.nib,
+                                                      f.seg + (in >> 14), P, true, bad);
+            const uint32_t d = v64_dw(2 * bx, 2 * by, 2 * bz);
+            D32[d] = v.x;
+            D32[d + 16] = v.y;
+            D32[d + kV64Plane] = v.z;
+            D32[d + kV64Plane + 16] = v.w;
+            // references to a node of another block (children at 0 on the axis)
+            open = ref_children(wd, (bx == 0 ? 1u : 0u) | (by == 0 ? 2u : 0u) | (bz == 0 ? 4u : 0u));
+            v0 = 2 * bx + 64 * by + 1024 * bz;  // x + 32 y + 512 z
+        }
+        for (uint64_t m; (m = __ballot(open != 0)) != 0;) {
+            if (open) {
+                const uint32_t k = (uint32_t)__builtin_ctz(open) >> 2, at = nout + mbcnt(m);
+                open &= open - 1u;
+                if (at < kV64OutCap) out[at] = (uint16_t)(v0 + (k & 1u) + 32 * ((k >> 1) & 1u) + 512 * (k >> 2));
+            }
+            nout += (uint32_t)__popcll(m);
+        }
+    }
+    wsync();
+    // a voxel's value: references followed inside the block, and out of it on
+    // the other block's operations
+    auto at = [&](uint32_t x, uint32_t y, uint32_t z) -> uint32_t { return 2 * v64_dw(x & ~1u, y, z) + (x & 1u); };
+    auto chase = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t v) -> uint32_t {
+        while (v >= kMark) {
+            const uint32_t ax = v - kMark;
+            const uint32_t c = ax == 0 ? x : ax == 1 ? y : z;
+            if (c == 0) {
+                const uint32_t q = spread5(PX + (x >> 1)) | (spread5(PY + (y >> 1)) << 1) | (spread5(PZ + (z >> 1)) << 2);
+                return eval64(f, morton_dec(q, 0x1249u << ax), (x & 1u) | ((y & 1u) << 1) | ((z & 1u) << 2) | (1u << ax));
+            }
+            x -= ax == 0 ? 1u : 0u;
+            y -= ax == 1 ? 1u : 0u;
+            z -= ax == 2 ? 1u : 0u;
+            v = D[at(x, y, z)];
+        }
+        return v;
+    };
+    for (uint32_t e = L; e < min(nout, kV64OutCap); e += 64) {
+        const uint32_t v = out[e], x = v & 31u, y = (v >> 5) & 15u, z = v >> 9, p = at(x, y, z);
+        D[p] = (uint16_t)chase(x, y, z, D[p]);
+    }
+    wsync();
+    const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+    dst += 2 * PX + 128 * PY + 8192 * PZ;
+    for (uint32_t c = 0; c < 16; c++) {
+        const uint32_t x = 4 * (L & 7u), y = (L >> 3) + 8 * (c & 1u), z = c >> 1;
+        const uint2 v = *reinterpret_cast<const uint2 *>(D32 + v64_dw(x, y, z));
+        uint32_t idx[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
+        if (max(max(idx[0], idx[1]), max(idx[2], idx[3])) >= kMark) {
+#pragma unroll
+            for (uint32_t b = 0; b < 4; b++)
+                if (idx[b] >= kMark) idx[b] = chase(x + b, y, z, idx[b]);
+        }
+        const uint4 o = plds ? make_uint4(spal[idx[0]], spal[idx[1]], spal[idx[2]], spal[idx[3]])
+                             : make_uint4(pal[idx[0]], pal[idx[1]], pal[idx[2]], pal[idx[3]]);
+        uint32_t *to = dst + x + 64 * y + 4096 * z;
+        if (al) store4<true>(to, o);
+        else store4<false>(to, o);
+    }
+}

@@ -323,14 +323,15 @@ enum ReqKind { kReqBadLod, kReqBadId, kReqCorrupt, kReqFill, kReqDecode };
 
 // A brick of edge 32 >> SH has the levels SH .. 5 of a 32^3 brick: its level
 // t is level t + SH here, in Hdr::t, in Hdr::c() and in every function of
-// the replay, and its finest level is level SH.
+// the replay, and its finest level is level SH.  (SH = -1, edge 64: the
+// entropy decode only, with c0 the symbols before the finest segment.)
 template <int SH>
 constexpr uint32_t header_words() { return csv::record_header_words(kLog2 - SH); }
 
 // symbols before the segment of the finest level (coded with the other table)
 template <int SH>
 __device__ __forceinline__ uint32_t leaf_start(const Hdr &h) {
-    return SH == 0 ? h.c1 : SH == 1 ? h.c2 : SH == 2 ? h.c3 : SH == 3 ? h.c4 : 0u;
+    return SH < 0 ? h.c0 : SH == 0 ? h.c1 : SH == 1 ? h.c2 : SH == 2 ? h.c3 : SH == 3 ? h.c4 : 0u;
 }
 
 // read and check request rq; for kReqFill, fill is the value of every output label
@@ -2038,6 +2039,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kSlow ?
     }
 }
 
+#include "csv_brick64.hpp"
+
 // Longest-first request order: requests are binned by their work (symbols
 // to decode plus output voxels / 8) on a log scale with 8 bins per octave
 // (the bits after the leading one), largest first; the order within a bin
@@ -2281,6 +2284,7 @@ struct csv_pool {
     uint8_t *d_vol_raw = nullptr;
     uint64_t use_clock = 0;
     uint32_t max_c0 = 0;                      // most symbols of any brick in the pool
+    uint32_t max_pal64 = 0;                   // largest palette of a 64^3 brick
     uint32_t max_fast_bytes = 0;              // largest LDS arena a brick of the pool needs (nibbles not staged)
     bool any_big_palette = false;
     uint64_t hbm_budget = 0;                  // HBM the pool may hold (0: no limit)
@@ -2579,7 +2583,9 @@ DecodeArgs decode_args(const csv_pool *pool, const uint32_t *ids, const uint8_t 
 // A decode on a pool of bricks of another edge than 32 (pool->mu held).
 // Edges 2..16: the front kernel alone, one wave per brick, the wave's slot
 // in the scratch of the stream's buffer set (packed nibbles, then the u16
-// levels of big palettes).  Edge 64: the generic decoder.
+// levels of big palettes).  Edge 64: the kernels of csv_brick64.hpp, or,
+// when a brick of the pool has a palette of k64PalMax entries or more, the
+// generic decoder (its u32 levels hold any palette).
 int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_t lod_scalar,
                  const uint64_t *out_off, uint32_t n, uint32_t *out, hipStream_t s, bool plain, int *req_err,
                  uint32_t rq_base) {
@@ -2620,9 +2626,49 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
         }
         return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
     }
-    // 8 workgroups per CU (few registers and 112 bytes of LDS each), 4 for
-    // 64^3 bricks (1.9 MB of scratch per workgroup)
-    const uint32_t groups = plain ? 1u : std::min(n, (pool->brick_log2 >= 6 ? 4u : 8u) * cu);
+    if (pool->max_pal64 < k64PalMax) {
+        bool rans = false;
+        for (uint8_t r : pool->vol_raw) rans = rans || !r;
+        Launch64 l{};
+        l.nib_off = (k64Info + 4 * (pool->max_c0 / 8 + 16) + 255u) & ~255u;
+        l.nib_dw = rans ? slot_dw(pool) : 0u;
+        l.slot_bytes = (l.nib_off + 4ull * l.nib_dw + 255u) & ~255ull;
+        l.lut_lds_words = lut_lds_words(pool);
+        const uint32_t lds_e = align16(4 * l.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
+        const uint32_t lds_l = 4 * k64PalLds + (uint32_t)k64LeafWaves * kV64Wave;
+        static std::once_flag once;
+        std::call_once(once, [] {
+            (void)set_lds_attr(entropy64_kernel<true>);
+            (void)set_lds_attr(entropy64_kernel<false>);
+            (void)set_lds_attr(upper64_kernel);
+            (void)set_lds_attr(leaf64_kernel);
+        });
+        // slots for 4 requests per CU at most (0.2 to 0.5 MB each)
+        const uint32_t per = plain ? 1u : std::min(n, 4u * cu);
+        const int rc = generic_bufs(pool, s, l.slot_bytes * per, &G);
+        if (rc) return rc;
+        l.slots = G->gen;
+        const uint64_t g = 64u >> (lods ? 0u : lod_scalar), cnt = lods ? 0 : g * g * g;
+        for (uint32_t at = 0; at < n; at += per) {
+            const uint32_t m = std::min(per, n - at);
+            const DecodeArgs a = decode_args(pool, ids + at, lods ? lods + at : nullptr, lod_scalar,
+                                             out_off ? out_off + at : nullptr, m, out_off ? out : out + at * cnt,
+                                             req_err ? req_err + at : nullptr, rq_base + at);
+            if (rans) {
+                const uint32_t ge = (m + kWavesGen - 1) / kWavesGen;
+                if (l.lut_lds_words)
+                    hipLaunchKernelGGL(entropy64_kernel<true>, dim3(ge), dim3(64 * kWavesGen), lds_e, s, a, l);
+                else
+                    hipLaunchKernelGGL(entropy64_kernel<false>, dim3(ge), dim3(64 * kWavesGen), lds_e, s, a, l);
+            }
+            hipLaunchKernelGGL(upper64_kernel, dim3(std::min(m, 2 * cu)), dim3(k64Threads), kU64Lds, s, a, l);
+            if (lods || lod_scalar == 0)
+                hipLaunchKernelGGL(leaf64_kernel, dim3(((m + 7) / 8) * 128), dim3(64 * k64LeafWaves), lds_l, s, a, l);
+        }
+        return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
+    }
+    // 4 workgroups per CU (1.9 MB of scratch per workgroup)
+    const uint32_t groups = plain ? 1u : std::min(n, 4u * cu);
     csv::GenericArgs ga{};
     ga.sym_cap = pool->max_c0 + 16;
     ga.scratch_per_group = csv::generic_scratch_bytes(pool->brick_log2, ga.sym_cap);
@@ -3068,13 +3114,14 @@ int csv_pool_add_volume(csv_pool *p, const uint8_t *blob, size_t blob_bytes, uin
     DeviceGuard g(p->device);
     const uint64_t rs = csv::record_area_offset(info.n_bricks);
     const uint64_t *index = reinterpret_cast<const uint64_t *>(blob + csv::kHeaderBytes);
-    uint32_t max_fast = p->max_fast_bytes, max_c0 = p->max_c0;
+    uint32_t max_fast = p->max_fast_bytes, max_c0 = p->max_c0, max_p64 = p->max_pal64;
     bool big = p->any_big_palette;
     for (uint32_t i = 0; i < info.n_bricks; i++) {
         const uint32_t *w = reinterpret_cast<const uint32_t *>(blob + rs + index[i]);
         const uint32_t P = w[0], c0 = w[3];
         if (c0 == 0) continue;
         max_c0 = std::max(max_c0, c0);
+        if (info.brick_log2 == (uint32_t)kLog2 + 1) max_p64 = std::max(max_p64, P);
         if (info.brick_log2 != (uint32_t)kLog2) continue;
         const uint32_t c1 = w[4];
         big |= P > kPalFast;
@@ -3095,6 +3142,7 @@ int csv_pool_add_volume(csv_pool *p, const uint8_t *blob, size_t blob_bytes, uin
     (void)hipDeviceSynchronize();
     p->max_c0 = max_c0;
     p->max_fast_bytes = max_fast;
+    p->max_pal64 = max_p64;
     p->any_big_palette = big;
     p->brick_log2 = info.brick_log2;
     p->generic = p->generic || gen;
