@@ -96,6 +96,80 @@ __device__ __forceinline__ uint32_t coord5(uint32_t p) {
     return (p & 1u) | ((p >> 2) & 2u) | ((p >> 4) & 4u) | ((p >> 6) & 8u) | ((p >> 8) & 16u);
 }
 
+// Children of one expanded parent (its 8 nibbles wd) as u16 indices: pv the
+// parent's index, nb the parent level's +1 neighbours, ipb the palette
+// position before the first child, pam / pdm its P_a / P_delta children
+// (bit 4k), dl its deltas.  As replay_children_u8, with low and high bytes
+// selected apart and then paired; nothing is checked here.
+__device__ __forceinline__ uint4 replay_children_u16(uint32_t wd, uint32_t pv, const uint32_t nb[3], uint32_t ipb,
+                                                     uint32_t pam, uint32_t pdm, uint32_t dl) {
+    auto perm = [](uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); };
+    // selector bytes (child_selectors): marks 0..2, parent 4, neighbours 5..7, zero 12
+    const uint32_t ye = wd & 0x07070707u, yo = (wd >> 4) & 0x07070707u;
+    const uint32_t be = perm(0x0C0C0C0Cu, 0x02010004u, ye), bo = perm(0x0C0C0C0Cu, 0x02010004u, yo);
+    const uint32_t f2e = perm(0u, 0x00050000u, ye), f3e = perm(0u, 0x05000000u, ye);
+    const uint32_t f1o = perm(0u, 0x00000500u, yo), f2o = perm(0u, 0x00050000u, yo), f3o = perm(0u, 0x05000000u, yo);
+    const uint32_t se = be + ((f2e & 0xFF00FF00u) | (f3e & 0xFFFF0000u));
+    const uint32_t so = bo + (f1o | (f2o & 0xFF00FF00u) | (f3o & 0xFFFF0000u));
+    const uint32_t sel_lo = perm(so, se, 0x05010400u), sel_hi = perm(so, se, 0x07030602u);
+    // low and high bytes of {parent, neighbours}; the marks are 0xFFFD .. 0xFFFF
+    const uint32_t t01 = perm(nb[0], pv, 0x05010400u), t23 = perm(nb[2], nb[1], 0x05010400u);
+    const uint32_t cl = perm(t23, t01, 0x05040100u), ch = perm(t23, t01, 0x07060302u);
+    const uint32_t l0 = perm(cl, 0x00FFFEFDu, sel_lo), h0 = perm(ch, 0x00FFFFFFu, sel_lo);
+    const uint32_t l1 = perm(cl, 0x00FFFEFDu, sel_hi), h1 = perm(ch, 0x00FFFFFFu, sel_hi);
+    // palette positions after the parent's first one: P_a children so far
+    // (itself included), on the P operations' bytes
+    const uint32_t y = wd & 0x77777777u, wp = (y >> 2) & 0x11111111u;
+    const uint32_t pa0 = nib_to_bytes(pam), pa1 = nib_to_bytes(pam >> 16), pb0 = nib_to_bytes(wp),
+                   pb1 = nib_to_bytes(wp >> 16);
+    const uint32_t m0 = (pb0 << 8) - pb0, m1 = (pb1 << 8) - pb1;
+    const uint32_t c0 = pa0 * 0x01010101u, c1 = pa1 * 0x01010101u + (c0 >> 24) * 0x01010101u;
+    const uint32_t p0 = c0 & m0, p1 = c1 & m1, ip2 = ipb * 0x00010001u;
+    uint4 v;
+    v.x = perm(h0, l0, 0x05010400u) + perm(0u, p0, 0x0C010C00u) + (ip2 & perm(0u, m0, 0x01010000u));
+    v.y = perm(h0, l0, 0x07030602u) + perm(0u, p0, 0x0C030C02u) + (ip2 & perm(0u, m0, 0x03030202u));
+    v.z = perm(h1, l1, 0x05010400u) + perm(0u, p1, 0x0C010C00u) + (ip2 & perm(0u, m1, 0x01010000u));
+    v.w = perm(h1, l1, 0x07030602u) + perm(0u, p1, 0x0C030C02u) + (ip2 & perm(0u, m1, 0x03030202u));
+    while (pdm) {  // delta d: the entry d + 1 before
+        const uint32_t k4 = (uint32_t)__builtin_ctz(pdm), j = k4 >> 3;
+        const uint32_t sub = ((dl & 15u) + 1u) << (4 * (k4 & 4u));
+        pdm &= pdm - 1u;
+        dl >>= 4;
+        v.x -= j == 0 ? sub : 0u;
+        v.y -= j == 1 ? sub : 0u;
+        v.z -= j == 2 ? sub : 0u;
+        v.w -= j == 3 ? sub : 0u;
+    }
+    return v;
+}
+// nibbles of wd whose reference leaves the brick: q on a low or high face of
+// the grid with axis mask pm
+__device__ __forceinline__ uint32_t leaving(uint32_t wd, uint32_t q, uint32_t pm) {
+    const uint32_t y = wd & 0x77777777u;
+    uint32_t out = 0;
+#pragma unroll
+    for (int x = 0; x < 3; x++) {
+        const uint32_t side = x == 0 ? 0x01010101u : x == 1 ? 0x00110011u : 0x00001111u;  // children at 0 on the axis
+        const uint32_t am = pm << x, v = q & am;
+        const uint32_t face = (v == 0 ? side : 0u) | (v == am ? 0x11111111u ^ side : 0u);
+        out |= zero_nibbles(y ^ (0x11111111u * (uint32_t)(x + 1))) & face;
+    }
+    return out;
+}
+
+// a delta past the first palette entry (dl: the deltas of the P_delta
+// children pdm); positions from 16 on hold any
+__device__ __forceinline__ bool short_delta(uint32_t ipb, uint32_t pam, uint32_t pdm, uint32_t dl) {
+    bool bad = false;
+    if (ipb < 16u)
+        for (; pdm; dl >>= 4) {
+            const uint32_t k4 = (uint32_t)__builtin_ctz(pdm);
+            pdm &= pdm - 1u;
+            bad |= ipb + (uint32_t)__builtin_popcount(pam & ((1u << k4) - 1u)) < (dl & 15u) + 1u;
+        }
+    return bad;
+}
+
 // One wave per rANS request; a serial chain of c_t / 64 steps (a brick of
 // the 512^3 cells volume has 100,000 symbols), so a launch of 512 bricks is
 // bound by that chain's latency, not by the machine.
@@ -151,8 +225,12 @@ __device__ constexpr uint32_t k64Bm[7] = {0, 0, 512, 576, 584, 585, 586};  // wo
 constexpr uint32_t kU64L1 = 2 * 4688, kU64Bm = kU64L1 + 65536, kU64Pre = kU64Bm + 8 * 588, kU64Sm = kU64Pre + 1024,
                    kU64Lds = kU64Sm + 96;
 
-// What bounds it: latency (a chain of six levels with a few barriers each,
-// at the two workgroups per CU that 80 KB of LDS allow).
+// What bounds it: latency (a chain of six levels with a few barriers and
+// dependent loads each, at the two workgroups per CU that 80 KB of LDS
+// allow) and vector issue (6.6 k wave-instructions per wave, half of the
+// time).  512 bricks of the 512^3 cells volume take 82 us; with a lane per
+// parent instead of per expanded parent, the counts of level 0 scanned 64 at
+// a time and deltas read child by child it was 118 us.
 __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4))) void upper64_kernel(DecodeArgs a,
                                                                                                    Launch64 l) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -201,10 +279,35 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
         bool ok = true;
         __syncthreads();
         if (*bad) ok = false;
-        // child level m from the 8^(5 - m) nodes of level m + 1: wave w takes
-        // K words of 64 parents from word w K on, a lane per parent
-        auto level = [&](int m, uint32_t K, uint32_t seg, uint32_t seg_end) __attribute__((always_inline)) -> bool {
-            const uint32_t Bp = (uint32_t)(5 - m), np = 1u << (3 * Bp), nw = np < 64 ? 1u : np / 64;
+        // node of rank r among the expanded nodes whose bits are pb and
+        // whose counts before each of 2^lw words are pre: the word by binary
+        // search, the bit by halving
+        auto node_of = [&](const uint64_t *pb, uint32_t lw, uint32_t r) -> uint32_t {
+            uint32_t word = 0;
+            for (uint32_t h = (1u << lw) >> 1; h; h >>= 1) word += pre[word + h] <= r ? h : 0u;
+            const uint64_t b = pb[word];
+            uint32_t n = r - pre[word], pos = 0, x = (uint32_t)b;
+            const uint32_t c = (uint32_t)__builtin_popcount(x);
+            if (n >= c) {
+                n -= c;
+                pos = 32;
+                x = (uint32_t)(b >> 32);
+            }
+#pragma unroll
+            for (uint32_t h = 16; h; h >>= 1) {
+                const uint32_t k = (uint32_t)__builtin_popcount(x & ((1u << h) - 1u));
+                const bool up = n >= k;
+                n -= up ? k : 0u;
+                pos += up ? h : 0u;
+                x = up ? x >> h : x;
+            }
+            return 64 * word + pos;
+        };
+        // child level m from the 8^(5 - m) nodes of level m + 1.  The
+        // expanded ones go to the waves in runs of chunks of 64, so that no
+        // lane idles at nodes that are not (two of three in the cells volume).
+        auto level = [&](uint32_t m, uint32_t seg, uint32_t seg_end) __attribute__((always_inline)) -> bool {
+            const uint32_t Bp = 5 - m, np = 1u << (3 * Bp), lw = Bp > 2 ? 3 * Bp - 6 : 0u, nw = 1u << lw;
             const uint64_t *pb = bmw + k64Bm[m + 1];
             const uint16_t *up = lv + k64Lv[m + 1];
             uint16_t *cur = m == 1 ? l1 : lv + k64Lv[m];
@@ -215,20 +318,22 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
                 pre[L] = (uint16_t)(inc - c);
                 if (L == 63) *tot = inc;
             }
+            // every child its parent's value; those of expanded nodes are
+            // overwritten below
+            for (uint32_t q = tid; q < np; q += k64Threads) {
+                *reinterpret_cast<typename V::T *>(cur + 8 * q) = V::splat(up[q]);
+                cb[q] = 0;
+            }
             __syncthreads();
             const uint32_t E = *tot;
             if ((uint64_t)seg + 8ull * E > seg_end) return false;
             const uint32_t D = seg_end - seg - 8 * E, ops0 = seg + D;  // deltas precede the operations
-            auto ops_of = [&](uint32_t j, uint64_t &b) -> uint32_t {  // the lane's operations (0: not expanded)
-                const uint32_t word = w * K + j;
-                b = word < nw ? pb[word] : 0ull;
-                return ((b >> L) & 1u) ? nib8(nib, ops0 + 8 * (pre[word & 511u] + mbcnt(b))) : 0u;
-            };
+            const uint32_t nch = (E + 63) / 64, cpw = (nch + k64Waves - 1) / k64Waves;
+            const uint32_t c0 = min(w * cpw, nch), c1 = min(c0 + cpw, nch);
             uint32_t sum = 0;
 #pragma unroll 4
-            for (uint32_t j = 0; j < K; j++) {
-                uint64_t b;
-                const uint32_t y = ops_of(j, b) & 0x77777777u;
+            for (uint32_t c = c0; c < c1; c++) {
+                const uint32_t r = 64 * c + L, y = (r < E ? nib8(nib, ops0 + 8 * r) : 0u) & 0x77777777u;
                 sum += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u)) |
                        ((uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u)) << 16);
             }
@@ -248,36 +353,31 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
             }
             if (tpd != D) return false;
             const uint32_t pm = axis_mask(0, Bp);
-            bool wrong = false;
+            bool wrong = ipl + tpa >= P;  // the last new palette entry
 #pragma unroll 1
-            for (uint32_t j = 0; j < K; j++) {
-                const uint32_t q = 64 * (w * K + j) + L;
-                uint64_t b;
-                const uint32_t wd = ops_of(j, b);
-                const bool act = (b >> L) & 1u;
+            for (uint32_t c = c0; c < c1; c++) {
+                const uint32_t r = 64 * c + L;
+                const bool act = r < E;
+                const uint32_t wd = act ? nib8(nib, ops0 + 8 * r) : 0u;
                 uint32_t pam, pdm, exm, cnt;
                 nibble_counts(wd, act, pam, pdm, exm, cnt);
                 const uint32_t inc = wave_incl_scan(cnt & 0xFFFFFu), exc = inc - (cnt & 0xFFFFFu);
                 const uint32_t all = uniform(__builtin_amdgcn_readlane(inc, 63));
-                if (q < np) {
-                    const uint32_t pv = up[q];
-                    typename V::T vals = V::splat(pv);
-                    if (act) {
-                        uint32_t nb[3], nbok = 0, lowok = 0;
+                if (act) {
+                    const uint32_t dl = pdm ? nib8(nib, seg + bpd + (exc >> 10)) : 0u;
+                    const uint32_t q = node_of(pb, lw, r);
+                    uint32_t nb[3];
 #pragma unroll
-                        for (int x = 0; x < 3; x++) {
-                            const uint32_t am = pm << x;
-                            const bool hi = (q & am) != am;
-                            nb[x] = hi ? (uint32_t)up[morton_inc(q, am)] : 0u;
-                            nbok |= hi ? (1u << x) : 0u;
-                            lowok |= (q & am) ? (1u << x) : 0u;
-                        }
-                        vals = replay_children<uint16_t>(wd, pv, nb, nbok, lowok, ipl + bpa + (exc & 1023u),
-                                                         compact_nibble_bits(pam), compact_nibble_bits(pdm), nib,
-                                                         seg + bpd + (exc >> 10), P, false, wrong);
+                    for (int x = 0; x < 3; x++) {  // (on a high face: any value)
+                        const uint32_t am = pm << x;
+                        nb[x] = up[morton_inc(q, am)];
                     }
-                    *reinterpret_cast<typename V::T *>(cur + 8 * q) = vals;
-                    cb[q] = act ? (uint8_t)compact_nibble_bits(exm) : 0;
+                    const uint32_t ipb = ipl + bpa + (exc & 1023u);
+                    *reinterpret_cast<typename V::T *>(cur + 8 * q) =
+                        replay_children_u16(wd, up[q], nb, ipb, pam, pdm, dl);
+                    cb[q] = (uint8_t)compact_nibble_bits(exm);
+                    wrong |= leaving(wd, q, pm) != 0 || zero_nibbles((wd & 0x77777777u) ^ 0x77777777u) != 0 ||
+                             short_delta(ipb, pam, pdm, dl);
                 }
                 bpa += all & 1023u;
                 bpd += all >> 10;
@@ -289,16 +389,14 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
             // values (at most three links; a reader sees a reference or its
             // final value, and both lead to the value)
 #pragma unroll 1
-            for (uint32_t j = 0; j < K; j++) {
-                const uint32_t word = w * K + j, q = 64 * word + L;
-                const uint64_t b = word < nw ? pb[word] : 0ull;
-                if (!((b >> L) & 1u)) continue;
-                const typename V::T vals = *reinterpret_cast<const typename V::T *>(cur + 8 * q);
-                uint32_t open = 0;
-#pragma unroll
-                for (int k = 0; k < 7; k++) open |= V::get(vals, k) >= kMark ? 1u << k : 0u;
+            for (uint32_t c = c0; c < c1; c++) {
+                const uint32_t r = 64 * c + L;
+                if (r >= E) continue;
+                const uint32_t wd = nib8(nib, ops0 + 8 * r);
+                uint32_t open = ref_children(wd, 7u);
+                const uint32_t q = node_of(pb, lw, r);
                 while (open) {
-                    uint32_t kk = (uint32_t)__builtin_ctz(open), qq = q;
+                    uint32_t kk = (uint32_t)__builtin_ctz(open) >> 2, qq = q;
                     const uint32_t at = 8 * q + kk;
                     open &= open - 1u;
                     uint32_t v = cur[at];
@@ -320,7 +418,7 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
             return m == 5 ? h.c[5] : m == 4 ? h.c[4] : m == 3 ? h.c[3] : m == 2 ? h.c[2] : m == 1 ? h.c[1] : 0u;
         };
 #pragma unroll 1
-        for (uint32_t m = 5; ok && m >= tl; m--) ok = level((int)m, m == 1 ? 8u : 1u, cum(m + 1), cum(m));
+        for (uint32_t m = 5; ok && m >= tl; m--) ok = level(m, cum(m + 1), cum(m));
         const uint32_t *pal = h.rec + hdr;
         if (ok && t >= 1) {  // level t to the output (every index has been checked against P)
             const uint32_t lg = 6 - t, G = 1u << lg;
@@ -358,25 +456,35 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
             ok = (uint64_t)seg + 8ull * E <= seg_end;
             if (ok) {
                 // per expanded node the P_a and P_delta operations before it:
-                // a wave takes a run of nodes in stream order, its totals
-                // first.  The same operations are checked: no stop bit, no
-                // code 7, deltas and palette positions in range.
+                // a wave takes a run of nodes in stream order, 512 at a time
+                // (8 per lane, one scan), its totals first.  The operations
+                // are checked: no stop bit, no code 7, deltas and palette
+                // positions in range.
                 const uint32_t D = seg_end - seg - 8 * E;
                 ops0 = seg + D;
-                const uint32_t nch = (E + 63) / 64, cpw = (nch + k64Waves - 1) / k64Waves;
+                const uint32_t nch = (E + 511) / 512, cpw = (nch + k64Waves - 1) / k64Waves;
                 const uint32_t cb = min(w * cpw, nch), ce = min(cb + cpw, nch);
-                uint32_t spa = 0, spd = 0;
+                // node r's operations (none past the end); P_a | P_delta << 16
+                auto ops_at = [&](uint32_t r) -> uint32_t { return r < E ? nib8(nib, ops0 + 8 * r) : 0u; };
+                auto counts = [&](uint32_t wd) -> uint32_t {
+                    const uint32_t y = wd & 0x77777777u;
+                    return (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u)) |
+                           ((uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u)) << 16);
+                };
+                uint32_t sum = 0;
                 bool wrong = false;
-#pragma unroll 4
                 for (uint32_t ch = cb; ch < ce; ch++) {
-                    const uint32_t r = 64 * ch + L;
-                    const uint32_t wd = r < E ? nib8(nib, ops0 + 8 * r) : 0u, y = wd & 0x77777777u;
-                    spa += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x66666666u));
-                    spd += (uint32_t)__builtin_popcount(zero_nibbles(y ^ 0x55555555u));
-                    wrong |= (wd & 0x88888888u) != 0 || zero_nibbles(y ^ 0x77777777u) != 0;
+                    uint32_t part = 0;
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; k++) {
+                        const uint32_t wd = ops_at(512 * ch + 64 * k + L);
+                        part += counts(wd);
+                        wrong |= (wd & 0x88888888u) != 0 || zero_nibbles((wd & 0x77777777u) ^ 0x77777777u) != 0;
+                    }
+                    sum += part;
                 }
-                spa = uniform(__builtin_amdgcn_readlane(wave_incl_scan(spa), 63));
-                spd = uniform(__builtin_amdgcn_readlane(wave_incl_scan(spd), 63));
+                uint32_t spa = uniform(__builtin_amdgcn_readlane(wave_incl_scan(sum & 0xFFFFu), 63));
+                uint32_t spd = uniform(__builtin_amdgcn_readlane(wave_incl_scan(sum >> 16), 63));
                 if (L == 0) {
                     wt[2 * w] = spa;
                     wt[2 * w + 1] = spd;
@@ -397,45 +505,48 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
                 if (ok) {
                     uint32_t *info = reinterpret_cast<uint32_t *>(slot + k64Info);
                     for (uint32_t ch = cb; ch < ce; ch++) {
-                        const uint32_t r = 64 * ch + L;
-                        const bool act = r < E;
-                        const uint32_t wd = act ? nib8(nib, ops0 + 8 * r) : 0u;
-                        uint32_t pam, pdm, exm, cnt;
-                        nibble_counts(wd, act, pam, pdm, exm, cnt);
-                        const uint32_t inc2 = wave_incl_scan(cnt & 0xFFFFFu), exc = inc2 - (cnt & 0xFFFFFu);
-                        const uint32_t all = uniform(__builtin_amdgcn_readlane(inc2, 63));
-                        const uint32_t pa = bpa + (exc & 1023u);
-                        uint32_t pd = bpd + (exc >> 10);
-                        if (act) info[r] = pa | (pd << 14);
-                        while (pdm) {  // delta d names the entry d + 1 before the last one used
-                            const uint32_t k4 = (uint32_t)__builtin_ctz(pdm);
-                            pdm &= pdm - 1u;
-                            const uint32_t ip =
-                                ipl + pa + (uint32_t)__builtin_popcount(pam & ((1u << k4) - 1u));
-                            wrong |= ip < nib1(nib, seg + pd) + 1u;
-                            pd++;
-                        }
-                        bpa += all & 1023u;
-                        bpd += all >> 10;
-                    }
-                    // references of nodes on the brick's faces must stay inside
-                    for (uint32_t word = w; word < 512; word += k64Waves) {
-                        const uint32_t q = 64 * word + L;
-                        const uint64_t b = b1[word];
-                        const uint32_t side[3] = {0x01010101u, 0x00110011u, 0x00001111u};  // children at 0 on the axis
-                        uint32_t face[3];  // nibbles whose reference along the axis would leave the brick
-                        bool any = false;
+                        const uint32_t r0 = 512 * ch + 8 * L;
+                        uint32_t cnt[8], part = 0;
 #pragma unroll
-                        for (int x = 0; x < 3; x++) {
-                            const uint32_t am = 0x1249u << x, v = q & am;
-                            face[x] = (v == 0 ? side[x] : 0u) | (v == am ? 0x11111111u ^ side[x] : 0u);
-                            any |= face[x] != 0;
+                        for (uint32_t k = 0; k < 8; k++) {
+                            const uint32_t c = counts(ops_at(r0 + k));
+                            cnt[k] = part;
+                            part += c;
                         }
-                        if (!__ballot(any && ((b >> L) & 1u))) continue;
-                        if (any && ((b >> L) & 1u)) {
-                            const uint32_t y = nib8(nib, ops0 + 8 * (pre[word] + mbcnt(b))) & 0x77777777u;
-                            wrong |= ((zero_nibbles(y ^ 0x11111111u) & face[0]) | (zero_nibbles(y ^ 0x22222222u) & face[1]) |
-                                      (zero_nibbles(y ^ 0x33333333u) & face[2])) != 0;
+                        const uint32_t inc = wave_incl_scan(part), exc = inc - part;
+                        const uint32_t all = uniform(__builtin_amdgcn_readlane(inc, 63));
+                        uint32_t o[8];
+#pragma unroll
+                        for (uint32_t k = 0; k < 8; k++) {
+                            const uint32_t e = exc + cnt[k];
+                            o[k] = (bpa + (e & 0xFFFFu)) | ((bpd + (e >> 16)) << 14);
+                        }
+                        // (the slot has room for whole groups of 8)
+                        if (r0 < E) {
+                            reinterpret_cast<uint4 *>(info + r0)[0] = make_uint4(o[0], o[1], o[2], o[3]);
+                            reinterpret_cast<uint4 *>(info + r0)[1] = make_uint4(o[4], o[5], o[6], o[7]);
+                        }
+                        if (ipl + bpa < 16u)
+                            for (uint32_t k = 0; k < 8; k++) {
+                                const uint32_t wd = ops_at(r0 + k), y = wd & 0x77777777u;
+                                const uint32_t in = o[k], pdm = zero_nibbles(y ^ 0x55555555u);
+                                if (pdm)
+                                    wrong |= short_delta(ipl + (in & (k64PalMax - 1u)), zero_nibbles(y ^ 0x66666666u),
+                                                         pdm, nib8(nib, seg + (in >> 14)));
+                            }
+                        bpa += all & 0xFFFFu;
+                        bpd += all >> 16;
+                    }
+                    // references of nodes on the brick's six faces must stay inside
+#pragma unroll 4
+                    for (uint32_t e = tid; e < 6 * 1024; e += k64Threads) {
+                        const uint32_t x = e >> 11, u = spread5(e & 31u), v = spread5((e >> 5) & 31u);
+                        const uint32_t am = 0x1249u << x, fixed = (e & 1024u) ? am : 0u;
+                        const uint32_t q = fixed | (x == 0 ? (u << 1) | (v << 2) : x == 1 ? u | (v << 2) : u | (v << 1));
+                        const uint64_t b = b1[q >> 6];
+                        if ((b >> (q & 63u)) & 1u) {
+                            const uint32_t r = pre[q >> 6] + (uint32_t)__popcll(b & ((1ull << (q & 63u)) - 1ull));
+                            wrong |= leaving(nib8(nib, ops0 + 8 * r), q, 0x1249u) != 0;
                         }
                     }
                 }
@@ -468,14 +579,18 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
     }
 }
 
-// LDS of a leaf wave: the block's 32 x 16 x 8 voxels as u16 (8 planes of 264
-// dwords), its expanded parents (word and lane), per word the rank of its
-// first one less its place in that list, voxels with a reference out of the
-// block
-constexpr uint32_t kV64Plane = 264, kV64List = 4 * 8 * kV64Plane, kV64Delta = kV64List + 1024, kV64Out = kV64Delta + 32,
-                   kV64OutCap = 256, kV64Wave = kV64Out + 2 * kV64OutCap;
-constexpr int k64LeafWaves = 4;
-constexpr uint32_t k64PalLds = 896;  // palette entries kept in LDS
+// A block of a leaf wave: 16 x 4 x 4 parents (4 words of 4 x 4 x 4), 32 x 8 x
+// 8 voxels.  5 KB of LDS per wave let 28 waves run on a CU; blocks of
+// twice the height issue 18 % fewer instructions, but at 12 waves per CU
+// took 216 us instead of 164 us (512 bricks of the 512^3 cells volume).
+constexpr uint32_t k64Words = 4, k64Blocks = 512 / k64Words;  // words of a block, blocks of a brick
+// LDS of a leaf wave: the block's voxels as u16 (planes of 8 rows of 16
+// dwords, plus 8), its expanded parents (word and lane), per word the rank of
+// its first parent less its place in that list, voxels with a reference
+constexpr uint32_t kV64Plane = 136, kV64List = 4 * 8 * kV64Plane, kV64Delta = kV64List + 256, kV64Ref = kV64Delta + 16,
+                   kV64RefCap = 192, kV64Wave = kV64Ref + 2 * kV64RefCap;
+constexpr uint32_t k64LeafWaves = 4;
+constexpr uint32_t k64PalLds = 752;  // palette entries kept in LDS
 
 // Dword of voxels (x, x + 1), x even, of a block row.  The exclusive or
 // spreads the four y-rows of parents that a store touches over the banks, the
@@ -483,7 +598,23 @@ constexpr uint32_t k64PalLds = 896;  // palette entries kept in LDS
 __device__ __forceinline__ uint32_t v64_dw(uint32_t x, uint32_t y, uint32_t z) {
     return kV64Plane * z + 16 * y + ((x >> 1) ^ (((y >> 1) & 3u) << 2));
 }
+// 2-bit coordinate of a parent in its word
+__device__ __forceinline__ uint32_t coord2(uint32_t p) { return (p & 1u) | ((p >> 2) & 2u); }
+// 4 * half H of q
+template <int H>
+__device__ __forceinline__ uint32_t half_x4(uint32_t q) {
+    uint32_t r;
+    __asm__("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_%c2"
+            : "=v"(r)
+            : "v"(q), "n"(H));
+    return r;
+}
 
+// What bounds the leaf kernel: vector issue (1,030 wave-instructions per
+// block, 80 % of its time) and the latency of its dependent gathers.  The 512
+// bricks take 144 us (3.8 TB/s of labels written).  Before, 338 us: children
+// one at a time with a delta load each, references followed in the output
+// loop, 12 waves per CU.
 struct Leaf64 {
     const uint16_t *l1;
     const uint64_t *bits;
@@ -518,7 +649,7 @@ __device__ __forceinline__ uint32_t eval64(const Leaf64 &f, uint32_t q, uint32_t
     }
 }
 
-__global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_eu(3))) void leaf64_kernel(DecodeArgs a,
+__global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_eu(7))) void leaf64_kernel(DecodeArgs a,
                                                                                                            Launch64 l) {
     extern __shared__ __align__(16) uint8_t smem[];
     uint32_t *spal = reinterpret_cast<uint32_t *>(smem);
@@ -526,13 +657,13 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     uint8_t *wl = smem + 4 * k64PalLds + w * kV64Wave;
     uint32_t *D32 = reinterpret_cast<uint32_t *>(wl);
     uint16_t *D = reinterpret_cast<uint16_t *>(wl);
-    uint16_t *list = reinterpret_cast<uint16_t *>(wl + kV64List);
+    uint8_t *list = wl + kV64List;
     uint32_t *delta = reinterpret_cast<uint32_t *>(wl + kV64Delta);
-    uint16_t *out = reinterpret_cast<uint16_t *>(wl + kV64Out);
-    constexpr uint32_t kMark = 65533u;
-    // workgroups go to the 8 XCDs in turn: the 16 workgroups of a brick on
-    // the XCD of its upper workgroup, whose L2 holds the slot
-    const uint32_t g = blockIdx.x >> 3, rq = (g >> 4) * 8 + (blockIdx.x & 7u);
+    uint16_t *refs = reinterpret_cast<uint16_t *>(wl + kV64Ref);
+    constexpr uint32_t kMark = 65533u, kGroups = k64Blocks / k64LeafWaves;  // workgroups per brick
+    // workgroups go to the 8 XCDs in turn: those of a brick on the XCD of its
+    // upper workgroup, whose L2 holds the slot
+    const uint32_t g = blockIdx.x >> 3, rq = (g / kGroups) * 8 + (blockIdx.x & 7u);
     if (rq >= a.n) return;
     const uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
     const Head64 *head = reinterpret_cast<const Head64 *>(slot + k64Head);
@@ -552,78 +683,85 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     const bool plds = P <= k64PalLds;
     if (plds)
         for (uint32_t e = threadIdx.x; e < P; e += 64 * k64LeafWaves) spal[e] = pal[e];
-    __syncthreads();
-    // the block: 16 x 8 x 4 parents, 2 x 4 x 8 of them in a brick
-    const uint32_t blk = (g & 15u) * k64LeafWaves + w;
-    const uint32_t PX = 16 * (blk & 1u), PY = 8 * ((blk >> 1) & 3u), PZ = 4 * (blk >> 3);
-    const uint32_t lx = coord5(L), ly = coord5(L >> 1), lz = coord5(L >> 2);  // of a parent in its word (0 .. 3)
+    // the block's first parent, and its Morton index
+    const uint32_t blk = (g % kGroups) * k64LeafWaves + w;
+    const uint32_t PX = 16 * (blk & 1u), PY = 4 * ((blk >> 1) & 7u), PZ = 4 * (blk >> 4);
+    const uint32_t Q0 = spread5(PX) | (spread5(PY) << 1) | (spread5(PZ) << 2);
+    const uint32_t lx = coord2(L), ly = coord2(L >> 1), lz = coord2(L >> 2);
     // every voxel its parent's value; the expanded parents listed
     uint32_t E = 0;
 #pragma unroll
-    for (uint32_t j = 0; j < 8; j++) {
-        const uint32_t wx = j & 3u, wy = j >> 2;
-        const uint32_t word = spread5((PX >> 2) + wx) | (spread5((PY >> 2) + wy) << 1) | (spread5(PZ >> 2) << 2);
+    for (uint32_t j = 0; j < k64Words; j++) {
+        const uint32_t q0 = Q0 + 64 * (j & 1u) + 512 * (j >> 1), word = q0 >> 6;
         const uint64_t b = ld_s(f.bits + word);
-        const uint32_t pv = f.l1[64 * word + L] * 0x00010001u;
-        const uint32_t d = v64_dw(2 * (4 * wx + lx), 2 * (4 * wy + ly), 2 * lz);  // (the rows y and y + 1 share it)
+        const uint32_t pv = f.l1[q0 + L] * 0x00010001u;
+        const uint32_t d = v64_dw(8 * j + 2 * lx, 2 * ly, 2 * lz);  // (the rows y and y + 1 share it)
         D32[d] = pv;
         D32[d + 16] = pv;
         D32[d + kV64Plane] = pv;
         D32[d + kV64Plane + 16] = pv;
-        if ((b >> L) & 1u) list[E + mbcnt(b)] = (uint16_t)(64 * j + L);
+        if ((b >> L) & 1u) list[E + mbcnt(b)] = (uint8_t)(64 * j + L);
         if (L == 0) delta[j] = ld_s_u16(f.pre + word) - E;
         E += (uint32_t)__popcll(b);
     }
-    wsync();
-    // the children of the expanded parents
-    uint32_t nout = 0;
-    for (uint32_t c = 0; c < (E + 63) / 64; c++) {
-        const uint32_t pos = 64 * c + L;
-        const bool act = pos < E;
-        const uint32_t idx = act ? (uint32_t)list[pos] : 0u, j = idx >> 6, i = idx & 63u;
-        const uint32_t bx = 4 * (j & 3u) + coord5(i), by = 4 * (j >> 2) + coord5(i >> 1), bz = coord5(i >> 2);
-        const uint32_t q = spread5(PX + bx) | (spread5(PY + by) << 1) | (spread5(PZ + bz) << 2);
-        uint32_t open = 0, v0 = 0;
-        if (act) {
-            const uint32_t r = pos + delta[j], wd = nib8(f.nib, f.ops0 + 8 * r), in = f.info[r];
-            uint32_t nb[3];
+    __syncthreads();  // the palette, for every wave
+    // the children of the expanded parents; those that refer to a same-level
+    // node are listed
+    struct Ops {
+        uint32_t idx, wd, in, pv, nb[3];
+    };
+    // what a lane needs of the expanded parent at place 64 c + L, loaded
+    // while the chunk before is replayed
+    auto load = [&](uint32_t c) -> Ops {
+        Ops o;
+        const uint32_t pos = min(64 * c + L, E - 1);
+        o.idx = list[pos];
+        const uint32_t j = o.idx >> 6, q = Q0 + (o.idx & 63u) + 64 * (j & 1u) + 512 * (j >> 1), r = pos + delta[j];
+        o.wd = nib8(f.nib, f.ops0 + 8 * r);
+        o.in = f.info[r];
+        o.pv = f.l1[q];
 #pragma unroll
-            for (int x = 0; x < 3; x++) {
-                const uint32_t am = 0x1249u << x;
-                nb[x] = (q & am) != am ? (uint32_t)f.l1[morton_inc(q, am)] : 0u;
-            }
-            uint32_t pam, pdm, exm, cnt;
-            nibble_counts(wd, true, pam, pdm, exm, cnt);
-            bool bad = false;  // (the upper kernel has checked the level)
-            const uint4 v = replay_children<uint16_t>(wd, f.l1[q], nb, 7u, 7u, f.ipl + (in & (k64PalMax - 1u)),
-                                                      compact_nibble_bits(pam), compact_nibble_bits(pdm), f.nib,
-                                                      f.seg + (in >> 14), P, true, bad);
+        for (int x = 0; x < 3; x++) o.nb[x] = f.l1[morton_inc(q, 0x1249u << x)];  // (on a high face: any value)
+        return o;
+    };
+    uint32_t nref = 0;
+    const uint32_t chunks = (E + 63) / 64;
+    Ops next{};
+    if (chunks) next = load(0);
+    for (uint32_t c = 0; c < chunks; c++) {
+        const Ops o = next;
+        if (c + 1 < chunks) next = load(c + 1);
+        uint32_t open = 0, v0 = 0;
+        if (64 * c + L < E) {
+            const uint32_t j = o.idx >> 6, i = o.idx & 63u;
+            const uint32_t bx = 4 * j + coord2(i), by = coord2(i >> 1), bz = coord2(i >> 2);
+            const uint32_t y = o.wd & 0x77777777u;
+            const uint32_t pam = zero_nibbles(y ^ 0x66666666u), pdm = zero_nibbles(y ^ 0x55555555u);
+            const uint32_t dl = pdm ? nib8(f.nib, f.seg + (o.in >> 14)) : 0u;
+            const uint4 v = replay_children_u16(o.wd, o.pv, o.nb, f.ipl + (o.in & (k64PalMax - 1u)), pam, pdm, dl);
             const uint32_t d = v64_dw(2 * bx, 2 * by, 2 * bz);
             D32[d] = v.x;
             D32[d + 16] = v.y;
             D32[d + kV64Plane] = v.z;
             D32[d + kV64Plane + 16] = v.w;
-            // references to a node of another block (children at 0 on the axis)
-            open = ref_children(wd, (bx == 0 ? 1u : 0u) | (by == 0 ? 2u : 0u) | (bz == 0 ? 4u : 0u));
-            v0 = 2 * bx + 64 * by + 1024 * bz;  // x + 32 y + 512 z
+            open = ref_children(o.wd, 7u);
+            v0 = 2 * bx + 64 * by + 512 * bz;  // x + 32 y + 256 z
         }
         for (uint64_t m; (m = __ballot(open != 0)) != 0;) {
-            if (open) {
-                const uint32_t k = (uint32_t)__builtin_ctz(open) >> 2, at = nout + mbcnt(m);
-                open &= open - 1u;
-                if (at < kV64OutCap) out[at] = (uint16_t)(v0 + (k & 1u) + 32 * ((k >> 1) & 1u) + 512 * (k >> 2));
-            }
-            nout += (uint32_t)__popcll(m);
+            const uint32_t k = (uint32_t)__builtin_ctz(open) >> 2, to = nref + mbcnt(m);
+            if (open && to < kV64RefCap) refs[to] = (uint16_t)(v0 + (k & 1u) + 16 * (k & 2u) + 64 * (k & 4u));
+            open &= open - 1u;
+            nref += (uint32_t)__popcll(m);
         }
     }
     wsync();
     // a voxel's value: references followed inside the block, and out of it on
-    // the other block's operations
-    auto at = [&](uint32_t x, uint32_t y, uint32_t z) -> uint32_t { return 2 * v64_dw(x & ~1u, y, z) + (x & 1u); };
+    // the other block's operations (concurrent chases see a reference or its
+    // value, both of which lead to the value)
+    auto at = [&](uint32_t x, uint32_t y, uint32_t z) -> uint32_t { return 2 * v64_dw(x, y, z) + (x & 1u); };
     auto chase = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t v) -> uint32_t {
         while (v >= kMark) {
-            const uint32_t ax = v - kMark;
-            const uint32_t c = ax == 0 ? x : ax == 1 ? y : z;
+            const uint32_t ax = v - kMark, c = ax == 0 ? x : ax == 1 ? y : z;
             if (c == 0) {
                 const uint32_t q = spread5(PX + (x >> 1)) | (spread5(PY + (y >> 1)) << 1) | (spread5(PZ + (z >> 1)) << 2);
                 return eval64(f, morton_dec(q, 0x1249u << ax), (x & 1u) | ((y & 1u) << 1) | ((z & 1u) << 2) | (1u << ax));
@@ -635,26 +773,33 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
         }
         return v;
     };
-    for (uint32_t e = L; e < min(nout, kV64OutCap); e += 64) {
-        const uint32_t v = out[e], x = v & 31u, y = (v >> 5) & 15u, z = v >> 9, p = at(x, y, z);
+    const bool listed = nref <= kV64RefCap;
+    for (uint32_t e = L; listed && e < nref; e += 64) {
+        const uint32_t v = refs[e], x = v & 31u, y = (v >> 5) & 7u, z = v >> 8, p = at(x, y, z);
         D[p] = (uint16_t)chase(x, y, z, D[p]);
     }
     wsync();
-    const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
-    dst += 2 * PX + 128 * PY + 8192 * PZ;
-    for (uint32_t c = 0; c < 16; c++) {
-        const uint32_t x = 4 * (L & 7u), y = (L >> 3) + 8 * (c & 1u), z = c >> 1;
-        const uint2 v = *reinterpret_cast<const uint2 *>(D32 + v64_dw(x, y, z));
-        uint32_t idx[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
-        if (max(max(idx[0], idx[1]), max(idx[2], idx[3])) >= kMark) {
-#pragma unroll
-            for (uint32_t b = 0; b < 4; b++)
-                if (idx[b] >= kMark) idx[b] = chase(x + b, y, z, idx[b]);
+    // the block through the palette: 8 rows of 32 voxels per store
+    const uint32_t x = 4 * (L & 7u), y = L >> 3;
+    dst += 2 * PX + 128 * PY + 8192 * PZ + x + 64 * y;
+    auto rows = [&](auto al16, auto p, auto refs_left) {
+#pragma unroll 2
+        for (uint32_t z = 0; z < 8; z++) {
+            uint2 v = *reinterpret_cast<const uint2 *>(D32 + v64_dw(x, y, z));
+            if constexpr (decltype(refs_left)::value) {  // more references than the list holds
+                v.x = chase(x, y, z, v.x & 0xFFFFu) | (chase(x + 1, y, z, v.x >> 16) << 16);
+                v.y = chase(x + 2, y, z, v.y & 0xFFFFu) | (chase(x + 3, y, z, v.y >> 16) << 16);
+            }
+            store4<decltype(al16)::value>(dst + 4096 * z, make_uint4(p(half_x4<0>(v.x)), p(half_x4<1>(v.x)),
+                                                                     p(half_x4<0>(v.y)), p(half_x4<1>(v.y))));
         }
-        const uint4 o = plds ? make_uint4(spal[idx[0]], spal[idx[1]], spal[idx[2]], spal[idx[3]])
-                             : make_uint4(pal[idx[0]], pal[idx[1]], pal[idx[2]], pal[idx[3]]);
-        uint32_t *to = dst + x + 64 * y + 4096 * z;
-        if (al) store4<true>(to, o);
-        else store4<false>(to, o);
-    }
+    };
+    const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+    const uint8_t *sp = smem, *gp = reinterpret_cast<const uint8_t *>(pal);
+    auto in_lds = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(sp + o); };
+    auto in_mem = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(gp + o); };
+    if (plds && al && listed) rows(std::true_type{}, in_lds, std::false_type{});
+    else if (al && listed) rows(std::true_type{}, in_mem, std::false_type{});
+    else if (al) rows(std::true_type{}, in_mem, std::true_type{});
+    else rows(std::false_type{}, in_mem, std::true_type{});
 }

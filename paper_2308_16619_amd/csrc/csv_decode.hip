@@ -2635,7 +2635,7 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
         l.slot_bytes = (l.nib_off + 4ull * l.nib_dw + 255u) & ~255ull;
         l.lut_lds_words = lut_lds_words(pool);
         const uint32_t lds_e = align16(4 * l.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
-        const uint32_t lds_l = 4 * k64PalLds + (uint32_t)k64LeafWaves * kV64Wave;
+        const uint32_t lds_l = 4 * k64PalLds + k64LeafWaves * kV64Wave;
         static std::once_flag once;
         std::call_once(once, [] {
             (void)set_lds_attr(entropy64_kernel<true>);
@@ -2663,7 +2663,7 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
             }
             hipLaunchKernelGGL(upper64_kernel, dim3(std::min(m, 2 * cu)), dim3(k64Threads), kU64Lds, s, a, l);
             if (lods || lod_scalar == 0)
-                hipLaunchKernelGGL(leaf64_kernel, dim3(((m + 7) / 8) * 128), dim3(64 * k64LeafWaves), lds_l, s, a, l);
+                hipLaunchKernelGGL(leaf64_kernel, dim3(((m + 7) / 8) * 8 * (k64Blocks / k64LeafWaves)), dim3(64 * k64LeafWaves), lds_l, s, a, l);
         }
         return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
     }
