@@ -98,8 +98,9 @@ void csv_free(void *p);
  * blob is in host memory (*blob, release with csv_free).  Only 32^3 bricks
  * (opts->brick_log2 5) and rANS coding (opts->coding 0); opts->threads is
  * ignored.  The call keeps its device
- * buffers (about 430 KiB per workgroup, 5 workgroups per CU, plus the
- * records and the container) and a pinned host buffer of the container's
+ * buffers (2.5 MiB per CU, arenas of together a third of the labels' bytes,
+ * or more where a volume's operations need it, and the container) and a
+ * pinned host buffer of the container's
  * size for later calls on the same device, until csv_encode_gpu_release;
  * calls on one device run one at a time.  Errors: CSV_EINVAL (null
  * pointers, zero dims, options out of range, a bad device), CSV_ERANGE

@@ -1,26 +1,26 @@
 // GPU compressor for 32^3 bricks: the container of csv_encode_volume, byte
 // for byte, built on the device from a label volume resident in HBM.
 //
-//   symbols kernel (a 256-thread workgroup per brick, persistent grid):
+//   reuse kernel (a 256-thread workgroup per brick, persistent grid):
 //     resolution pyramid (Sec. 3.1)    level 1 from the volume, levels 2..5
-//                                      in LDS; level 0 read where needed
-//     operations (Sec. 3.2, Alg. 2)    per child level, the children of the
-//                                      expanded parents in Morton order: the
-//                                      reuse operations (parent, neighbours)
-//                                      in parallel, then the palette
-//                                      operations of the remaining children
-//                                      in order by one wavefront holding the
-//                                      last 17 palette entries in its lanes
-//     frequency tables (Sec. 3.3/3.4)  histograms of the sampled bricks'
-//                                      symbols, normalised on the host
-//     the symbol stream and palette of every brick go to an arena
-//   rANS kernel (a wavefront per brick): interleaved rANS (Sec. 3.3), one
-//     state per lane, symbols from last to first, the words of a step
-//     placed by ballot; the record into a second arena
+//                                      in LDS
+//     reuse operations (Sec. 3.2,      a lane per expanded parent: its eight
+//       Alg. 2)                        children against the parent and the
+//                                      neighbours, all levels alike; the
+//                                      children left over (they need the
+//                                      palette) listed in stream order
+//   palette kernel (a wavefront per brick): the palette operations of those
+//     children one by one, the last 17 palette entries in its lanes; then
+//     the symbol stream as packed nibbles (per level the deltas, then the
+//     operations), and the histograms of the sampled bricks
+//   rANS kernel (a wavefront per brick): the frequency tables (Sec. 3.3/3.4)
+//     from the histograms, interleaved rANS, one state per lane, symbols
+//     from last to first; the record into an arena
 //   packing: a device scan of record sizes, one copy kernel
 //
-// Per-workgroup and per-wavefront scratch in global memory holds the
-// symbol stream, palette and words of the bricks in flight.
+// The kernels pass their results through arenas in global memory; a brick
+// takes its part by an atomic add, and a part that does not fit makes the
+// host repeat the launches with the sizes they report.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,66 +29,107 @@
 #include <mutex>
 #include <new>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #include "csv.h"
 #include "csv_format.hpp"
 
-namespace csv {
-// frequency normalisation of the host compressor (same arithmetic, one copy)
-void normalize_counts(const uint64_t cnt[16], uint32_t M, uint32_t f[16]);
-}
-
 namespace {
 
 constexpr int kN = 5;
 constexpr uint32_t kThreads = 256;
-constexpr uint32_t kPer = 3;                  // child slots per thread per chunk
-constexpr uint32_t kChunk = kThreads * kPer;
-constexpr uint32_t kNone = 0xFFFFFFFFu;       // no slot
+constexpr uint32_t kWaves = kThreads / 64;
 constexpr uint32_t kNodes = 4681;           // levels 1..5 of a 32^3 brick
 constexpr uint32_t kMaxChildren = 37448;    // 8 * (1 + 8 + 64 + 512 + 4096)
 constexpr uint32_t kMaxSym = 2 * kMaxChildren;  // operations and deltas
-// per-workgroup scratch (bytes)
-constexpr size_t kOffSym = 0;
-constexpr size_t kOffOps = 76800;           // >= kMaxSym
-constexpr size_t kOffDel = kOffOps + 32768;
-constexpr size_t kOffPal = kOffDel + 32768;
-constexpr size_t kScratch = kOffPal + 4 * 37456;  // palette <= kMaxChildren + 1
-// per-wavefront scratch of the rANS kernel: the words of one brick
-constexpr size_t kWordsScratch = 2 * (size_t)kMaxSym + 64;
+// per-workgroup scratch of the reuse kernel (dwords): the operations of the
+// expanded parents of levels 5..2 (at most 585) and of level 1, then per
+// chunk of 64 parents (10 and 64 chunks) the labels of its left-over children
+constexpr uint32_t kReuseThreads = 1024;
+constexpr uint32_t kChunksA = 10, kChunks = kChunksA + 64, kOpsA = 640;
+constexpr uint32_t kOffCand = kOpsA + 4096;
+constexpr size_t kScratch = 4 * ((size_t)kOffCand + 512 * kChunks);
+// per-wavefront scratch of the rANS kernel: the words of one brick (filled
+// from the end, 512 at a time), a multiple of 16 bytes
+constexpr size_t kWordsScratch = (2 * (size_t)kMaxSym + 1024 + 64 + 15) & ~(size_t)15;
 
 __device__ __forceinline__ uint32_t lane() { return __lane_id(); }
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-__device__ __forceinline__ uint32_t spread3(uint32_t v) {
-    v &= 0x3FFu;
-    v = (v | (v << 16)) & 0x030000FFu;
-    v = (v | (v << 8)) & 0x0300F00Fu;
-    v = (v | (v << 4)) & 0x030C30C3u;
-    v = (v | (v << 2)) & 0x09249249u;
-    return v;
-}
-__device__ __forceinline__ uint32_t compact3(uint32_t v) {
-    v &= 0x09249249u;
-    v = (v ^ (v >> 2)) & 0x030C30C3u;
-    v = (v ^ (v >> 4)) & 0x0300F00Fu;
-    v = (v ^ (v >> 8)) & 0xFF0000FFu;
-    v = (v ^ (v >> 16)) & 0x000003FFu;
-    return v;
-}
-// Morton index: bit 0 of each 3-bit group is x, then y, then z
-__device__ __forceinline__ uint32_t morton(uint32_t x, uint32_t y, uint32_t z) {
-    return spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
 }
 // offset of level l (1..5) in the LDS node arrays
 __device__ __forceinline__ uint32_t lvl_off(int l) {
     return l == 1 ? 0u : (l == 2 ? 4096u : (l == 3 ? 4608u : (l == 4 ? 4672u : 4680u)));
 }
 
-// Per-workgroup phase clocks, only in builds with CSV_PHASE_TIMING: 8 u64
-// per workgroup, the shader clocks its thread 0 spent in each phase.
+// 2-bit coordinate (bits 0 and 3)
+__device__ __forceinline__ uint32_t coord2(uint32_t p) { return (p & 1u) | ((p >> 2) & 2u); }
+// 4-bit coordinate (bits 0, 3, 6, 9)
+__device__ __forceinline__ uint32_t coord4(uint32_t p) { return coord2(p) | (coord2(p >> 6) << 2); }
+__device__ __forceinline__ uint32_t morton_inc(uint32_t m, uint32_t mask) { return (((m | ~mask) + 1u) & mask) | (m & ~mask); }
+__device__ __forceinline__ uint32_t morton_dec(uint32_t m, uint32_t mask) { return (((m & mask) - 1u) & mask) | (m & ~mask); }
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint32_t readlane(uint32_t v, uint32_t k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); }
+// inclusive prefix sum over the 64 lanes
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return v;
+}
+// this wave's global stores before its own loads of them
+__device__ __forceinline__ void own_stores() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+// order a wave's own LDS operations
+__device__ __forceinline__ void wsync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// A device address as a pointer into the global address space, so that the
+// accesses compile to global (not flat) instructions
+template <class T>
+__device__ __forceinline__ T *glob(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
+// position of the n-th set bit of b (n below its count)
+__device__ __forceinline__ uint32_t select_bit(uint64_t b, uint32_t n) {
+    uint32_t pos = 0, x = (uint32_t)b;
+    const uint32_t c = (uint32_t)__builtin_popcount(x);
+    if (n >= c) {
+        n -= c;
+        pos = 32;
+        x = (uint32_t)(b >> 32);
+    }
+#pragma unroll
+    for (uint32_t h = 16; h; h >>= 1) {
+        const uint32_t k = (uint32_t)__builtin_popcount(x & ((1u << h) - 1u));
+        const bool up = n >= k;
+        n -= up ? k : 0u;
+        pos += up ? h : 0u;
+        x = up ? x >> h : x;
+    }
+    return pos;
+}
+// bits 0..7 of v to bits 0, 4, .., 28
+__device__ __forceinline__ uint32_t spread_nibbles(uint32_t v) {
+    v = (v | (v << 12)) & 0x000F000Fu;
+    v = (v | (v << 6)) & 0x03030303u;
+    return (v | (v << 3)) & 0x11111111u;
+}
+// nibble k of z is zero -> bit 4k of the result
+__device__ __forceinline__ uint32_t zero_nibbles(uint32_t z) { return ~(z | (z >> 1) | (z >> 2) | (z >> 3)) & 0x11111111u; }
+
+// Per-workgroup phase clocks of the reuse kernel, only in builds with
+// CSV_PHASE_TIMING: 8 u64 per workgroup, the shader clocks its thread 0
+// spent in each phase.
 #ifdef CSV_PHASE_TIMING
 __device__ uint64_t *g_enc_phase = nullptr;
 struct PhaseClock {
@@ -112,66 +153,57 @@ struct PhaseClock {
 };
 #endif
 
+// What the kernels know of a brick
+struct BrickMeta {
+    uint64_t off1;   // arena 1: operations of the expanded parents (stream order), then left-over children's labels
+    uint64_t pad;
+    uint32_t E[kN];  // expanded parents whose children are on level m
+    uint32_t NC[kN]; // children on level m that need the palette
+    uint32_t root;   // label of the root
+    uint32_t ok;     // 1: arena 1 holds the brick
+    uint32_t n, P;   // symbols, palette entries
+    uint32_t pal;    // dwords before the palette in arena 2
+    uint32_t cum[kN];
+};
+static_assert(sizeof(BrickMeta) == 96, "brick meta");
+
+// counters of a compression, cleared before its first kernel
+struct EncCtl {
+    unsigned long long hist[2][16];  // symbols of the sampled bricks
+    unsigned long long top1, top3;   // bytes asked of arenas 1 and 3
+    unsigned long long total;        // bytes of the records
+    uint16_t freq[2][16];            // the tables, for the header
+};
+
+// A brick's part of arena 2 lies at three times its place in arena 1 (no
+// counter: thousands of waves that start at once would queue for it): packed
+// nibbles, palette, then its record if that is not larger than the nibbles,
+// palette, header and 64 states (8 E + 9 c + 314 bytes for E parents and c
+// left-over children; before the record is written, a byte for each outcome
+// and delta).  In arena 1 it takes 4 (E + c) bytes and a pad that keeps the
+// parts three times that apart.
+constexpr uint32_t kPad1 = 128;
+static_assert(3 * kPad1 >= 314, "a brick's part of arena 2");
+__host__ __device__ constexpr uint64_t part2(uint64_t off1) { return 3 * off1; }
+
 struct EncArgs {
     const uint32_t *vol;
     uint32_t nx, ny, nz, nbx, nby;
     uint32_t n_items;          // bricks
     uint32_t sample_stride;    // the frequency tables count every sample_stride-th brick
-    unsigned long long *hist;  // 2 x 16 symbol counters of the sampled bricks
-    uint32_t f[2][16], c[2][16];
-    uint32_t bits, lane_k, lane_max;
-    uint8_t *scratch;          // symbols kernel: per workgroup
+    uint32_t bits, lane_k, lane_max, one_table;
+    EncCtl *ctl;
+    BrickMeta *meta;
+    uint8_t *scratch;          // reuse kernel: per workgroup
     uint8_t *wscratch;         // rANS kernel: per wavefront
-    uint8_t *sarena;           // symbol streams and palettes (symbols kernel -> rANS kernel)
-    uint64_t sarena_cap;
-    unsigned long long *sarena_top;
-    uint64_t *soff;            // per brick: offset in sarena
-    uint32_t *sn, *sp, *scum;  // per brick: symbols, palette entries, cum[5]
-    uint8_t *arena;
-    uint64_t arena_cap;
-    unsigned long long *arena_top;
+    uint8_t *arena1, *arena2, *arena3;
+    uint64_t cap1, cap3;
     uint32_t *sizes;  // per brick: record bytes
-    uint64_t *aoff;   // per brick: record offset in the arena
+    uint64_t *aoff;   // per brick: record address
 };
 
-struct Brick {
-    uint64_t x0, y0, z0;
-};
-
-// label of voxel (cx, cy, cz) of the brick; 0 beyond the volume (padding).
-// The address is clamped into the volume and the value masked, so that the
-// loads of a thread need no branches and issue together.
-__device__ __forceinline__ uint32_t voxel(const EncArgs &a, const Brick &b, uint32_t cx, uint32_t cy, uint32_t cz) {
-    const uint64_t x = b.x0 + cx, y = b.y0 + cy, z = b.z0 + cz;
-    const bool in = x < a.nx && y < a.ny && z < a.nz;
-    const uint64_t xc = in ? x : 0, yc = in ? y : 0, zc = in ? z : 0;
-    const uint32_t v = a.vol[xc + (uint64_t)a.nx * (yc + (uint64_t)a.ny * zc)];
-    return in ? v : 0u;
-}
-
-// label of node j (Morton) on level m
-__device__ __forceinline__ uint32_t label_at(const EncArgs &a, const Brick &b, const uint32_t *lab, int m, uint32_t j) {
-    if (m >= 1) return lab[lvl_off(m) + j];
-    return voxel(a, b, compact3(j), compact3(j >> 1), compact3(j >> 2));
-}
-
-// rank of this thread's flag among the workgroup's set flags, and their count
-__device__ __forceinline__ uint32_t wg_rank(bool f, uint32_t &total, uint32_t *wcnt) {
-    const uint64_t m = __ballot(f);
-    const uint32_t w = threadIdx.x >> 6;
-    if (lane() == 0) wcnt[w] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < kThreads / 64; k++) {
-        const uint32_t c = wcnt[k];
-        before += k < w ? c : 0u;
-        tot += c;
-    }
-    __syncthreads();
-    total = tot;
-    return before + mbcnt(m);
-}
+// four labels in x from any 4-byte aligned address
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ uint32_t lanes_for(uint32_t n, uint32_t K, uint32_t Wmax) {
     if (n == 0) return 0;
@@ -182,414 +214,772 @@ __device__ __forceinline__ uint32_t lanes_for(uint32_t n, uint32_t K, uint32_t W
 
 // the most frequent of 8 children, the earliest winning a tie; same: all equal
 __device__ __forceinline__ uint32_t mode8(const uint32_t ch[8], bool &same) {
-    same = true;
+    uint32_t n[8] = {};
 #pragma unroll
-    for (int k = 1; k < 8; k++) same &= ch[k] == ch[0];
-    if (same) return ch[0];
-    int bestk = 0, bestn = 0;
+    for (int i = 0; i < 8; i++)
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-        int n = 0;
-#pragma unroll
-        for (int r = 0; r < 8; r++) n += ch[r] == ch[k];
-        if (n > bestn) {
-            bestn = n;
-            bestk = k;
+        for (int j = i + 1; j < 8; j++) {
+            const uint32_t e = ch[i] == ch[j] ? 1u : 0u;
+            n[i] += e;
+            n[j] += e;
         }
-    }
-    uint32_t v = ch[0];
+    same = n[0] == 7u;
+    uint32_t best = 8 * n[0] + 7, v = ch[0];
 #pragma unroll
-    for (int k = 1; k < 8; k++) v = k == bestk ? ch[k] : v;
+    for (uint32_t k = 1; k < 8; k++) best = max(best, 8 * n[k] + 7 - k);
+#pragma unroll
+    for (uint32_t k = 1; k < 8; k++) v = (best & 7u) == 7 - k ? ch[k] : v;
     return v;
 }
 
-// Pyramid, operations and palette of one brick per workgroup; the symbol
-// stream and palette go to the arena for the rANS kernel.
-// (LDS under 32 KB and 5 waves per SIMD: five workgroups per CU)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void symbols_kernel(EncArgs a) {
-    __shared__ uint32_t lab[kNodes];
-    __shared__ uint32_t cstb[(kNodes + 31) / 32];  // constant-subtree flags, one bit per node
-    __shared__ uint16_t expl[4096];
-    __shared__ uint32_t c_lab[kChunk];
-    __shared__ uint8_t c_op[kChunk];
-    __shared__ uint32_t wcnt[kThreads / 64];
-    __shared__ uint32_t wcnt4[kPer][kThreads / 64];
-    __shared__ uint32_t share[8];  // 0: deltas of a level; 3: palette entries; 4, 5: arena offset
-    __shared__ uint32_t s_cum[kN];
-    __shared__ uint32_t hist_l[32];
-    const uint32_t t = threadIdx.x, L = lane(), w = t >> 6;
-    uint8_t *scr = a.scratch + (size_t)blockIdx.x * kScratch;
-    uint8_t *sym = scr + kOffSym;
-    uint8_t *ops = scr + kOffOps;
-    uint8_t *dels = scr + kOffDel;
-    uint32_t *pal = reinterpret_cast<uint32_t *>(scr + kOffPal);
+// A parent's children c, its value p and the neighbours its children may
+// refer to: at child 0 on an axis the same-level nodes at -1 (xm by ky + 2
+// kz, ym by kx + 2 kz, zm by kx + 2 ky), at child 1 the parent level's node
+// at +1.  low / high: bit a set if there is a node at -1 / +1 on axis a.
+struct Family {
+    uint32_t c[8], p, xm[4], ym[4], zm[4], xp, yp, zp, low, high;
+};
+// the reuse operations (bestOperation's order: parent, x, y, z), a nibble
+// per child, 6 where none applies; left: those children (bit k)
+__device__ __forceinline__ uint32_t reuse_ops(const Family &f, uint32_t &left) {
+    uint32_t mp = 0, mx = 0, my = 0, mz = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; k++) {
+        const uint32_t c = f.c[k];
+        mp |= c == f.p ? 1u << k : 0u;
+        mx |= c == ((k & 1) ? f.xp : f.xm[k >> 1]) ? 1u << k : 0u;
+        my |= c == ((k & 2) ? f.yp : f.ym[(k & 1) | ((k >> 2) << 1)]) ? 1u << k : 0u;
+        mz |= c == ((k & 4) ? f.zp : f.zm[k & 3]) ? 1u << k : 0u;
+    }
+    mx &= ((f.low & 1u) ? 0x55u : 0u) | ((f.high & 1u) ? 0xAAu : 0u);
+    my &= ((f.low & 2u) ? 0x33u : 0u) | ((f.high & 2u) ? 0xCCu : 0u);
+    mz &= ((f.low & 4u) ? 0x0Fu : 0u) | ((f.high & 4u) ? 0xF0u : 0u);
+    mx &= ~mp;
+    my &= ~(mp | mx);
+    mz &= ~(mp | mx | my);
+    left = 0xFFu & ~(mp | mx | my | mz);
+    static_assert(csv::kRp == 0 && csv::kRx == 1 && csv::kRy == 2 && csv::kRz == 3 && csv::kPa == 6, "operation codes");
+    return spread_nibbles(mx | mz) | (spread_nibbles(my | mz | left) << 1) | (spread_nibbles(left) << 2);
+}
+
+// LDS of a reuse workgroup: the brick's labels, levels 1..5 in Morton order
+// (see lvl_off), their constant-subtree flags, what finds an expanded node of
+// a given rank, per chunk of 64 parents its left-over children
+struct ReuseLds {
+    uint32_t vox[32768];          // see vox_at
+    uint32_t lab[kNodes + 7];
+    uint64_t cst[74];             // level 1, 2, 3 from words 0, 64, 72; level 4 and 5 in bits 0..7 and 8 of 73
+    uint64_t wA[16];              // expanded nodes of levels 5, 4, 3 and 2 (8 words)
+    uint64_t share;
+    uint32_t nE[kN], nC[kN];
+    uint32_t before[kChunks + 6]; // left-over children before a chunk's (first: the chunk's own)
+    uint16_t preA[16];            // expanded nodes before each word of wA
+    uint16_t pre1[64];            // ... of level 1 before each of its words
+};
+static_assert(sizeof(ReuseLds) <= 160 * 1024, "one workgroup per CU");
+
+// Dword of voxel (x, y, z) of the brick.  Rows of four groups of 8 dwords,
+// exchanged so that the 4 x 4 cells in x and y that a wave reads at once
+// lie in different banks (groups of 4 dwords in x stay together).
+__device__ __forceinline__ uint32_t vox_at(uint32_t x, uint32_t y, uint32_t z) {
+    return 1024 * z + 32 * y + (x ^ ((y & 6u) << 2));
+}
+
+// Pyramid and reuse operations of one brick per workgroup of 16 waves, one
+// workgroup per CU: the brick's 128 KB of labels are read once, into
+// registers while the brick before is worked on, and kept in LDS for the
+// operations, which look at every expanded node's eight children and twelve
+// neighbours.  Bound by vector issue (20 k wave-instructions per brick, 43 %
+// of the time) and the steps of few waves between barriers; 307 us for the
+// 512^3 cells volume (1.75 TB/s of labels).  Reading the labels again from
+// memory, with six smaller workgroups per CU, exceeded the L2 and took 625
+// us; a thread per child with its own addresses for every neighbour, and the
+// palette operations in the same workgroup, 1.19 ms.
+__global__ __launch_bounds__(kReuseThreads) __attribute__((amdgpu_waves_per_eu(4))) void reuse_kernel(EncArgs a) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    ReuseLds &S = *reinterpret_cast<ReuseLds *>(smem);
+    constexpr uint32_t kW = kReuseThreads / 64;
+    const uint32_t t = threadIdx.x, L = lane(), w = uniform(t >> 6);
+    uint32_t *opw = glob(reinterpret_cast<uint32_t *>(a.scratch + (size_t)blockIdx.x * kScratch));
+    const uint32_t lx = coord2(L), ly = coord2(L >> 1), lz = coord2(L >> 2);
+    const uint64_t row = a.nx, plane = (uint64_t)a.nx * a.ny;
+    // this thread's voxels: 4 in x of row (t >> 3) & 31 in the planes t >> 8, + 4, ..
+    const uint32_t vx = 4 * (t & 7u), vy = (t >> 3) & 31u, vz = t >> 8;
+    uint4 pre[8];
+    auto fetch = [&](uint32_t id) {
+        const uint64_t x = (uint64_t)(id % a.nbx) * 32 + vx, y = (uint64_t)((id / a.nbx) % a.nby) * 32 + vy;
+        const uint64_t z0 = (id / ((uint64_t)a.nbx * a.nby)) * 32;
+        const uint32_t *v = glob(a.vol) + x + row * y + plane * (z0 + vz);
+        if ((x | 31u) < a.nx && (y | 31u) < a.ny && z0 + 32 <= a.nz) {  // (the same for the whole brick)
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++) {
+                const u32x4 r = *reinterpret_cast<const u32x4 *>(v + 4 * k * plane);
+                pre[k] = make_uint4(r.x, r.y, r.z, r.w);
+            }
+        } else {  // labels beyond the volume are 0 (padding)
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++) {
+                const bool in = y < a.ny && z0 + vz + 4 * k < a.nz;
+                const uint32_t *u = v + 4 * k * plane;
+                pre[k].x = in && x < a.nx ? u[0] : 0u;
+                pre[k].y = in && x + 1 < a.nx ? u[1] : 0u;
+                pre[k].z = in && x + 2 < a.nx ? u[2] : 0u;
+                pre[k].w = in && x + 3 < a.nx ? u[3] : 0u;
+            }
+        }
+    };
     PhaseClock pc;
-    for (uint32_t item = blockIdx.x; item < a.n_items; item += gridDim.x) {
+    if (blockIdx.x < a.n_items) fetch(blockIdx.x);
+    for (uint32_t id = blockIdx.x; id < a.n_items; id += gridDim.x) {
         pc.start();
-        const uint64_t id = item;
-        Brick b;
-        b.x0 = (id % a.nbx) * 32;
-        b.y0 = ((id / a.nbx) % a.nby) * 32;
-        b.z0 = (id / ((uint64_t)a.nbx * a.nby)) * 32;
-        for (uint32_t i = t; i < (kNodes + 31) / 32; i += kThreads) cstb[i] = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 8; k++) *reinterpret_cast<uint4 *>(&S.vox[vox_at(vx, vy, vz + 4 * k)]) = pre[k];
+        if (t < kN) S.nC[t] = 0;
         __syncthreads();
-        // level 1 from the volume (every level-0 node is a constant subtree)
-        for (uint32_t q = t; q < 4096; q += kThreads) {
-            const uint32_t x = 2 * compact3(q), y = 2 * compact3(q >> 1), z = 2 * compact3(q >> 2);
+        if (a.n_items - id > gridDim.x) fetch(id + gridDim.x);
+        pc.stop(0);  // labels
+        // level 1 (every level-0 node is a constant subtree): a wave takes
+        // 4 x 4 x 4 nodes, one flag word
+        for (uint32_t g = w; g < 64; g += kW) {
+            const uint32_t X = 4 * coord2(g) + lx, Y = 4 * coord2(g >> 1) + ly, Z = 4 * coord2(g >> 2) + lz;
             uint32_t ch[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) ch[k] = voxel(a, b, x + (k & 1), y + ((k >> 1) & 1), z + (k >> 2));
+            for (uint32_t k = 0; k < 4; k++) {
+                const uint2 r = *reinterpret_cast<const uint2 *>(&S.vox[vox_at(2 * X, 2 * Y + (k & 1), 2 * Z + (k >> 1))]);
+                ch[2 * k] = r.x;
+                ch[2 * k + 1] = r.y;
+            }
             bool same;
-            lab[q] = mode8(ch, same);
-            // a wavefront's 64 nodes are one aligned pair of flag words
+            S.lab[64 * g + L] = mode8(ch, same);
             const uint64_t bm = __ballot(same);
+            if (L == 0) S.cst[g] = bm;
+        }
+        __syncthreads();
+        // levels 2..5
+        auto coarser = [&](int l, uint32_t q, bool act) -> uint64_t {
+            const uint32_t lo = lvl_off(l - 1) + 8 * (act ? q : 0u);
+            uint32_t ch[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) ch[k] = S.lab[lo + k];
+            bool same;
+            const uint32_t v = mode8(ch, same);
+            if (act) S.lab[lvl_off(l) + q] = v;
+            // the 8 children's flags: one byte
+            return __ballot(act && same && reinterpret_cast<const uint8_t *>(S.cst)[lo >> 3] == 0xFFu);
+        };
+        if (w < 8) {
+            const uint64_t m = coarser(2, 64 * w + L, true);
+            if (L == 0) S.cst[64 + w] = m;
+        } else if (w == 8) {  // the expanded nodes (not constant) of level 1
+            const uint32_t c = (uint32_t)__popcll(~S.cst[L]), inc = wave_incl_scan(c);
+            S.pre1[L] = (uint16_t)(inc - c);
+            if (L == 63) S.nE[0] = inc;
+        }
+        __syncthreads();
+        pc.stop(1);  // levels 1 and 2
+        const uint32_t EB = S.nE[0], nchB = (EB + 63) / 64;
+        // a chunk's operations to opw[r] and its left-over children, counted
+        // and listed in the chunk's own place
+        auto put = [&](const Family &f, bool act, uint32_t r, uint32_t stops, uint32_t ch) -> uint32_t {
+            uint32_t left = 0;
+            const uint32_t o = reuse_ops(f, left) | (spread_nibbles(stops) << 3);
+            if (!act) left = 0;
+            if (act) opw[r] = o;
+            const uint32_t c = (uint32_t)__builtin_popcount(left), inc = wave_incl_scan(c);
+            uint32_t *to = opw + kOffCand + 512 * ch + inc - c;
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++)
+                if ((left >> k) & 1u) *to++ = f.c[k];
+            if (L == 63) S.before[ch] = inc;
+            return c;
+        };
+        if (w == kW - 1) {
+            // levels 3..5, and their and level 2's expanded nodes in stream order
+            const uint64_t m3 = coarser(3, L, true);
+            if (L == 0) S.cst[72] = m3;
+            wsync();
+            const uint64_t m4 = coarser(4, L, L < 8);
+            if (L == 0) S.cst[73] = m4;
+            wsync();
+            const uint64_t m5 = coarser(5, L, L == 0);
+            if (L == 0) S.cst[73] = m4 | (m5 << 8);
+            uint64_t x = 0;
+            if (L == 0) x = ~m5 & 1u;
+            else if (L == 1) x = ~m4 & 0xFFu;
+            else if (L == 2) x = ~m3;
+            else if (L < 11) x = ~S.cst[61 + L];
+            const uint32_t c = (uint32_t)__popcll(x), inc = wave_incl_scan(c);
+            if (L < 16) {
+                S.wA[L] = x;
+                S.preA[L] = L < 11 ? (uint16_t)(inc - c) : (uint16_t)0xFFFFu;
+            }
+            if (L < 3) S.nE[4 - L] = c;
+            const uint32_t up = readlane(inc, 2);
+            if (L == 10) S.nE[1] = inc - up;
+        } else {
+            // children on level 0
+            for (uint32_t ch = w; ch < nchB; ch += kW - 1) {
+                const uint32_t r = 64 * ch + L;
+                const bool act = r < EB;
+                const uint32_t rr = act ? r : 0u;
+                uint32_t wd = 0;
+#pragma unroll
+                for (uint32_t h = 32; h; h >>= 1) wd += S.pre1[wd + h] <= rr ? h : 0u;
+                const uint32_t q = 64 * wd + select_bit(~S.cst[wd], rr - S.pre1[wd]);
+                const uint32_t X = coord4(q), Y = coord4(q >> 1), Z = coord4(q >> 2);
+                Family f;
+                f.low = (X ? 1u : 0u) | (Y ? 2u : 0u) | (Z ? 4u : 0u);
+                f.high = (X < 15 ? 1u : 0u) | (Y < 15 ? 2u : 0u) | (Z < 15 ? 4u : 0u);
+                // (a neighbour outside the brick: any value)
+                const uint32_t x1 = X ? 2 * X - 1 : 0u, y1 = Y ? 2 * Y - 1 : 0u, z1 = Z ? 2 * Z - 1 : 0u;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; k++) {  // k: ky + 2 kz
+                    const uint32_t y = 2 * Y + (k & 1), z = 2 * Z + (k >> 1);
+                    const uint2 c = *reinterpret_cast<const uint2 *>(&S.vox[vox_at(2 * X, y, z)]);
+                    f.c[2 * k] = c.x;
+                    f.c[2 * k + 1] = c.y;
+                    f.xm[k] = S.vox[vox_at(x1, y, z)];
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < 2; k++) {
+                    const uint2 c = *reinterpret_cast<const uint2 *>(&S.vox[vox_at(2 * X, y1, 2 * Z + k)]);
+                    f.ym[2 * k] = c.x;
+                    f.ym[2 * k + 1] = c.y;
+                    const uint2 d = *reinterpret_cast<const uint2 *>(&S.vox[vox_at(2 * X, 2 * Y + k, z1)]);
+                    f.zm[2 * k] = d.x;
+                    f.zm[2 * k + 1] = d.y;
+                }
+                f.p = S.lab[q];
+                f.xp = S.lab[X < 15 ? morton_inc(q, 0x249u) : q];
+                f.yp = S.lab[Y < 15 ? morton_inc(q, 0x492u) : q];
+                f.zp = S.lab[Z < 15 ? morton_inc(q, 0x924u) : q];
+                put(f, act, kOpsA + r, 0u, kChunksA + ch);
+            }
+        }
+        __syncthreads();
+        pc.stop(2);  // operations of level 0
+        const uint32_t EA = S.nE[1] + S.nE[2] + S.nE[3] + S.nE[4], nchA = (EA + 63) / 64;
+        // children on levels 4..1
+        if (w < nchA) {
+            const uint32_t r = 64 * w + L;
+            const bool act = r < EA;
+            const uint32_t rr = act ? r : 0u;
+            uint32_t wd = 0;
+#pragma unroll
+            for (uint32_t h = 8; h; h >>= 1) wd += S.preA[wd + h] <= rr ? h : 0u;
+            const uint32_t pos = select_bit(S.wA[wd], rr - S.preA[wd]);
+            const int l = wd == 0 ? 5 : (wd == 1 ? 4 : (wd == 2 ? 3 : 2));
+            const uint32_t q = wd >= 3 ? 64 * (wd - 3) + pos : pos;
+            const uint32_t lo = lvl_off(l - 1), lp = lvl_off(l);
+            const uint32_t pm = 0x49249249u & ((1u << (3 * (5 - l))) - 1u);
+            Family f;
+            f.low = f.high = 0;
+            uint32_t at[3], up[3];
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                const uint32_t am = pm << x;
+                f.low |= (q & am) ? 1u << x : 0u;
+                f.high |= (q & am) != am ? 1u << x : 0u;
+                at[x] = lo + 8 * ((q & am) ? morton_dec(q, am) : q);
+                up[x] = S.lab[lp + ((q & am) != am ? morton_inc(q, am) : q)];
+            }
+            f.p = S.lab[lp + q];
+            f.xp = up[0];
+            f.yp = up[1];
+            f.zp = up[2];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; k++) f.c[k] = S.lab[lo + 8 * q + k];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; k++) {
+                f.xm[k] = S.lab[at[0] + 2 * k + 1];
+                f.ym[k] = S.lab[at[1] + (k & 1) + 2 + 4 * (k >> 1)];
+                f.zm[k] = S.lab[at[2] + k + 4];
+            }
+            const uint32_t stops = reinterpret_cast<const uint8_t *>(S.cst)[(lo >> 3) + q];
+            const uint32_t c = put(f, act, r, stops, w);
+            if (c) atomicAdd(&S.nC[l - 1], c);
+        }
+        __syncthreads();
+        // operations and left-over labels to arena 1
+        const uint32_t Et = EA + EB;
+        if (w == 0) {
+            // chunks of levels 4..1, then of level 0: the left-over children
+            // before each
+            const uint32_t cA = L < nchA ? S.before[L] : 0u, cB = L < nchB ? S.before[kChunksA + L] : 0u;
+            const uint32_t iA = wave_incl_scan(cA), iB = wave_incl_scan(cB);
+            const uint32_t tA = readlane(iA, 63), tB = readlane(iB, 63);
+            if (L < nchA) S.before[L] = iA - cA;
+            if (L < nchB) S.before[kChunksA + L] = tA + iB - cB;
+            const uint64_t bytes = 4ull * (Et + tA + tB) + kPad1;
             if (L == 0) {
-                cstb[q >> 5] = (uint32_t)bm;
-                cstb[(q >> 5) + 1] = (uint32_t)(bm >> 32);
+                const uint64_t off = atomicAdd(&glob(a.ctl)->top1, (unsigned long long)bytes);
+                const bool ok = off + bytes <= a.cap1;
+                S.share = ok ? off : ~0ull;
+                S.nC[0] = tB;
+                BrickMeta *m = glob(a.meta) + id;
+                m->off1 = off;
+                m->ok = ok ? 1u : 0u;
+                m->root = S.lab[lvl_off(kN)];
+                for (int k = 0; k < kN; k++) {
+                    m->E[k] = S.nE[k];
+                    m->NC[k] = S.nC[k];
+                }
             }
         }
         __syncthreads();
-        for (int l = 2; l <= kN; l++) {
-            const uint32_t n = 1u << (3 * (kN - l)), lo = lvl_off(l - 1), hi = lvl_off(l);
-            for (uint32_t q = t; q < n; q += kThreads) {
-                uint32_t ch[8];
-#pragma unroll
-                for (int k = 0; k < 8; k++) ch[k] = lab[lo + 8 * q + k];
-                // the 8 children's flags: one byte of a word (lo and 8q are multiples of 8)
-                const uint32_t c8 = lo + 8 * q;
-                const bool allc = ((cstb[c8 >> 5] >> (c8 & 31)) & 0xFFu) == 0xFFu;
-                bool same;
-                lab[hi + q] = mode8(ch, same);
-                if (n >= 64) {  // levels 2, 3: as level 1 (their offsets are multiples of 64)
-                    const uint64_t bm = __ballot(same && allc);
-                    if (L == 0) {
-                        cstb[(hi + q) >> 5] = (uint32_t)bm;
-                        cstb[((hi + q) >> 5) + 1] = (uint32_t)(bm >> 32);
-                    }
-                } else if (same && allc) {  // levels 4, 5 share a word
-                    atomicOr(&cstb[(hi + q) >> 5], 1u << ((hi + q) & 31));
-                }
+        const uint64_t off = S.share;
+        if (off != ~0ull) {
+            uint32_t *d = glob(reinterpret_cast<uint32_t *>(a.arena1 + off));
+            for (uint32_t i = t; i < Et; i += kReuseThreads) d[i] = opw[i < EA ? i : kOpsA - EA + i];
+            d += Et;
+            const uint32_t tot = S.nC[0] + S.nC[1] + S.nC[2] + S.nC[3] + S.nC[4];
+            for (uint32_t k = w; k < nchA + nchB; k += kW) {
+                const uint32_t ch = k < nchA ? k : kChunksA + k - nchA;
+                const uint32_t at = S.before[ch];
+                const uint32_t to = k + 1 == nchA + nchB ? tot : S.before[k + 1 < nchA ? k + 1 : kChunksA + k + 1 - nchA];
+                for (uint32_t i = L; i < to - at; i += 64) d[at + i] = opw[kOffCand + 512 * ch + i];
             }
-            __syncthreads();
-        }
-        pc.stop(0);  // pyramid
-        // symbol stream: child levels 4 .. 0
-        uint32_t win = 0, P = 1, D = 0;  // wavefront 0: palette window (lane i: entry P-1-i), size, deltas
-        if (w == 0 && L == 0) {
-            win = lab[lvl_off(kN)];
-            pal[0] = win;
-        }
-        uint32_t base = 0;
-        for (int m = kN - 1; m >= 0; m--) {
-            const int l = m + 1;
-            const uint32_t np = 1u << (3 * (kN - l)), G = 32u >> m;
-            uint32_t E = 0;
-            for (uint32_t q0 = 0; q0 < np; q0 += kThreads) {
-                const uint32_t q = q0 + t;
-                const bool f = q < np && !((cstb[(lvl_off(l) + q) >> 5] >> ((lvl_off(l) + q) & 31)) & 1u);
-                uint32_t tot;
-                const uint32_t r = wg_rank(f, tot, wcnt);
-                if (f) expl[E + r] = (uint16_t)q;
-                E += tot;
-            }
-            __syncthreads();
-            D = 0;
-            for (uint32_t s0 = 0; s0 < 8 * E; s0 += kChunk) {
-                // kPer child slots per thread (slot s0 + u * kThreads + t),
-                // their label and neighbour loads all in flight together
-                uint32_t opv[kPer], lblv[kPer], rk[kPer];
-                uint64_t bal[kPer];
-#pragma unroll
-                for (uint32_t u = 0; u < kPer; u++) {
-                    const uint32_t s = s0 + u * kThreads + t;
-                    const bool valid = s < 8 * E;
-                    uint32_t op = kNone, lbl = 0;
-                    if (valid) {
-                        const uint32_t q = expl[s >> 3], j = 8 * q + (s & 7);
-                        const uint32_t cx = compact3(j), cy = compact3(j >> 1), cz = compact3(j >> 2);
-                        lbl = label_at(a, b, lab, m, j);
-                        const uint32_t par = lab[lvl_off(l) + q];
-                        uint32_t nv[3];
-                        bool nok[3];
-#pragma unroll
-                        for (uint32_t ax = 0; ax < 3; ax++) {
-                            const uint32_t c = ax == 0 ? cx : (ax == 1 ? cy : cz);
-                            if ((c & 1u) == 0) {  // the same-level node at -1
-                                nok[ax] = c > 0;
-                                const uint32_t d = nok[ax] ? 1u : 0u;
-                                nv[ax] = label_at(a, b, lab, m,
-                                                  morton(cx - (ax == 0 ? d : 0u), cy - (ax == 1 ? d : 0u),
-                                                         cz - (ax == 2 ? d : 0u)));
-                            } else {  // the parent of the node at +1
-                                nok[ax] = c + 1 < G;
-                                const uint32_t d = nok[ax] ? 1u : 0u;
-                                nv[ax] = lab[lvl_off(l) + morton((cx + (ax == 0 ? d : 0u)) >> 1,
-                                                                 (cy + (ax == 1 ? d : 0u)) >> 1,
-                                                                 (cz + (ax == 2 ? d : 0u)) >> 1)];
-                            }
-                        }
-                        op = par == lbl ? csv::kRp
-                                        : (nok[0] && nv[0] == lbl
-                                               ? csv::kRx
-                                               : (nok[1] && nv[1] == lbl ? csv::kRy
-                                                                         : (nok[2] && nv[2] == lbl ? csv::kRz : csv::kPa)));
-                        const uint32_t stop =
-                            (m >= 1 && ((cstb[(lvl_off(m) + j) >> 5] >> ((lvl_off(m) + j) & 31)) & 1u)) ? 1u : 0u;
-                        op |= stop << 8;
-                    }
-                    opv[u] = op;
-                    lblv[u] = lbl;
-                    bal[u] = __ballot(op != kNone && (op & 0xFFu) == csv::kPa);
-                    if (L == 0) wcnt4[u][w] = (uint32_t)__popcll(bal[u]);
-                }
-                __syncthreads();
-                // candidates ranked in slot order
-                uint32_t nc = 0;
-#pragma unroll
-                for (uint32_t u = 0; u < kPer; u++) {
-                    uint32_t bw = 0, tu = 0;
-#pragma unroll
-                    for (uint32_t k = 0; k < kThreads / 64; k++) {
-                        const uint32_t c = wcnt4[u][k];
-                        bw += k < w ? c : 0u;
-                        tu += c;
-                    }
-                    rk[u] = nc + bw + mbcnt(bal[u]);
-                    nc += tu;
-                    if ((bal[u] >> L) & 1ull) c_lab[rk[u]] = lblv[u];
-                }
-                __syncthreads();
-                pc.stop(m == 0 ? 2 : 1);  // reuse operations
-                if (w == 0) {
-                    // palette operations in order: P_0, else the smallest delta
-                    // among the 16 entries before it, else append.  Lane k
-                    // holds candidate c0 + k and receives its operation.
-                    for (uint32_t c0 = 0; c0 < nc; c0 += 64) {
-                        const uint32_t lv = c0 + L < nc ? c_lab[c0 + L] : 0u;
-                        const uint32_t cn = min(64u, nc - c0);
-                        uint32_t mine = 0;
-                        for (uint32_t k = 0; k < cn; k++) {
-                            const uint32_t lc = (uint32_t)__builtin_amdgcn_readlane((int)lv, (int)k);
-                            const uint64_t mm = __ballot(L <= 16 && L < P && win == lc);
-                            uint32_t o;
-                            if (mm & 1ull) {
-                                o = csv::kP0;
-                            } else if (mm) {
-                                o = csv::kPd;
-                                if (L == 0) dels[D] = (uint8_t)(__builtin_ctzll(mm) - 1);
-                                D++;
-                            } else {
-                                o = csv::kPa;
-                                // lane i takes lane i - 1's entry (DPP wave shift right by one)
-                                win = (uint32_t)__builtin_amdgcn_update_dpp((int)win, (int)win, 0x138, 0xF, 0xF, false);
-                                if (L == 0) {
-                                    win = lc;
-                                    pal[P] = lc;
-                                }
-                                P++;
-                            }
-                            mine = L == k ? o : mine;
-                        }
-                        if (c0 + L < nc) c_op[c0 + L] = (uint8_t)mine;
-                    }
-                }
-                __syncthreads();
-                pc.stop(3);  // palette operations
-#pragma unroll
-                for (uint32_t u = 0; u < kPer; u++) {
-                    const uint32_t s = s0 + u * kThreads + t;
-                    if (opv[u] != kNone) {
-                        const uint32_t o = ((bal[u] >> L) & 1ull) ? c_op[rk[u]] : (opv[u] & 0xFFu);
-                        ops[s] = (uint8_t)(o | ((opv[u] >> 8) << 3));
-                    }
-                }
-            }
-            if (t == 0) share[0] = D;
-            __syncthreads();
-            const uint32_t nd = share[0];
-            // a level's delta nibbles precede its operation nibbles
-            for (uint32_t i = t; i < nd; i += kThreads) sym[base + i] = dels[i];
-            for (uint32_t i = t; i < 8 * E; i += kThreads) sym[base + nd + i] = ops[i];
-            base += nd + 8 * E;
-            if (t == 0) s_cum[m] = base;
-            __syncthreads();
-        }
-        pc.stop(4);  // level ends
-        const uint32_t n = base, leaf = s_cum[1];
-        // the sampled bricks' symbol histograms (the frequency tables, Sec. 3.4)
-        if (id % a.sample_stride == 0) {
-            if (t < 32) hist_l[t] = 0;
-            __syncthreads();
-            for (uint32_t i = t; i < n; i += kThreads) atomicAdd(&hist_l[(i >= leaf ? 16u : 0u) + sym[i]], 1u);
-            __syncthreads();
-            if (t < 32 && hist_l[t]) atomicAdd(&a.hist[t], (unsigned long long)hist_l[t]);
-        }
-        // symbols and palette to the arena, for the rANS kernel
-        if (w == 0 && L == 0) share[3] = P;
-        __syncthreads();
-        const uint32_t Pn = share[3];
-        const uint64_t bytes = (((uint64_t)n + 3) & ~3ull) + 4ull * Pn;
-        if (t == 0) {
-            const uint64_t off = atomicAdd(a.sarena_top, (unsigned long long)bytes);
-            a.soff[id] = off;
-            a.sn[id] = n;
-            a.sp[id] = Pn;
-            for (int m = 0; m < kN; m++) a.scum[(size_t)kN * id + m] = s_cum[m];
-            share[4] = (uint32_t)off;
-            share[5] = (uint32_t)(off >> 32);
         }
         __syncthreads();
-        const uint64_t off = ((uint64_t)share[5] << 32) | share[4];
-        if (off + bytes <= a.sarena_cap) {
-            uint8_t *d = a.sarena + off;
-            // whole dwords (the arena offset and the scratch are 4-byte aligned;
-            // the bytes past n are padding that the rANS kernel does not read)
-            const uint32_t *sw = reinterpret_cast<const uint32_t *>(sym);
-            uint32_t *dw = reinterpret_cast<uint32_t *>(d);
-            for (uint32_t i = t; i < (n + 3) / 4; i += kThreads) dw[i] = sw[i];
-            uint32_t *dp = reinterpret_cast<uint32_t *>(d + ((n + 3) & ~3u));
-            for (uint32_t i = t; i < Pn; i += kThreads) dp[i] = pal[i];
-        }
-        __syncthreads();
-        pc.stop(5);  // arena
+        pc.stop(3);  // levels 4..1, arena
     }
     pc.flush();
 }
 
-// Interleaved rANS and the record of one brick per wavefront (Sec. 3.3):
-// symbol i to state i mod W, from the last symbol to the first; the words
-// of a step are placed by ballot rank in descending lane order, then
-// reversed into the record so that the decoder reads them in symbol order.
-__global__ __launch_bounds__(kThreads) void rans_kernel(EncArgs a) {
-    __shared__ uint32_t tf[2][16], tc[2][16];
-    __shared__ double trcp[2][16];
-    const uint32_t t = threadIdx.x, L = lane(), w = t >> 6;
-    if (t < 32) {
-        tf[t >> 4][t & 15] = a.f[t >> 4][t & 15];
-        tc[t >> 4][t & 15] = a.c[t >> 4][t & 15];
-        trcp[t >> 4][t & 15] = 1.0 / (double)a.f[t >> 4][t & 15];
-    }
-    __syncthreads();
-    constexpr uint32_t kWaves = kThreads / 64;
-    uint16_t *words = reinterpret_cast<uint16_t *>(a.wscratch + ((size_t)blockIdx.x * kWaves + w) * kWordsScratch);
-    const uint64_t xmax_unit = (uint64_t)((csv::kRansLower >> a.bits) << 16);
-    const uint32_t hdr = csv::record_header_words(kN);
+// Palette operations (P_0, else the smallest delta among the 16 entries
+// before it, else append; Alg. 2) of one brick's left-over children per
+// wavefront, then its symbol stream.  An append moves the window that the
+// next child searches, so appends are a chain, but only they: lanes hold 64
+// children and the place of each one's label among the last 17 entries; the
+// first child without a place is appended, which moves the places behind it
+// by one (or to 0), and those before it are final.  A brick of the 512^3
+// cells volume has about 300 left-over children and 100 appends; 63 us for
+// its 4,096 bricks (155 us with a step per child and outcomes in global
+// memory, 113 us with a counter for places in arena 2).
+constexpr uint32_t kOutcomes = 2048;  // left-over children whose outcome fits LDS
+__global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
+    __shared__ __align__(8) uint8_t cop_l[kWaves][kOutcomes];
+    __shared__ __align__(8) uint8_t del_l[kWaves][kOutcomes + 8 * kN + 8];
+    const uint32_t L = lane(), w = uniform(threadIdx.x >> 6);
     for (uint32_t id = blockIdx.x * kWaves + w; id < a.n_items; id += gridDim.x * kWaves) {
-        const uint32_t n = a.sn[id], Pn = a.sp[id], leaf = a.scum[(size_t)kN * id + 1];
-        const uint8_t *sym = a.sarena + a.soff[id];
-        const uint32_t *pal = reinterpret_cast<const uint32_t *>(sym + ((n + 3) & ~3u));
-        const uint32_t W = lanes_for(n, a.lane_k, a.lane_max);
-        uint32_t x = csv::kRansLower, pushed = 0;
-        if (n) {
-            constexpr int kBlk = 16;
-            for (int64_t s_hi = (int64_t)((n - 1) / W); s_hi >= 0; s_hi -= kBlk) {
-                uint32_t sy[kBlk];
+        BrickMeta *m = glob(a.meta) + id;
+        if (uniform(m->ok) == 0) continue;
+        uint32_t E[kN], NC[kN], Et = 0, nc = 0;
 #pragma unroll
-                for (int k = 0; k < kBlk; k++) {
-                    const int64_t s = s_hi - k;
-                    const uint32_t i = (uint32_t)s * W + L;
-                    sy[k] = (s >= 0 && L < W && i < n) ? (uint32_t)sym[i] : 0xFFu;
+        for (int k = 0; k < kN; k++) {
+            E[k] = uniform(m->E[k]);
+            NC[k] = uniform(m->NC[k]);
+            Et += E[k];
+            nc += NC[k];
+        }
+        const uint32_t *opw = glob(reinterpret_cast<const uint32_t *>(a.arena1 + m->off1));
+        const uint32_t *cand = opw + Et;
+        uint32_t win = uniform(m->root), P = 1;  // lane i: entry P - 1 - i
+        uint32_t lbn = L < nc ? cand[L] : 0u;    // labels from the next child on
+        uint32_t xn = L < Et ? opw[L] : 0u;      // operations from the next parent on
+        // arena 2: nibbles, palette, then, for bricks with many left-over
+        // children, a byte per child and its level's deltas from a multiple
+        // of 8 bytes on (else in LDS)
+        const bool small = nc <= kOutcomes;
+        const uint32_t ndw = (8 * Et + nc + 7) / 8 + 1;
+        uint32_t *nib = glob(reinterpret_cast<uint32_t *>(a.arena2 + part2(m->off1)));
+        uint32_t *pal = nib + ndw;
+        if (L == 0) pal[0] = win;
+        uint32_t n = 0;
+        uint32_t D[kN], d0[kN];
+        auto work = [&](auto *cop, auto *del) {
+            uint32_t c0 = 0, dp = 0;
+#pragma unroll
+            for (int lv = kN - 1; lv >= 0; lv--) {
+                d0[lv] = dp;
+                uint32_t d = 0;
+                for (uint32_t i0 = 0; i0 < NC[lv]; i0 += 64) {
+                    const uint32_t cn = min(64u, NC[lv] - i0), at = c0 + i0;
+                    const uint32_t lb = lbn;
+                    lbn = at + cn + L < nc ? cand[at + cn + L] : 0u;
+                    // each child's place in the window: 0 the last entry, 17
+                    // and more: none
+                    uint32_t pos = 32;
+#pragma unroll
+                    for (int i = 16; i >= 0; i--) {
+                        const uint32_t e = readlane(win, (uint32_t)i);
+                        pos = (uint32_t)i < P && lb == e ? (uint32_t)i : pos;
+                    }
+                    const uint32_t P0 = P;
+                    uint64_t ma = 0, todo = cn == 64 ? ~0ull : (1ull << cn) - 1ull;
+                    for (uint64_t miss; (miss = __ballot(pos > 16u) & todo) != 0;) {
+                        const uint32_t k = (uint32_t)__builtin_ctzll(miss), lc = readlane(lb, k);
+                        todo &= ~((2ull << k) - 1ull);
+                        ma |= 1ull << k;
+                        // (appended entries move through the lanes: DPP wave shift right by one)
+                        win = (uint32_t)__builtin_amdgcn_update_dpp((int)lc, (int)win, 0x138, 0xF, 0xF, false);
+                        P++;
+                        const uint32_t moved = lb == lc ? 0u : pos + 1u;
+                        pos = L > k ? moved : pos;
+                    }
+                    const bool in = L < cn, ap = (ma >> L) & 1u, dl = in && !ap && pos > 0;
+                    const uint64_t md = __ballot(dl);
+                    if (ap) pal[P0 + mbcnt(ma)] = lb;
+                    if (dl) del[dp + d + mbcnt(md)] = (uint8_t)(pos - 1u);
+                    // what turns the placeholder (P_a) into the operation
+                    if (in) cop[at + L] = (uint8_t)(ap ? 0u : (dl ? (csv::kPa ^ csv::kPd) : (csv::kPa ^ csv::kP0)));
+                    d += (uint32_t)__popcll(md);
+                }
+                c0 += NC[lv];
+                D[lv] = d;
+                dp = (dp + d + 7u) & ~7u;
+            }
+            own_stores();
+            // the stream: words of 8 nibbles appended behind sh pending ones,
+            // which are the top nibbles of cw
+            uint32_t op = 0, sh = 0, cw = 0, rk = 0, eb = 0;
+            auto append = [&](uint32_t x, uint32_t k) {  // k words, lane i holds word i
+                const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)cw, (int)x, 0x138, 0xF, 0xF, false);
+                const uint32_t o = sh ? __builtin_amdgcn_alignbit(x, prev, 32 - 4 * sh) : x;
+                if (L < k) nib[op + L] = o;
+                op += k;
+                cw = readlane(x, k - 1);
+            };
+#pragma unroll
+            for (int lv = kN - 1; lv >= 0; lv--) {
+                for (uint32_t i0 = 0; i0 < D[lv]; i0 += 512) {
+                    const uint32_t left = min(512u, D[lv] - i0), i = 8 * L;
+                    uint32_t x = 0;
+                    if (i < left) {
+                        const auto *b = reinterpret_cast<const uint32_t *>(del + d0[lv] + i0 + i);
+                        const uint32_t bx = b[0], by = b[1];
+                        const uint32_t lo = (bx | (bx >> 4)) & 0x00FF00FFu, hi = (by | (by >> 4)) & 0x00FF00FFu;
+                        x = ((lo | (lo >> 8)) & 0xFFFFu) | (((hi | (hi >> 8)) & 0xFFFFu) << 16);
+                    }
+                    const uint32_t k = left / 8, rem = left & 7u;
+                    if (k) append(x, k);
+                    if (rem) {  // (the last deltas of the level)
+                        const uint32_t v = readlane(x, k) & ((1u << (4 * rem)) - 1u);
+                        const uint32_t both = sh ? (cw >> (32 - 4 * sh)) | (v << (4 * sh)) : v;
+                        if (sh + rem >= 8) {
+                            if (L == 0) nib[op] = both;
+                            op++;
+                            const uint32_t over = sh + rem - 8;
+                            cw = over ? (v >> (4 * (8 - sh))) << (32 - 4 * over) : 0u;
+                            sh = over;
+                        } else {
+                            sh += rem;
+                            cw = both << (32 - 4 * sh);
+                        }
+                    }
+                }
+                for (uint32_t r0 = 0; r0 < E[lv]; r0 += 64) {
+                    const uint32_t k = min(64u, E[lv] - r0), nx = eb + r0 + k + L;
+                    uint32_t x = L < k ? xn : 0u;
+                    xn = nx < Et ? opw[nx] : 0u;
+                    // the placeholders, in the order of their children
+                    uint32_t left = zero_nibbles((x & 0x77777777u) ^ 0x66666666u);
+                    const uint32_t c = (uint32_t)__builtin_popcount(left), inc = wave_incl_scan(c);
+                    uint32_t at = rk + inc - c;
+                    while (left) {
+                        const uint32_t b = (uint32_t)__builtin_ctz(left);
+                        left &= left - 1u;
+                        x ^= (uint32_t)cop[at++] << b;
+                    }
+                    rk += readlane(inc, 63);
+                    append(x, k);
+                }
+                eb += E[lv];
+                n += D[lv] + 8 * E[lv];
+                if (L == 0) m->cum[lv] = n;
+            }
+            if (sh && L == 0) nib[op] = cw >> (32 - 4 * sh);
+        };
+        if (small) {
+            work(cop_l[w], del_l[w]);
+        } else {
+            uint8_t *cop = glob(reinterpret_cast<uint8_t *>((reinterpret_cast<uintptr_t>(pal + 1 + nc) + 7) & ~(uintptr_t)7));
+            work(cop, cop + ((nc + 7u) & ~7u));
+        }
+        wsync();  // the LDS is reused for this wave's next brick
+        if (L == 0) {
+            m->pal = ndw;
+            m->n = n;
+            m->P = P;
+        }
+        // the sampled bricks' symbols (the frequency tables, Sec. 3.4)
+        if (id % a.sample_stride == 0) {
+            own_stores();
+            const uint32_t leaf = n - D[0] - 8 * E[0];
+            for (uint32_t tb = 0; tb < 2; tb++) {
+                const uint32_t i0 = tb ? leaf : 0u, i1 = tb ? n : leaf;
+                uint32_t cnt[16] = {};
+#pragma unroll 4
+                for (uint32_t d = (i0 >> 3) + L; 8 * d < i1; d += 64) {
+                    const uint32_t x = nib[d];
+                    // a bit per symbol of the range
+                    uint32_t in = 0x11111111u;
+                    if (8 * d < i0) in &= ~0u << (4 * (i0 - 8 * d));
+                    if (8 * d + 8 > i1) in &= (1u << (4 * (i1 - 8 * d))) - 1u;
+                    const uint32_t b0 = x, b1 = x >> 1, b2 = x >> 2, b3 = x >> 3;
+                    const uint32_t lo[4] = {~b0 & ~b1, b0 & ~b1, ~b0 & b1, b0 & b1};
+                    const uint32_t hi[4] = {in & ~b2 & ~b3, in & b2 & ~b3, in & ~b2 & b3, in & b2 & b3};
+#pragma unroll
+                    for (int v = 0; v < 16; v++) cnt[v] += (uint32_t)__builtin_popcount(lo[v & 3] & hi[v >> 2]);
                 }
 #pragma unroll
-                for (int k = 0; k < kBlk; k++) {
-                    const int64_t s = s_hi - k;
-                    const uint32_t i = (uint32_t)s * W + L;
-                    const bool act = sy[k] != 0xFFu;  // (false for every lane once s < 0)
-                    bool emit = false;
-                    uint32_t wd = 0;
-                    if (act) {
-                        const uint32_t tb = i >= leaf ? 1u : 0u;
-                        const uint32_t f = tf[tb][sy[k]], c = tc[tb][sy[k]];
-                        uint32_t v = x;
-                        if ((uint64_t)v >= xmax_unit * f) {
-                            emit = true;
-                            wd = v & 0xFFFFu;
-                            v >>= 16;
-                        }
-                        // v / f: a double reciprocal is within one of the
-                        // quotient; the remainder corrects it
-                        uint32_t q = (uint32_t)((double)v * trcp[tb][sy[k]]);
-                        int64_t r = (int64_t)v - (int64_t)q * f;
-                        if (r < 0) {
-                            q--;
-                            r += f;
-                        } else if (r >= (int64_t)f) {
-                            q++;
-                            r -= f;
-                        }
-                        x = (q << a.bits) + (uint32_t)r + c;
-                    }
-                    // the host order within a step is descending lanes
-                    const uint64_t em = __ballot(emit);
-                    if (emit) words[pushed + (uint32_t)__popcll(L == 63 ? 0ull : (em >> (L + 1)))] = (uint16_t)wd;
-                    pushed += (uint32_t)__popcll(em);
+                for (int v = 0; v < 16; v++) {
+                    const uint32_t c = readlane(wave_incl_scan(cnt[v]), 63);
+                    if (L == 0 && c) atomicAdd(&glob(a.ctl)->hist[tb][v], (unsigned long long)c);
                 }
             }
         }
+    }
+}
+
+// Interleaved rANS and the record of one brick per wavefront (Sec. 3.3):
+// symbol i to state i mod W, from the last symbol to the first; the words
+// of a step go to descending lanes, so they are placed from the end of the
+// wave's scratch towards its start, where the decoder's order begins.
+// Division by a frequency is a multiply by its 32-bit reciprocal with one
+// correction.  The chain of a step is a dozen operations (the symbols and
+// table entries of 16 steps are fetched ahead, the words gathered in LDS);
+// bound by vector issue: 82 us for the 4,096 bricks (122 us with a store per
+// word, tables unpacked in every step and a double reciprocal).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void rans_kernel(EncArgs a) {
+    // per table and symbol: the reciprocal m, f | s << 24, 2^bits - f and the
+    // start c of its slots; with 2^s < f <= 2^(s + 1), v / f is
+    // (v m >> 32 >> s) or one more
+    __shared__ uint4 tab[32];
+    __shared__ uint32_t freq[32];
+    // per wave: the packed symbols of a block of 16 steps, the last 1024 words
+    __shared__ uint32_t sym_l[kWaves][128];
+    __shared__ __align__(16) uint16_t word_l[kWaves][1024];
+    const uint32_t t = threadIdx.x, L = lane(), w = uniform(t >> 6), bits = a.bits, M = 1u << bits;
+    if (t < 32) {  // the host compressor's normalisation of the counts
+        const uint32_t k = t >> 4, q = t & 15u;
+        const unsigned long long *h0 = glob(a.ctl)->hist[0], *h1 = glob(a.ctl)->hist[1];
+        uint64_t tot = 0;
+        for (uint32_t s = 0; s < 16; s++) tot += (a.one_table ? h0[s] + h1[s] : (k ? h1[s] : h0[s])) + 1;
+        const uint64_t c = (a.one_table ? h0[q] + h1[q] : (k ? h1[q] : h0[q])) + 1, v = c * M / tot;
+        freq[t] = v ? (uint32_t)v : 1u;
+    }
+    __syncthreads();
+    if (t < 2) {
+        uint32_t *f = freq + 16 * t, sum = 0, best = 0;
+        for (uint32_t s = 0; s < 16; s++) sum += f[s];
+        if (sum < M) {
+            for (uint32_t s = 1; s < 16; s++)
+                if (f[s] > f[best]) best = s;
+            f[best] += M - sum;
+        }
+        for (; sum > M; sum--) {
+            best = 16;
+            for (uint32_t s = 0; s < 16; s++)
+                if (f[s] > 1 && (best == 16 || f[s] > f[best])) best = s;
+            f[best]--;
+        }
+    }
+    __syncthreads();
+    if (t < 32) {
+        const uint32_t f = freq[t];
+        uint32_t c = 0, s = 0;
+        for (uint32_t k = t & 16u; k < t; k++) c += freq[k];
+        while ((2u << s) < f) s++;
+        const uint64_t m = ((uint64_t)1 << (32 + s)) / f;
+        tab[t] = make_uint4(m >> 32 ? 0xFFFFFFFFu : (uint32_t)m, f | (s << 24), M - f, c);
+        if (blockIdx.x == 0) glob(a.ctl)->freq[t >> 4][t & 15] = (uint16_t)f;
+    }
+    __syncthreads();
+    // word i of a brick goes to LDS place 1023 - (i mod 1024), and each 512 of
+    // them in one store per lane to the scratch, which fills downwards
+    uint8_t *wend = glob(a.wscratch) + ((size_t)blockIdx.x * kWaves + w + 1) * kWordsScratch - 64;
+    uint16_t *words = word_l[w];
+    uint32_t *syms = sym_l[w];
+    const uint32_t hdr = csv::record_header_words(kN);
+    for (uint32_t id = blockIdx.x * kWaves + w; id < a.n_items; id += gridDim.x * kWaves) {
+        const BrickMeta *bm = glob(a.meta) + id;
+        if (uniform(bm->ok) == 0u) continue;
+        const uint32_t n = uniform(bm->n), Pn = uniform(bm->P), leaf = uniform(bm->cum[1]);
+        const uint32_t *nib = glob(reinterpret_cast<const uint32_t *>(a.arena2 + part2(bm->off1)));
+        const uint32_t *pal = nib + bm->pal;
+        const uint32_t W = lanes_for(n, a.lane_k, a.lane_max);
+        uint32_t x = csv::kRansLower, pushed = 0, kept = 0;
+        auto flush = [&]() {  // words kept .. kept + 511
+            wsync();
+            const uint4 v = *reinterpret_cast<const uint4 *>(words + 512 - (kept & 1023u) + 8 * L);
+            kept += 512;
+            *reinterpret_cast<uint4 *>(wend - 2 * (size_t)kept + 16 * L) = v;
+            wsync();
+        };
+        if (n) {
+            // blocks of 16 steps from a multiple of 16 steps on, the last
+            // first; their symbols are 2 W dwords, loaded a block ahead
+            constexpr int kBlk = 16;
+            const uint32_t steps = (n + W - 1) / W, ndw = (n + 7) / 8;
+            uint32_t blk = (steps - 1) / kBlk;
+            auto fetch = [&](uint32_t b) -> uint2 {
+                const uint32_t d = 2 * W * b + L;
+                return make_uint2(L < 2 * W && d < ndw ? nib[d] : 0u, L + 64 < 2 * W && d + 64 < ndw ? nib[d + 64] : 0u);
+            };
+            const uint64_t lanes = W == 64 ? ~0ull : (1ull << W) - 1ull;
+            uint2 next = fetch(blk);
+            // all: every state of the block has a symbol in every step
+            auto block = [&](auto all) {
+                wsync();
+                syms[L] = next.x;
+                syms[L + 64] = next.y;
+                wsync();
+                if (blk) next = fetch(blk - 1);
+                uint4 te[kBlk];
+#pragma unroll
+                for (int k = 0; k < kBlk; k++) {
+                    const uint32_t j = (uint32_t)(kBlk - 1 - k) * W + L, i = kBlk * W * blk + j;
+                    const uint32_t sy = (syms[(j >> 3) & 127u] >> (4 * (j & 7u))) & 15u;
+                    te[k] = tab[sy + (i >= leaf ? 16u : 0u)];
+                }
+#pragma unroll
+                for (int k = 0; k < kBlk; k++) {
+                    const uint4 e = te[k];
+                    bool act = true;
+                    if constexpr (!decltype(all)::value)
+                        act = kBlk * W * blk + (uint32_t)(kBlk - 1 - k) * W + L < n && L < W;
+                    // (the shift leaves f alone of e.y)
+                    const bool full = x >= e.y << (32 - bits) && act;
+                    const uint64_t em = __ballot(full) & lanes;
+                    const uint32_t v = full ? x >> 16 : x;
+                    // the host order within a step is descending lanes
+                    const uint32_t cnt = (uint32_t)__popcll(em);
+                    if ((em >> L) & 1ull) words[(mbcnt(em) - pushed - cnt) & 1023u] = (uint16_t)x;
+                    pushed += cnt;
+                    uint32_t q = __umulhi(v, e.x) >> (e.y >> 24);
+                    q += v - __umul24(q, e.y) >= (e.y & 0xFFFFFFu) ? 1u : 0u;
+                    const uint32_t y = __umul24(q, e.z) + v + e.w;
+                    x = act ? y : x;
+                    if (pushed - kept >= 512) flush();
+                }
+            };
+            if (n % (kBlk * W)) {
+                block(std::false_type{});
+                if (blk-- == 0) blk = 0xFFFFFFFFu;
+            }
+            for (; blk != 0xFFFFFFFFu; blk--) block(std::true_type{});
+            // the rest (up to 511 words), in a whole store: what lies before
+            // them is not read
+            if (pushed != kept) flush();
+        }
         const uint32_t nw = pushed;
         const uint32_t size = (4 * (hdr + Pn + W) + 2 * nw + 3) & ~3u;
-        uint32_t lo = 0, hi = 0;
-        if (L == 0) {
-            const uint64_t o = atomicAdd(a.arena_top, (unsigned long long)size);
-            a.sizes[id] = size;
-            a.aoff[id] = o;
-            lo = (uint32_t)o;
-            hi = (uint32_t)(o >> 32);
+        // behind the palette in arena 2; a record larger than its nibbles
+        // (symbols unlike the sampled ones) takes a part of arena 3
+        uint64_t at = reinterpret_cast<uintptr_t>(pal + Pn);
+        bool room = 2 * (uint64_t)nw <= 4ull * bm->pal;
+        if (!room) {
+            uint64_t off = 0;
+            if (L == 0) off = atomicAdd(&glob(a.ctl)->top3, (unsigned long long)size);
+            off = (uint64_t)readlane((uint32_t)off, 0) | ((uint64_t)readlane((uint32_t)(off >> 32), 0) << 32);
+            room = off + size <= a.cap3;
+            at = reinterpret_cast<uintptr_t>(a.arena3) + off;
         }
-        const uint64_t off = ((uint64_t)(uint32_t)__shfl((int)hi, 0) << 32) | (uint32_t)__shfl((int)lo, 0);
-        // this wavefront's word stores before its own loads of them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (off + size <= a.arena_cap) {
-            uint32_t *r = reinterpret_cast<uint32_t *>(a.arena + off);
+        if (L == 0) {
+            a.sizes[id] = size;
+            a.aoff[id] = at;
+        }
+        own_stores();
+        if (room) {
+            uint32_t *r = glob(reinterpret_cast<uint32_t *>(at));
             if (L == 0) {
                 r[0] = Pn;
                 r[1] = W;
                 r[2] = nw;
-                for (int m = 0; m < kN; m++) r[3 + m] = a.scum[(size_t)kN * id + m];
+                for (int m = 0; m < kN; m++) r[3 + m] = bm->cum[m];
             }
-            for (uint32_t i = L; i < Pn; i += 64) r[hdr + i] = pal[i];
+            // eight loads in flight per lane
+            auto copy = [&](uint32_t *to, uint32_t cnt, auto get) {
+                for (uint32_t q0 = 0; q0 < cnt; q0 += 512) {
+                    uint32_t v[8];
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; k++) {
+                        const uint32_t q = q0 + 64 * k + L;
+                        v[k] = q < cnt ? get(q) : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t k = 0; k < 8; k++) {
+                        const uint32_t q = q0 + 64 * k + L;
+                        if (q < cnt) to[q] = v[k];
+                    }
+                }
+            };
+            copy(r + hdr, Pn, [&](uint32_t q) -> uint32_t { return pal[q]; });
             if (L < W) r[hdr + Pn + L] = x;
-            uint16_t *wr = reinterpret_cast<uint16_t *>(r + hdr + Pn + W);
-            for (uint32_t q = L; q < nw; q += 64) wr[q] = words[nw - 1 - q];
-            if (L == 0 && (nw & 1u)) wr[nw] = 0;
+            // the words lie in order from -nw on; dwords from an even place
+            uint32_t *wr = r + hdr + Pn + W;
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(wend) - (nw + 1) / 2;
+            if (nw & 1u)
+                copy(wr, (nw + 1) / 2, [&](uint32_t q) -> uint32_t {
+                    const uint32_t hi = 2 * q + 1 < nw ? src[q + 1] : 0u;
+                    return (src[q] >> 16) | (hi << 16);
+                });
+            else
+                copy(wr, nw / 2, [&](uint32_t q) -> uint32_t { return src[q]; });
         }
         // the words region is reused by this wavefront's next brick
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        own_stores();
     }
 }
 
-// exclusive scan of the record sizes into the container's u64 index
-__global__ __launch_bounds__(1024) void scan_kernel(const uint32_t *sizes, uint32_t n, uint64_t *index) {
-    __shared__ uint64_t part[1024];
-    const uint32_t t = threadIdx.x;
+// whether every arena held what was asked of it (else the host repeats the
+// launches, and the sizes and offsets of some bricks are not written)
+__device__ __forceinline__ bool arenas_held(const EncArgs &a) {
+    const EncCtl *c = glob(a.ctl);
+    return c->top1 <= a.cap1 && c->top3 <= a.cap3;
+}
+
+// exclusive scan of the record sizes into the container's u64 index: four
+// sizes per thread and round, a wave scan, the waves' sums in LDS
+__global__ __launch_bounds__(1024) void scan_kernel(EncArgs a, uint64_t *index) {
+    __shared__ uint64_t part[16];
+    if (!arenas_held(a)) return;
+    const uint32_t t = threadIdx.x, L = lane(), w = t >> 6, n = a.n_items;
     uint64_t carry = 0;
-    for (uint32_t b0 = 0; b0 < n; b0 += 1024) {
-        const uint64_t v = b0 + t < n ? sizes[b0 + t] : 0;
-        part[t] = v;
-        __syncthreads();
-        for (uint32_t d = 1; d < 1024; d <<= 1) {
-            const uint64_t o = t >= d ? part[t - d] : 0;
-            __syncthreads();
-            part[t] += o;
-            __syncthreads();
+    for (uint32_t b0 = 0; b0 < n; b0 += 4096) {
+        const uint32_t i = b0 + 4 * t;
+        uint32_t v[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            v[k] = i + k < n && i + k >= i ? a.sizes[i + k] : 0u;
+            sum += v[k];  // (a record is below 2^20 bytes)
         }
-        if (b0 + t < n) index[b0 + t] = carry + part[t] - v;
-        carry += part[1023];
+        const uint32_t inc = wave_incl_scan(sum);
+        if (L == 63) part[w] = inc;
+        __syncthreads();
+        uint64_t before = carry, all = carry;
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k++) {
+            before += k < w ? part[k] : 0ull;
+            all += part[k];
+        }
+        uint64_t o = before + inc - sum;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            if (i + k < n && i + k >= i) index[i + k] = o;
+            o += v[k];
+        }
+        carry = all;
         __syncthreads();
     }
-    if (t == 0) index[n] = carry;
+    if (t == 0) {
+        index[n] = carry;
+        glob(a.ctl)->total = carry;
+    }
 }
 
-// records from the arena to their place in the container's record area
-__global__ __launch_bounds__(256) void pack_kernel(const uint8_t *arena, const uint64_t *aoff, const uint32_t *sizes,
-                                                   const uint64_t *index, uint32_t n, uint8_t *records) {
-    for (uint32_t id = blockIdx.x; id < n; id += gridDim.x) {
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(arena + aoff[id]);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(records + index[id]);
-        const uint32_t nd = sizes[id] / 4;
-        for (uint32_t i = threadIdx.x; i < nd; i += 256) dst[i] = src[i];
+// records from the arenas to their place in the container's record area of
+// cap bytes
+__global__ __launch_bounds__(256) void pack_kernel(EncArgs a, const uint64_t *index, uint8_t *records,
+                                                   uint64_t cap) {
+    if (!arenas_held(a)) return;
+    for (uint32_t id = blockIdx.x; id < a.n_items; id += gridDim.x) {
+        const uint32_t *src = glob(reinterpret_cast<const uint32_t *>(a.aoff[id]));
+        const uint64_t at = index[id], size = a.sizes[id];
+        if (at + size > cap) return;  // (the host repeats the copy)
+        uint32_t *dst = glob(reinterpret_cast<uint32_t *>(records + at));
+        for (uint32_t i = threadIdx.x; i < size / 4; i += 256) dst[i] = src[i];
     }
 }
 
@@ -621,20 +1011,23 @@ struct DevBuf {
 // per device: the buffers of the last call, kept for the next one
 struct EncCache {
     std::mutex mu;
-    DevBuf scratch, wscratch, hist, sizes, aoff, top, arena, dblob, sarena, smeta;
+    DevBuf scratch, wscratch, ctl, meta, sizes, aoff, arena1, arena2, arena3, dblob;
+    EncCtl *h_ctl = nullptr;   // pinned
     uint8_t *h_pin = nullptr;  // pinned staging of the container on its way to host memory
     size_t h_pin_bytes = 0;
     void release() {
         scratch.release();
         wscratch.release();
-        sarena.release();
-        smeta.release();
-        hist.release();
+        ctl.release();
+        meta.release();
         sizes.release();
         aoff.release();
-        top.release();
-        arena.release();
+        arena1.release();
+        arena2.release();
+        arena3.release();
         dblob.release();
+        if (h_ctl) (void)hipHostFree(h_ctl);
+        h_ctl = nullptr;
         if (h_pin) (void)hipHostFree(h_pin);
         h_pin = nullptr;
         h_pin_bytes = 0;
@@ -686,23 +1079,33 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     int cu = 0;
     if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cu < 1) cu = 1;
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(B64, (uint64_t)cu * 5);  // symbols kernel: 5 workgroups per CU
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(B64, (uint64_t)cu);  // reuse kernel: a workgroup per CU
+    const uint32_t grid2 = (uint32_t)std::min<uint64_t>((B64 + kWaves - 1) / kWaves, (uint64_t)cu * 4);
     const uint64_t raw = (uint64_t)nx * ny * nz * 4;
-    uint64_t cap = std::max<uint64_t>(16ull << 20, raw / 8);
+    const uint64_t rs = csv::record_area_offset(B);
     EncCache *ec = cache_for(device);
     if (!ec) return CSV_ENOMEM;
     std::lock_guard<std::mutex> lk(ec->mu);  // one compression per device at a time
-    DevBuf &scratch = ec->scratch, &wscratch = ec->wscratch, &hist = ec->hist, &sizes = ec->sizes,
-           &aoff = ec->aoff, &top = ec->top, &arena = ec->arena, &dblob = ec->dblob, &sarena = ec->sarena,
-           &smeta = ec->smeta;
-    const uint32_t waves2 = (uint32_t)std::min<uint64_t>((B64 + 3) / 4, (uint64_t)cu * 4) * 4;
-    uint64_t scap = std::max<uint64_t>(16ull << 20, raw / 8);
-    if (!scratch.ensure(kScratch * grid) || !wscratch.ensure(kWordsScratch * waves2) || !hist.ensure(32 * 8) ||
-        !sizes.ensure(4ull * B) || !aoff.ensure(8ull * B) || !top.ensure(16) || !arena.ensure(cap) ||
-        !sarena.ensure(scap) || !smeta.ensure((8ull + 4 + 4 + 4 * kN) * B))
+    // arena 1 at first for a part of 1/12 of the labels (dense cells take
+    // 1/15), or of 1/64 where that does not fit the device
+    auto arenas = [&](uint64_t cap1) -> bool {
+        return ec->arena1.ensure(cap1) && ec->arena2.ensure(part2(ec->arena1.bytes));
+    };
+    if (!ec->scratch.ensure(kScratch * grid) || !ec->wscratch.ensure(kWordsScratch * grid2 * kWaves) ||
+        !ec->ctl.ensure(sizeof(EncCtl)) || !ec->meta.ensure(sizeof(BrickMeta) * (size_t)B) || !ec->sizes.ensure(4ull * B) ||
+        !ec->aoff.ensure(8ull * B) || !ec->arena3.ensure(1ull << 20))
         return CSV_ENOMEM;
-    cap = arena.bytes;
-    scap = sarena.bytes;
+    if (!arenas(std::max<uint64_t>(16ull << 20, raw / 12)) && !arenas(std::max<uint64_t>(16ull << 20, raw / 64)))
+        return CSV_ENOMEM;
+    if (!ec->dblob.ensure(rs + std::max<uint64_t>(16ull << 20, raw / 32))) return CSV_ENOMEM;
+    if (!ec->h_ctl &&
+        hipHostMalloc(reinterpret_cast<void **>(&ec->h_ctl), sizeof(EncCtl), hipHostMallocDefault) != hipSuccess)
+        return CSV_ENOMEM;
+    static std::once_flag once;
+    std::call_once(once, [] {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(reuse_kernel),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ReuseLds));
+    });
     EncArgs a;
     std::memset(&a, 0, sizeof(a));
     a.vol = labels;
@@ -716,72 +1119,50 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
     a.bits = o.scale_bits;
     a.lane_k = o.lane_k;
     a.lane_max = o.lane_max;
-    a.scratch = scratch.as<uint8_t>();
-    a.wscratch = wscratch.as<uint8_t>();
-    a.hist = hist.as<unsigned long long>();
-    a.arena_top = top.as<unsigned long long>();
-    a.sarena_top = top.as<unsigned long long>() + 1;
-    a.sizes = sizes.as<uint32_t>();
-    a.aoff = aoff.as<uint64_t>();
-    a.soff = smeta.as<uint64_t>();
-    a.sn = reinterpret_cast<uint32_t *>(a.soff + B);
-    a.sp = a.sn + B;
-    a.scum = a.sp + B;
-    // symbols of every brick (and the sampled bricks' histograms); a second
-    // pass with the exact arena size if they did not fit
-    uint64_t used = 0;
-    for (int pass = 0; pass < 2; pass++) {
-        a.sarena = sarena.as<uint8_t>();
-        a.sarena_cap = scap;
-        if (hipMemsetAsync(a.hist, 0, 32 * 8, s) != hipSuccess || hipMemsetAsync(a.sarena_top, 0, 8, s) != hipSuccess)
-            return CSV_EHIP;
-        hipLaunchKernelGGL(symbols_kernel, dim3(grid), dim3(kThreads), 0, s, a);
+    a.one_table = o.tables == 1 ? 1u : 0u;
+    a.ctl = ec->ctl.as<EncCtl>();
+    a.meta = ec->meta.as<BrickMeta>();
+    a.scratch = ec->scratch.as<uint8_t>();
+    a.wscratch = ec->wscratch.as<uint8_t>();
+    a.sizes = ec->sizes.as<uint32_t>();
+    a.aoff = ec->aoff.as<uint64_t>();
+    // all launches in one go; repeated with larger arenas if one was short
+    // (arena 3's demand is only known once arena 1 held)
+    const uint32_t grid_p = std::min<uint32_t>(B, (uint32_t)cu * 8);
+    for (int pass = 0;; pass++) {
+        a.arena1 = ec->arena1.as<uint8_t>();
+        a.arena2 = ec->arena2.as<uint8_t>();
+        a.arena3 = ec->arena3.as<uint8_t>();
+        a.cap1 = ec->arena1.bytes;
+        a.cap3 = ec->arena3.bytes;
+        uint64_t *index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
+        if (hipMemsetAsync(a.ctl, 0, sizeof(EncCtl), s) != hipSuccess) return CSV_EHIP;
+        hipLaunchKernelGGL(reuse_kernel, dim3(grid), dim3(kReuseThreads), sizeof(ReuseLds), s, a);
+        hipLaunchKernelGGL(palette_kernel, dim3(grid2), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(rans_kernel, dim3(grid2), dim3(kThreads), 0, s, a);
+        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a, index);
+        hipLaunchKernelGGL(pack_kernel, dim3(grid_p), dim3(256), 0, s, a, (const uint64_t *)index,
+                           ec->dblob.as<uint8_t>() + rs, ec->dblob.bytes - rs);
         if (hipGetLastError() != hipSuccess ||
-            hipMemcpyAsync(&used, a.sarena_top, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipMemcpyAsync(ec->h_ctl, a.ctl, sizeof(EncCtl), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess)
             return CSV_EHIP;
-        if (used <= scap) break;
-        scap = used;
-        if (pass == 1 || !sarena.ensure(scap)) return CSV_ENOMEM;
-    }
-    uint64_t cnt[2][16];
-    if (hipMemcpy(cnt, a.hist, sizeof(cnt), hipMemcpyDeviceToHost) != hipSuccess) return CSV_EHIP;
-    if (o.tables == 1)  // one table for all symbols
-        for (int q = 0; q < 16; q++) cnt[0][q] = cnt[1][q] = cnt[0][q] + cnt[1][q];
-    uint32_t f[2][16];
-    for (int k = 0; k < 2; k++) {
-        csv::normalize_counts(cnt[k], 1u << o.scale_bits, f[k]);
-        uint32_t c = 0;
-        for (int q = 0; q < 16; q++) {
-            a.f[k][q] = f[k][q];
-            a.c[k][q] = c;
-            c += f[k][q];
+        const EncCtl &c = *ec->h_ctl;
+        if (c.top1 <= a.cap1 && c.top3 <= a.cap3) {
+            if (rs + c.total <= ec->dblob.bytes) break;
+            // the records did not fit the container's buffer
+            if (!ec->dblob.ensure(rs + c.total)) return CSV_ENOMEM;
+            index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
+            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a, index);
+            hipLaunchKernelGGL(pack_kernel, dim3(grid_p), dim3(256), 0, s, a, (const uint64_t *)index,
+                               ec->dblob.as<uint8_t>() + rs, ec->dblob.bytes - rs);
+            if (hipGetLastError() != hipSuccess) return CSV_EHIP;
+            break;
         }
+        if (pass == 2 || !arenas(c.top1) || !ec->arena3.ensure(c.top3)) return CSV_ENOMEM;
     }
-    // rANS and records, a wavefront per brick; a second pass with the exact
-    // arena size if the records did not fit
-    for (int pass = 0; pass < 2; pass++) {
-        a.arena = arena.as<uint8_t>();
-        a.arena_cap = cap;
-        if (hipMemsetAsync(a.arena_top, 0, 8, s) != hipSuccess) return CSV_EHIP;
-        hipLaunchKernelGGL(rans_kernel, dim3(waves2 / 4), dim3(kThreads), 0, s, a);
-        if (hipGetLastError() != hipSuccess ||
-            hipMemcpyAsync(&used, a.arena_top, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return CSV_EHIP;
-        if (used <= cap) break;
-        cap = used;
-        if (pass == 1 || !arena.ensure(cap)) return CSV_ENOMEM;
-    }
-    // container: header (host), index (device scan), records (device copy)
-    const uint64_t rs = csv::record_area_offset(B);
-    const uint64_t total = rs + used;
-    if (!dblob.ensure(total)) return CSV_ENOMEM;
-    uint64_t *index = reinterpret_cast<uint64_t *>(dblob.as<uint8_t>() + csv::kHeaderBytes);
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a.sizes, B, index);
-    hipLaunchKernelGGL(pack_kernel, dim3(std::min<uint32_t>(B, (uint32_t)cu * 8)), dim3(256), 0, s,
-                       (const uint8_t *)a.arena, (const uint64_t *)a.aoff, (const uint32_t *)a.sizes,
-                       (const uint64_t *)index, B, dblob.as<uint8_t>() + rs);
+    const uint64_t total = rs + ec->h_ctl->total;
+    DevBuf &dblob = ec->dblob;
     if (ec->h_pin_bytes < total) {
         if (ec->h_pin) (void)hipHostFree(ec->h_pin);
         ec->h_pin = nullptr;
@@ -790,8 +1171,7 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
             return CSV_ENOMEM;
         ec->h_pin_bytes = total;
     }
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(ec->h_pin, dblob.p, total, hipMemcpyDeviceToHost, s) != hipSuccess ||
+    if (hipMemcpyAsync(ec->h_pin, dblob.p, total, hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return CSV_EHIP;
     uint8_t *out = static_cast<uint8_t *>(std::malloc(total));
@@ -823,7 +1203,7 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
     h.lane_max = o.lane_max;
     h.sample_stride = stride;
     for (int k = 0; k < 2; k++)
-        for (int q = 0; q < 16; q++) h.freq[k][q] = (uint16_t)f[k][q];
+        for (int q = 0; q < 16; q++) h.freq[k][q] = ec->h_ctl->freq[k][q];
     std::memcpy(out, &h, sizeof(h));
     const uint64_t idx_end = csv::kHeaderBytes + 8ull * (B + 1);
     std::memset(out + idx_end, 0, rs - idx_end);  // padding before the record area

@@ -1,0 +1,63 @@
+"""The GPU compressor where its paths part: ragged volumes and row strides,
+numbers of states per brick and symbols per block, records that do not fit
+where they are usually written, bricks with few and many palette operations."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def csvlib():
+    torch_cuda()
+    import paper_2308_16619_amd as csv
+    csv.lib()
+    return csv
+
+
+def check(csvlib, orc, vol, **kw):
+    opts = {"scale_bits": 10, "lane_k": 64, "lane_max": 64, **kw}
+    print("[gpu-test] encode %s %s" % (vol.shape, opts), flush=True)
+    got = csvlib.encode_volume_gpu(np.ascontiguousarray(vol), **opts)
+    assert got == orc.encode_volume(vol, **opts)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 65), (65, 1, 1), (31, 33, 32), (32, 32, 33), (64, 40, 97),
+                                   (33, 96, 129), (96, 31, 34)])
+def test_ragged_volumes(csvlib, orc, shape):
+    n = max(shape)
+    vol = synth.cells(n=n, grid=max(2, n // 6), seed=n)[:shape[0], :shape[1], :shape[2]]
+    check(csvlib, orc, vol, sample_stride=2)
+
+
+@pytest.mark.parametrize("lane_k,lane_max,bits", [(64, 64, 8), (64, 32, 12), (1, 64, 10), (7, 16, 9), (64, 8, 11),
+                                                  (3, 4, 10), (1, 2, 10), (1, 1, 12)])
+def test_states_and_blocks(csvlib, orc, lane_k, lane_max, bits):
+    # 40 labels a brick down to 1: from 0 symbols to thousands, so that last
+    # blocks of 16 steps are whole, partial and the only one
+    vol = synth.cells(n=96, grid=9, seed=bits + lane_k)
+    vol[:32, :32, :32] = 4
+    vol[32:64, :32, :32] = np.where(np.arange(32)[:, None, None] < 16, 4, 5)
+    vol[:32, 32:64, :32][0, 0, 0] = 77
+    check(csvlib, orc, vol, lane_k=lane_k, lane_max=lane_max, scale_bits=bits, sample_stride=1)
+
+
+def test_records_larger_than_their_nibbles(csvlib, orc):
+    # the only sampled brick is smooth, so that the tables give the others'
+    # symbols up to 12 bits
+    vol = np.random.default_rng(5).integers(1, 40, (96, 96, 128)).astype(np.uint32)
+    vol[:32, :32, :32] = 1
+    vol[:16, :32, :32] = 2
+    check(csvlib, orc, vol, scale_bits=12)
+
+
+@pytest.mark.parametrize("labels", [2, 17, 18, 60, 5000])
+def test_palette_window(csvlib, orc, labels):
+    # the last 17 entries: every label in it, one too many, most appended
+    vol = np.random.default_rng(labels).integers(0, labels, (64, 64, 64)).astype(np.uint32)
+    vol[32:] = np.repeat(np.repeat(np.repeat(vol[:16, :32, :32], 2, 0), 2, 1), 2, 2)
+    check(csvlib, orc, vol, sample_stride=1)
+    check(csvlib, orc, vol, tables=1)
