@@ -108,6 +108,16 @@ void csv_free(void *p);
  */
 int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz, const csv_encode_opts *opts,
                           int device, void *stream, uint8_t **blob, size_t *blob_bytes);
+/*
+ * csv_encode_volume_gpu into memory of the caller's: alloc(bytes, ctx) is
+ * called once, by the calling thread, when the container's size is known,
+ * and returns where it goes (NULL: CSV_ENOMEM).  If the call fails after
+ * that, the memory's content is undefined; it stays the caller's either way.
+ * alloc must not call the GPU compressor.
+ */
+int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
+                                const csv_encode_opts *opts, int device, void *stream,
+                                void *(*alloc)(size_t bytes, void *ctx), void *ctx, size_t *blob_bytes);
 /* Free the buffers csv_encode_volume_gpu keeps for `device` (waits for the device). */
 int csv_encode_gpu_release(int device);
 

@@ -22,6 +22,11 @@ MAX_LOD = 5
 CSV_OK, CSV_EINVAL, CSV_ERANGE, CSV_ECORRUPT, CSV_ENOMEM, CSV_EHIP, CSV_EBUSY, CSV_EDETAIL = 0, -1, -2, -3, -4, -5, -6, -7
 CSV_DETAIL_HOST = 1
 _lib = None
+_ALLOC = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)
+_new_bytes = ctypes.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.restype, _new_bytes.argtypes = ctypes.py_object, [ctypes.c_void_p, ctypes.c_ssize_t]
+_bytes_at = ctypes.pythonapi.PyBytes_AsString
+_bytes_at.restype, _bytes_at.argtypes = ctypes.c_void_p, [ctypes.py_object]
 
 
 class CsvError(RuntimeError):
@@ -113,6 +118,8 @@ def lib():
                                         ctypes.POINTER(ctypes.c_size_t)]
         L.csv_encode_volume_gpu.argtypes = [vp, u32, u32, u32, ctypes.POINTER(EncodeOpts), i32, vp,
                                             ctypes.POINTER(vp), ctypes.POINTER(ctypes.c_size_t)]
+        L.csv_encode_volume_gpu_alloc.argtypes = [vp, u32, u32, u32, ctypes.POINTER(EncodeOpts), i32, vp, _ALLOC, vp,
+                                                  ctypes.POINTER(ctypes.c_size_t)]
         L.csv_encode_gpu_release.argtypes = [i32]
         L.csv_free.argtypes = [vp]
         L.csv_blob_info.argtypes = [vp, ctypes.c_size_t, ctypes.POINTER(VolumeInfo)]
@@ -217,14 +224,20 @@ def encode_volume_gpu(vol, brick_log2: int = 5, scale_bits: int = 10, lane_k: in
     vol = vol.contiguous()
     nz, ny, nx = vol.shape
     o = EncodeOpts(brick_log2, scale_bits, lane_k, lane_max, sample_stride, 0, tables, 0)
-    p = ctypes.c_void_p()
     n = ctypes.c_size_t()
-    _chk(L.csv_encode_volume_gpu(ctypes.c_void_p(vol.data_ptr()), nx, ny, nz, ctypes.byref(o), vol.device.index or 0,
-                                 _stream_handle(stream), ctypes.byref(p), ctypes.byref(n)), "csv_encode_volume_gpu")
-    try:
-        return ctypes.string_at(p, n.value)
-    finally:
-        L.csv_free(p)
+    out = []
+
+    def alloc(size, ctx):  # the container is written straight into the bytes object
+        try:
+            out.append(_new_bytes(None, size))
+            return _bytes_at(out[0])
+        except (MemoryError, OverflowError):
+            return None
+
+    _chk(L.csv_encode_volume_gpu_alloc(ctypes.c_void_p(vol.data_ptr()), nx, ny, nz, ctypes.byref(o),
+                                       vol.device.index or 0, _stream_handle(stream), _ALLOC(alloc), None,
+                                       ctypes.byref(n)), "csv_encode_volume_gpu")
+    return out[0]
 
 
 def encode_gpu_release(device: int = 0) -> None:

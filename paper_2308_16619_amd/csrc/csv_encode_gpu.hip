@@ -24,13 +24,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
 #include <thread>
 #include <type_traits>
-#include <vector>
 
 #include "csv.h"
 #include "csv_format.hpp"
@@ -1008,6 +1008,14 @@ struct DevBuf {
     }
 };
 
+// A container of at least kPiecewise bytes leaves in kPieces copies, which
+// kCopyThreads threads move from the pinned buffer to the caller's memory as
+// they arrive: the copy ends 1/16 of the container after the transfer (14.7
+// MB: 0.4 ms after the kernels, against 1.1 ms with the whole transfer, a
+// copy to a buffer of the library and one from there in turn)
+constexpr unsigned kPieces = 16, kCopyThreads = 8;
+constexpr size_t kPiecewise = 8u << 20;
+
 // per device: the buffers of the last call, kept for the next one
 struct EncCache {
     std::mutex mu;
@@ -1015,6 +1023,7 @@ struct EncCache {
     EncCtl *h_ctl = nullptr;   // pinned
     uint8_t *h_pin = nullptr;  // pinned staging of the container on its way to host memory
     size_t h_pin_bytes = 0;
+    hipEvent_t arrived[kPieces] = {};  // the pieces of a large container
     void release() {
         scratch.release();
         wscratch.release();
@@ -1031,6 +1040,55 @@ struct EncCache {
         if (h_pin) (void)hipHostFree(h_pin);
         h_pin = nullptr;
         h_pin_bytes = 0;
+        for (auto &e : arrived) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
+        }
+    }
+    // bytes of device memory src through h_pin to dst, on stream s
+    int bring(uint8_t *dst, const uint8_t *src, size_t bytes, hipStream_t s) {
+        bool pieces = bytes >= kPiecewise;
+        for (unsigned k = 0; pieces && k < kPieces; k++)
+            if (!arrived[k] && hipEventCreateWithFlags(&arrived[k], hipEventDisableTiming) != hipSuccess) pieces = false;
+        if (!pieces) {
+            if (hipMemcpyAsync(h_pin, src, bytes, hipMemcpyDeviceToHost, s) != hipSuccess ||
+                hipStreamSynchronize(s) != hipSuccess)
+                return CSV_EHIP;
+            std::memcpy(dst, h_pin, bytes);
+            return CSV_OK;
+        }
+        const size_t piece = ((bytes + kPieces - 1) / kPieces + 4095) & ~(size_t)4095;
+        auto at = [=](unsigned k) { return std::min(bytes, k * piece); };
+        bool ok = true;
+        for (unsigned k = 0; ok && k < kPieces; k++) {
+            if (at(k + 1) > at(k))
+                ok = hipMemcpyAsync(h_pin + at(k), src + at(k), at(k + 1) - at(k), hipMemcpyDeviceToHost, s) == hipSuccess;
+            ok = ok && hipEventRecord(arrived[k], s) == hipSuccess;
+        }
+        if (!ok) {
+            (void)hipStreamSynchronize(s);
+            return CSV_EHIP;
+        }
+        std::atomic<unsigned> next{0};
+        std::atomic<bool> failed{false};
+        auto work = [&] {
+            for (unsigned k; (k = next.fetch_add(1)) < kPieces;) {
+                if (hipEventSynchronize(arrived[k]) != hipSuccess) failed = true;
+                else std::memcpy(dst + at(k), h_pin + at(k), at(k + 1) - at(k));
+            }
+        };
+        std::thread th[kCopyThreads - 1];
+        for (auto &x : th) {
+            try {
+                x = std::thread(work);
+            } catch (...) {  // fewer threads then
+                break;
+            }
+        }
+        work();
+        for (auto &x : th)
+            if (x.joinable()) x.join();
+        return failed ? CSV_EHIP : CSV_OK;
     }
 };
 constexpr int kMaxDevices = 64;
@@ -1057,10 +1115,10 @@ struct DeviceGuard {
 
 }  // namespace
 
-extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
-                                     const csv_encode_opts *opts, int device, void *stream, uint8_t **blob,
-                                     size_t *blob_bytes) {
-    if (!labels || !blob || !blob_bytes || !nx || !ny || !nz) return CSV_EINVAL;
+extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
+                                           const csv_encode_opts *opts, int device, void *stream,
+                                           void *(*alloc)(size_t bytes, void *ctx), void *ctx, size_t *blob_bytes) {
+    if (!labels || !alloc || !blob_bytes || !nx || !ny || !nz) return CSV_EINVAL;
     csv_encode_opts o;
     csv_encode_opts_default(&o);
     if (opts) o = *opts;
@@ -1171,21 +1229,12 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
             return CSV_ENOMEM;
         ec->h_pin_bytes = total;
     }
-    if (hipMemcpyAsync(ec->h_pin, dblob.p, total, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return CSV_EHIP;
-    uint8_t *out = static_cast<uint8_t *>(std::malloc(total));
-    if (!out) return CSV_ENOMEM;
-    // into fresh host pages: several threads share the page faults and the copy
-    const unsigned nt = total >= (8u << 20) ? 8u : 1u;
-    const size_t chunk = (total + nt - 1) / nt;
-    std::vector<std::thread> th;
-    for (unsigned k = 1; k < nt; k++) {
-        const size_t o = k * chunk, len = o < total ? std::min(chunk, total - o) : 0;
-        if (len) th.emplace_back([=] { std::memcpy(out + o, ec->h_pin + o, len); });
+    uint8_t *out = static_cast<uint8_t *>(alloc(total, ctx));
+    if (!out) {
+        (void)hipStreamSynchronize(s);
+        return CSV_ENOMEM;
     }
-    std::memcpy(out, ec->h_pin, std::min(chunk, total));
-    for (auto &x : th) x.join();
+    if (const int rc = ec->bring(out, dblob.as<uint8_t>(), total, s)) return rc;
     csv::VolumeHeader h;
     std::memset(&h, 0, sizeof(h));
     h.magic = csv::kMagic;
@@ -1207,9 +1256,22 @@ extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32
     std::memcpy(out, &h, sizeof(h));
     const uint64_t idx_end = csv::kHeaderBytes + 8ull * (B + 1);
     std::memset(out + idx_end, 0, rs - idx_end);  // padding before the record area
-    *blob = out;
     *blob_bytes = total;
     return CSV_OK;
+}
+
+extern "C" int csv_encode_volume_gpu(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
+                                     const csv_encode_opts *opts, int device, void *stream, uint8_t **blob,
+                                     size_t *blob_bytes) {
+    if (!blob) return CSV_EINVAL;
+    void *out = nullptr;
+    const int rc = csv_encode_volume_gpu_alloc(
+        labels, nx, ny, nz, opts, device, stream,
+        [](size_t bytes, void *ctx) -> void * { return *static_cast<void **>(ctx) = std::malloc(bytes); }, &out,
+        blob_bytes);
+    if (rc) std::free(out);
+    else *blob = static_cast<uint8_t *>(out);
+    return rc;
 }
 
 extern "C" int csv_encode_gpu_release(int device) {

@@ -61,3 +61,26 @@ def test_palette_window(csvlib, orc, labels):
     vol[32:] = np.repeat(np.repeat(np.repeat(vol[:16, :32, :32], 2, 0), 2, 1), 2, 2)
     check(csvlib, orc, vol, sample_stride=1)
     check(csvlib, orc, vol, tables=1)
+
+
+def test_container_memory(csvlib, orc):
+    # the library's own memory, the caller's, and a caller that has none;
+    # sizes on both sides of the piecewise copy
+    import ctypes
+    torch = torch_cuda()
+    L = csvlib.lib()
+    for n, labels in ((64, 50), (160, 1 << 20)):
+        vol = np.random.default_rng(n).integers(1, labels, (n, n, n)).astype(np.uint32)
+        want = csvlib.encode_volume(vol)
+        d = torch.from_numpy(vol.view(np.int32)).cuda()
+        o = csvlib.EncodeOpts(5, 10, 64, 64, 0, 0, 2, 0)
+        p, size = ctypes.c_void_p(), ctypes.c_size_t()
+        print("[gpu-test] container of %d bytes" % len(want), flush=True)
+        args = [ctypes.c_void_p(d.data_ptr()), n, n, n, ctypes.byref(o), 0, None]
+        assert L.csv_encode_volume_gpu(*args, ctypes.byref(p), ctypes.byref(size)) == 0
+        assert ctypes.string_at(p, size.value) == want
+        L.csv_free(p)
+        assert csvlib.encode_volume_gpu(d) == want
+        none = csvlib._ALLOC(lambda size, ctx: None)
+        assert L.csv_encode_volume_gpu_alloc(*args, none, None, ctypes.byref(size)) == csvlib.CSV_ENOMEM
+    assert (len(want) >= 8 << 20) and csvlib.encode_volume_gpu(d) == want
