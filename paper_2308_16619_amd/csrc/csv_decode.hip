@@ -582,6 +582,16 @@ __device__ __forceinline__ void store4(uint32_t *dst, const uint4 &o) {
     }
 }
 
+// 4 * byte b of q in one instruction (an SDWA source select)
+template <int B>
+__device__ __forceinline__ uint32_t byte_x4(uint32_t q) {
+    uint32_t r;
+    __asm__("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_%c2"
+            : "=v"(r)
+            : "v"(q), "n"(B));
+    return r;
+}
+
 // count labels of value v, by kThreads threads (tid: this thread's index)
 template <uint32_t kThreads>
 __device__ __forceinline__ void fill_labels(uint32_t *dst, uint32_t count, uint32_t v, uint32_t tid) {
@@ -738,7 +748,6 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
                 x = need ? ((x << 16) | wd) : x;
                 cursor += (uint32_t)__popcll(bal);
                 sb[64 * j + L] = (uint8_t)e;  // the symbol (bits 4..7 of an entry are zero)
-                if (cursor >= ring_lo + 512) refill();
             }
             wsync();
             const uint2 b = *reinterpret_cast<const uint2 *>(sb + 8 * L);
@@ -746,6 +755,9 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const uint32_t packed = ((lo | (lo >> 8)) & 0xFFFFu) | (((hi | (hi >> 8)) & 0xFFFFu) << 16);
             out[(s << 3) + L] = packed;
             if ((s << 3) + L < kWDeltaDw) lcopy[(s << 3) + L] = packed;
+            // 8 steps take at most 512 words, so a block that starts in the
+            // ring's first half stays inside it: one look per block
+            if (cursor >= ring_lo + 512) refill();
             wsync();
             s += 8;
             upper_done(s << 6);
@@ -782,7 +794,6 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
                 x = need ? ((x << 16) | wd) : x;
                 cursor += (uint32_t)__popcll(bal);
                 sb[((uint32_t)j << lw) + L] = (uint8_t)e;
-                if (cursor >= ring_lo + 512) refill();
             }
             wsync();
             const uint2 b = *reinterpret_cast<const uint2 *>(sb + 8 * L);
@@ -793,6 +804,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
                 out[at] = packed;
                 if (at < kWDeltaDw) lcopy[at] = packed;
             }
+            if (cursor >= ring_lo + 512) refill();
             wsync();
             s += 8;
             upper_done(s << lw);
@@ -1098,6 +1110,31 @@ __device__ __forceinline__ void upper_output(const IdxT *lv, uint32_t t, const u
         return;
     }
     const uint32_t lg = (uint32_t)(kLog2 - t);
+    if constexpr (sizeof(IdxT) == 1 && !kG) {
+        if (t == 1) {
+            // 16^3 labels, a plane per step: lane L holds voxels 4 (L & 3) ..
+            // + 3 of row L >> 2, whose Morton index apart from z does not
+            // change; bytes (x, x + 1) are neighbours in Morton order
+            const uint8_t *p = reinterpret_cast<const uint8_t *>(res) + (spread4(4 * (L & 3u)) | (spread4(L >> 2) << 1));
+            const uint8_t *pb = reinterpret_cast<const uint8_t *>(pal);
+            auto planes = [&](auto al16) {
+#pragma unroll 4
+                for (uint32_t z = 0; z < 16; z++) {
+                    const uint8_t *r = p + (spread4(z) << 2);
+                    const uint32_t a = *reinterpret_cast<const uint16_t *>(r), b = *reinterpret_cast<const uint16_t *>(r + 8);
+                    uint4 o;
+                    o.x = *reinterpret_cast<const uint32_t *>(pb + byte_x4<0>(a));
+                    o.y = *reinterpret_cast<const uint32_t *>(pb + byte_x4<1>(a));
+                    o.z = *reinterpret_cast<const uint32_t *>(pb + byte_x4<0>(b));
+                    o.w = *reinterpret_cast<const uint32_t *>(pb + byte_x4<1>(b));
+                    store4<decltype(al16)::value>(dst + 256 * z + 4 * L, o);
+                }
+            };
+            if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) planes(std::true_type{});
+            else planes(std::false_type{});
+            return;
+        }
+    }
     auto rows = [&](auto al16) {
         for (uint32_t e = 4 * L; e < G * G * G; e += 256) {
             const uint32_t x0 = e & (G - 1), yy = (e >> lg) & (G - 1), zz = e >> (2 * lg);
@@ -1426,16 +1463,6 @@ __device__ __forceinline__ uint32_t ref_children(uint32_t w, uint32_t lowok) {
     return (zero_nibbles(y ^ 0x11111111u) & ((lowok & 1u) ? 0x01010101u : 0u)) |
            (zero_nibbles(y ^ 0x22222222u) & ((lowok & 2u) ? 0x00110011u : 0u)) |
            (zero_nibbles(y ^ 0x33333333u) & ((lowok & 4u) ? 0x00001111u : 0u));
-}
-
-// 4 * byte b of q in one instruction (an SDWA source select)
-template <int B>
-__device__ __forceinline__ uint32_t byte_x4(uint32_t q) {
-    uint32_t r;
-    __asm__("v_lshlrev_b32_sdwa %0, 2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_%c2"
-            : "=v"(r)
-            : "v"(q), "n"(B));
-    return r;
 }
 
 // follow a chain of same-level references in the dense leaf level: value v
