@@ -882,6 +882,69 @@ __device__ __forceinline__ bool raw_nibbles(const Hdr &h, uint32_t *out, uint32_
     return (last >> (4 * (c & 3u))) == 0;
 }
 
+// Level 4 or 3 (8 or 64 nodes) of a u8 replay with a lane per child: up the
+// parent level (nullptr: the root), pb the expansion bits of its nodes.  The
+// palette positions come from ballots, the expansion bits are one, and every
+// nibble lies in the entropy decoder's copy.  (With a lane per parent, as for
+// the levels below, these two levels of at most 1 and 8 parents took as many
+// instructions as any chunk of 64: 16 % of a brick decoded to level 1.)
+// False on a malformed stream.
+template <int SH>
+__device__ __forceinline__ bool top_level(const Hdr &h, int m, const uint8_t *up, uint32_t pb, uint8_t *cur,
+                                          uint8_t *cbm, uint16_t *clist, const uint32_t *nib, uint32_t &ipl,
+                                          uint32_t &Ex) {
+    constexpr uint32_t kMark = 253u;
+    const uint32_t L = lane(), q = L >> 3, k = L & 7u, P = h.P;
+    const uint32_t E = (uint32_t)__builtin_popcount(pb);
+    const uint32_t seg = m == kLog2 - 1 ? 0u : h.c((uint32_t)m + 1), seg_end = h.c((uint32_t)m);
+    // (at most as many deltas as children; the last level's end is checked
+    // against the nibbles that the decoder's copy holds)
+    if (seg + 8 * E > seg_end || seg_end - seg > 16 * E || seg_end > 8 * (kWDeltaDw - 1)) return false;
+    const uint32_t D = seg_end - seg - 8 * E, ops0 = seg + D;  // deltas precede the operations
+    const bool act = ((pb >> q) & 1u) != 0;
+    const uint32_t nb = act ? nib1(nib, ops0 + 8 * (uint32_t)__builtin_popcount(pb & ((1u << q) - 1u)) + k) : 0u;
+    const uint32_t op = nb & 7u;
+    const uint64_t pam = __ballot(op == csv::kPa), pdm = __ballot(op == csv::kPd);
+    if ((uint32_t)__popcll(pdm) != D) return false;
+    const bool in = m == 3 || L < 8;
+    uint32_t v = up && in ? (uint32_t)up[q] : 0u;
+    bool bad = op == 7u || (SH > 0 && m == SH && nb >= 8u);
+    if (op >= csv::kP0) {
+        const uint32_t ip = ipl + mbcnt(pam);
+        uint32_t sub = 0;
+        if (op == csv::kPd) sub = nib1(nib, seg + mbcnt(pdm)) + 1u;
+        v = ip + (op == csv::kPa ? 1u : 0u) - sub;
+        bad |= v >= P;  // (also where the delta passes the first entry)
+    } else if (op) {
+        const uint32_t a = op - 1u;
+        const bool hi = (k >> a) & 1u, low = (q >> a) & 1u;
+        bad |= m == kLog2 - 1 || hi == low;
+        v = hi ? (m == 3 ? (uint32_t)up[q | (1u << a)] : 0u) : kMark + a;
+    }
+    if (__ballot(bad)) return false;
+    if (in) cur[L] = (uint8_t)v;
+    wsync();
+    // same-level references (level 3), followed to their values
+    if (v >= kMark && in) {
+        uint32_t j = L;
+        while (v >= kMark) {
+            j = morton_dec(j, 9u << (v - kMark));
+            v = cur[j];
+        }
+        cur[L] = (uint8_t)v;
+    }
+    const uint64_t ex = __ballot(act && nb < 8u);
+    if (L == 0) {
+        if (m == 3) *reinterpret_cast<uint64_t *>(cbm) = ex;
+        else cbm[0] = (uint8_t)ex;
+    }
+    if ((ex >> L) & 1u) clist[mbcnt(ex)] = (uint16_t)L;
+    ipl += (uint32_t)__popcll(pam);
+    Ex = (uint32_t)__popcll(ex);
+    wsync();
+    return true;
+}
+
 // Replay of levels 4 .. max(t, 1) by one wave (Alg. 1).  lv: the level
 // arrays (LDS, or the slot when kG); bm, lst: expansion bits and lists of
 // levels 2..4 in LDS; nib: the brick's nibbles (global).  On return E and
@@ -908,6 +971,15 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
         const bool want_list = m >= 2 && !(SH > 0 && m == SH);  // L_1's list is rebuilt from its bits by the leaf kernel
         uint16_t *clist = lst + kLstOff[m];
         const uint32_t list_cap = 1u << (3 * (kLog2 - m));
+        if constexpr (sizeof(IdxT) == 1 && !kG) {
+            if (m >= 3) {
+                uint32_t Ex = 0;
+                if (!top_level<SH>(h, m, up, pbm ? uniform((uint32_t)pbm[0]) : 1u, cur, cbm, clist, dstage, ipl, Ex))
+                    return false;
+                E = Ex;
+                continue;
+            }
+        }
         // children of parents that are not expanded inherit the parent's index
         if (sizeof(IdxT) == 1 && !kG && up) {
             // u8 levels in LDS: a lane takes 8 parents and writes the children
