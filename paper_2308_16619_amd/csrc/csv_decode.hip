@@ -446,6 +446,16 @@ __device__ __forceinline__ typename Vec8<IdxT>::T replay_children(uint32_t w, ui
     return out;
 }
 
+// children of one expanded node that the child replay leaves as same-level
+// references (bit 4k for child k): R_x at kx = 0, R_y at ky = 0, R_z at
+// kz = 0, each where the neighbour lies inside the brick (lowok)
+__device__ __forceinline__ uint32_t ref_children(uint32_t w, uint32_t lowok) {
+    const uint32_t y = w & 0x77777777u;
+    return (zero_nibbles(y ^ 0x11111111u) & ((lowok & 1u) ? 0x01010101u : 0u)) |
+           (zero_nibbles(y ^ 0x22222222u) & ((lowok & 2u) ? 0x00110011u : 0u)) |
+           (zero_nibbles(y ^ 0x33333333u) & ((lowok & 4u) ? 0x00001111u : 0u));
+}
+
 // nibbles 0..3 of x -> bytes 0..3
 __device__ __forceinline__ uint32_t nib_to_bytes(uint32_t x) {
     x &= 0xFFFFu;
@@ -1013,6 +1023,7 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
         // per level instead of one per 64 nodes), else global memory.  src
         // holds the nibbles from position off on.
         uint32_t bpa = 0, bpd = 0, bex = 0;
+        uint32_t open2 = 0, q2 = 0;  // level 2 (one chunk): this lane's parent and its children with references
         bool bad = false;
         auto run = [&](const uint32_t *src, uint32_t off) __attribute__((always_inline)) {
             for (uint32_t c = 0; c < (E + 63) / 64; c++) {
@@ -1030,9 +1041,9 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
 #pragma unroll
                     for (int a = 0; a < 3; a++) {
                         const uint32_t am = a == 0 ? pmask0 : (a == 1 ? pmask1 : pmask2);
-                        const bool hi = up && (q & am) != am;
-                        nb[a] = hi ? (uint32_t)up[morton_inc(q, am)] : 0u;
-                        nbok |= hi ? (1u << a) : 0u;
+                        // (on the high face: some node of the level, not used)
+                        nb[a] = up ? (uint32_t)up[morton_inc(q, am)] : 0u;
+                        nbok |= (up && (q & am) != am) ? (1u << a) : 0u;
                         lowok |= (q & am) ? (1u << a) : 0u;
                     }
                     const VT vals = replay8<IdxT>(wd, pv, nb, nbok, lowok, ipl + bpa + (exc & 1023u),
@@ -1040,6 +1051,10 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
                                                           seg - off + bpd + ((exc >> 10) & 1023u), P,
                                                           SH > 0 && m == SH, bad);
                     *reinterpret_cast<VT *>(cur + 8 * q) = vals;
+                    if (sizeof(IdxT) == 1 && !kG && m == 2) {
+                        open2 = ref_children(wd, lowok);
+                        q2 = q;
+                    }
                     uint32_t ex8 = compact_nibble_bits(exm);
                     cbm[q] = (uint8_t)ex8;
                     if (want_list) {
@@ -1083,6 +1098,22 @@ __device__ __forceinline__ bool upper_replay(const Hdr &h, const uint32_t *nib, 
         // is then followed by a lane of its own.
         bool listed = false;
         if constexpr (sizeof(IdxT) == 1 && !kG) {
+            if (m == 2) {
+                while (open2) {
+                    uint32_t qq = q2, kk = (uint32_t)__builtin_ctz(open2) >> 2;
+                    const uint32_t at = 8 * qq + kk;
+                    open2 &= open2 - 1u;
+                    uint32_t v = cur[at];
+                    while (v >= kMark) {
+                        const uint32_t a = v - kMark;
+                        qq = morton_dec(qq, pmask0 << a);
+                        kk |= 1u << a;
+                        v = cur[8 * qq + kk];
+                    }
+                    cur[at] = (IdxT)v;
+                }
+                listed = true;
+            }
             if (m == 1) {
                 uint16_t *refs = reinterpret_cast<uint16_t *>(dstage);
                 constexpr uint32_t kCap = 2 * kWDeltaDw;
@@ -1527,16 +1558,6 @@ __device__ __forceinline__ uint32_t morton_coord(uint32_t p) {
     return (p & 1u) | ((p >> 2) & 2u) | ((p >> 4) & 4u) | ((p >> 6) & 8u);
 }
 
-// children of one expanded node that the child replay leaves as same-level
-// references (bit 4k for child k): R_x at kx = 0, R_y at ky = 0, R_z at
-// kz = 0, each where the neighbour lies inside the brick (lowok)
-__device__ __forceinline__ uint32_t ref_children(uint32_t w, uint32_t lowok) {
-    const uint32_t y = w & 0x77777777u;
-    return (zero_nibbles(y ^ 0x11111111u) & ((lowok & 1u) ? 0x01010101u : 0u)) |
-           (zero_nibbles(y ^ 0x22222222u) & ((lowok & 2u) ? 0x00110011u : 0u)) |
-           (zero_nibbles(y ^ 0x33333333u) & ((lowok & 4u) ? 0x00001111u : 0u));
-}
-
 // follow a chain of same-level references in the dense leaf level: value v
 // at voxel i, a reference to the voxel at -1 along axis v - kMark
 template <class IdxT>
@@ -1718,8 +1739,8 @@ __device__ __forceinline__ bool leaf_replay(const Hdr &h, uint32_t E1, uint32_t 
         if (act) {
             const uint32_t i = X + 16 * Y + 256 * Z;
             const uint32_t pv = l1[i];
-            const uint32_t nbv[3] = {X < 15 ? (uint32_t)l1[i + 1] : 0u, Y < 15 ? (uint32_t)l1[i + 16] : 0u,
-                                     Z < 15 ? (uint32_t)l1[i + 256] : 0u};
+            // (on a high face: what lies behind, not used; the arena goes on)
+            const uint32_t nbv[3] = {(uint32_t)l1[i + 1], (uint32_t)l1[i + 16], (uint32_t)l1[i + 256]};
             const uint32_t nbok = (X < 15 ? 1u : 0u) | (Y < 15 ? 2u : 0u) | (Z < 15 ? 4u : 0u);
             const VT vals = replay8<IdxT>(wd, pv, nbv, nbok, lowok, ipl + bpa + (exc & 1023u),
                                           compact_nibble_bits(pam), compact_nibble_bits(pdm), nib,
