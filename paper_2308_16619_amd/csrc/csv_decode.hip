@@ -1329,6 +1329,17 @@ __device__ __forceinline__ bool front_replay(const Hdr &h, const LaunchA &l, con
     return true;
 }
 
+// The kernel's arguments, read anew from the kernel-argument segment (the
+// scalar cache) wherever they are used in this brick: held in registers
+// across bricks they and what the compiler derives from them fill the scalar
+// registers, and 140 of them moved to vector lanes and back.
+template <class T>
+__device__ __forceinline__ const T &brick_args(uint32_t offset) {
+    auto p = (const __attribute__((address_space(4))) uint8_t *)__builtin_amdgcn_kernarg_segment_ptr() + offset;
+    __asm__ volatile("" : "+s"(p));
+    return *(const T *)(const __attribute__((address_space(4))) T *)p;
+}
+
 // kLutLds: the decode tables of every volume are copied to LDS (else read
 // from global memory)
 // SH, kGen: bricks of edge 32 >> SH, rANS or raw nibbles.  SH > 0 decodes a
@@ -1342,16 +1353,16 @@ __device__ __forceinline__ bool front_replay(const Hdr &h, const LaunchA &l, con
 // workgroup per brick with its levels in global scratch took 2.59 ms.
 template <int WPG, bool kLutLds, int SH = 0, bool kGen = false>
 // 16 waves per CU at most (LDS); registers for 4 per SIMD
-__global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) void front_kernel(DecodeArgs a, LaunchA l) {
+__global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) void front_kernel(DecodeArgs a0, LaunchA l0) {
     extern __shared__ __align__(16) uint8_t smem[];
     uint32_t *slut = reinterpret_cast<uint32_t *>(smem);
     if (kLutLds)
-        for (uint32_t e = threadIdx.x; e < l.lut_lds_words; e += blockDim.x) slut[e] = a.luts[e];
+        for (uint32_t e = threadIdx.x; e < l0.lut_lds_words; e += blockDim.x) slut[e] = a0.luts[e];
     __syncthreads();
     const uint32_t L = lane(), wave = uniform(threadIdx.x >> 6);
-    uint8_t *wl = smem + align16(4 * l.lut_lds_words) + wave * kWaveLds;
+    uint8_t *wl = smem + align16(4 * l0.lut_lds_words) + wave * kWaveLds;
     const uint32_t wid = blockIdx.x * WPG + wave;
-    const uint32_t n_req = a.n_dev ? min(a.n, ld_s(a.n_dev)) : a.n;
+    const uint32_t n_req = a0.n_dev ? min(a0.n, ld_s(a0.n_dev)) : a0.n;
     // With a work counter, each request is taken one brick ahead (lane 0)
     // and its value read at the end of the brick before: a read at the top
     // of a brick would wait behind the previous brick's stores (on gfx9 one
@@ -1359,12 +1370,14 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
     // brick's own loads would wait again.  An increment, not an add: the
     // compiler rewrites a uniform-address add to read its result at once.
     uint32_t taken = 0, cur = 0;
-    if (l.queue) {
-        if (L == 0) taken = atomicInc(l.queue, 0xFFFFFFFFu);
+    if (l0.queue) {
+        if (L == 0) taken = atomicInc(l0.queue, 0xFFFFFFFFu);
         cur = uniform(taken);
-        if (L == 0) taken = atomicInc(l.queue, 0xFFFFFFFFu);
+        if (L == 0) taken = atomicInc(l0.queue, 0xFFFFFFFFu);
     }
     for (uint32_t k = 0;; k++) {
+        const DecodeArgs &a = brick_args<DecodeArgs>(0);
+        const LaunchA &l = brick_args<LaunchA>(sizeof(DecodeArgs));
         if (k > 0 && l.queue) {
             cur = uniform(taken);
             if (L == 0) taken = atomicInc(l.queue, 0xFFFFFFFFu);
@@ -1449,19 +1462,21 @@ constexpr uint32_t kPairDecLds = align16(kPairOk + 8);
 // decode and the replay.  Both waves take every brick of the workgroup
 // (static round robin) and pass the same barriers on every path.
 template <bool kLutLds>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) void front_pair_kernel(DecodeArgs a,
-                                                                                                LaunchA l) {
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) void front_pair_kernel(DecodeArgs a0,
+                                                                                                LaunchA l0) {
     extern __shared__ __align__(16) uint8_t smem[];
     uint32_t *slut = reinterpret_cast<uint32_t *>(smem);
     if (kLutLds)
-        for (uint32_t e = threadIdx.x; e < l.lut_lds_words; e += blockDim.x) slut[e] = a.luts[e];
+        for (uint32_t e = threadIdx.x; e < l0.lut_lds_words; e += blockDim.x) slut[e] = a0.luts[e];
     __syncthreads();
     const uint32_t L = lane(), wave = uniform(threadIdx.x >> 6);
-    uint8_t *wl0 = smem + align16(4 * l.lut_lds_words);  // wave 0: the word ring
+    uint8_t *wl0 = smem + align16(4 * l0.lut_lds_words);  // wave 0: the word ring
     uint8_t *wl1 = wl0 + kPairDecLds;                      // wave 1: the levels (first nibbles at kWPal)
     uint32_t *ok_word = reinterpret_cast<uint32_t *>(wl0 + kPairOk);  // wave 0's verdict, by brick parity
-    const uint32_t n_req = a.n_dev ? min(a.n, ld_s(a.n_dev)) : a.n;
+    const uint32_t n_req = a0.n_dev ? min(a0.n, ld_s(a0.n_dev)) : a0.n;
     for (uint32_t k = 0;; k++) {
+        const DecodeArgs &a = brick_args<DecodeArgs>(0);
+        const LaunchA &l = brick_args<LaunchA>(sizeof(DecodeArgs));
         const uint32_t req = l.base + blockIdx.x + k * gridDim.x;
         if (req >= n_req) break;
         const uint32_t rq = l.order ? ld_s(l.order + req) : req;
