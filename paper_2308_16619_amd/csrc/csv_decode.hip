@@ -2970,6 +2970,9 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const uint32_t grid_a = std::max(1u, std::min(cu * fit_a, (n + per_wg - 1) / per_wg));
     const uint32_t bricks_a = grid_a * per_wg;
     const uint32_t grid_b = std::min(cu * groups_b, n);
+    // no request of one coarser level of detail reaches the leaf kernels; with
+    // a work counter they still run, to clear it
+    const bool leaves = lods || lod_scalar == 0 || queue;
     auto go_a = [&](const DecodeArgs &aa, const LaunchA &L, uint32_t grid) {
         if (gen) {
             launch_gen<0>(aa, L, grid, lds_a, s);
@@ -2989,6 +2992,7 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
             la.base = i;
             b.n = i + 1;
             go_a(b, la, 1);
+            if (!leaves) continue;
             hipLaunchKernelGGL((leaf_kernel<kWavesLeaf, false>), dim3(1), dim3(64 * kWavesLeaf), lds_b, s, b, lb);
             if (slow) hipLaunchKernelGGL((leaf_kernel<kWavesLeafG, true>), dim3(1), dim3(64 * kWavesLeafG), lds_g, s, b, lb);
         }
@@ -3002,8 +3006,9 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
             la.order = B->order;
         }
         go_a(a, la, grid_a);
-        hipLaunchKernelGGL((leaf_kernel<kWavesLeaf, false>), dim3(grid_b), dim3(64 * kWavesLeaf), lds_b, s, a, lb);
-        if (slow) {
+        if (leaves)
+            hipLaunchKernelGGL((leaf_kernel<kWavesLeaf, false>), dim3(grid_b), dim3(64 * kWavesLeaf), lds_b, s, a, lb);
+        if (leaves && slow) {
             hipLaunchKernelGGL((leaf_kernel<kWavesLeafG, true>), dim3(grid_g), dim3(64 * kWavesLeafG), lds_g, s, a, lb);
         }
     }
