@@ -2959,8 +2959,10 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const size_t lds_b = kSmallB + (size_t)lb.arena_bytes;
     const size_t lds_g = kSmallB;
     lb.slow_list = slow ? B->slow_list : nullptr;
-    // a small batch takes smaller front workgroups, so that its bricks spread over the CUs
-    while (waves_a > 4 && (n + (uint32_t)waves_a - 1) / (uint32_t)waves_a < cu) waves_a /= 2;
+    // a small batch takes smaller front workgroups, so that its bricks spread
+    // over the CUs, and so does one whose count is on the device: it may be far
+    // below the bound n
+    while (waves_a > 4 && (n_dev || (n + (uint32_t)waves_a - 1) / (uint32_t)waves_a < cu)) waves_a /= 2;
     // front kernel: as many workgroups as a CU's LDS and 32 wave slots allow;
     // bricks_a of them in flight at once (one per wave, or one per paired workgroup)
     const uint32_t per_wg = waves_a == 2 ? 1u : (uint32_t)waves_a;
