@@ -3732,7 +3732,10 @@ int csv_autotune(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
     };
     // one coordinate at a time: the two kernels' shapes with the requests
     // split in up to four chunks, then the chunk count, then the work
-    // counters and the longest-first order
+    // counters and the longest-first order; then the leaf groups once more,
+    // as the number that fits best falls with the chunk count and the order
+    // (16,384 mixed requests, two ordered chunks: 291 us with two groups, 310
+    // with three; in four chunks without order three were the best)
     const uint32_t c0 = std::max(1u, std::min(4u, n / kMinChunk));
     const int waves[3] = {2, 8, 16};
     const uint32_t groups[3] = {2, 3, 4};
@@ -3754,6 +3757,13 @@ int csv_autotune(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
                 sh.lpt_order = o;
                 consider(sh);
             }
+    const csv_shape base3 = win;
+    for (uint32_t gb : groups)
+        if (gb != base3.groups_per_cu) {
+            csv_shape sh = base3;
+            sh.groups_per_cu = gb;
+            consider(sh);
+        }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
