@@ -84,3 +84,13 @@ def test_container_memory(csvlib, orc):
         none = csvlib._ALLOC(lambda size, ctx: None)
         assert L.csv_encode_volume_gpu_alloc(*args, none, None, ctypes.byref(size)) == csvlib.CSV_ENOMEM
     assert (len(want) >= 8 << 20) and csvlib.encode_volume_gpu(d) == want
+
+
+@pytest.mark.parametrize("shape", [(5, 17, 33), (64, 64, 64), (64, 70, 96), (96, 128, 130), (128, 160, 161)])
+def test_container_exits(csvlib, orc, shape):
+    # containers of some KB to some 10 MB: with the state, in one copy when
+    # the pinned buffer grows, in pieces; the second call finds it grown
+    vol = np.random.default_rng(shape[2]).integers(1, 1 << 20, shape).astype(np.uint32)
+    for _ in range(2):
+        check(csvlib, orc, vol)
+    check(csvlib, orc, vol[:3])
