@@ -175,8 +175,8 @@ void csv_pool_destroy(csv_pool *pool);
  * brick_log2 1..6; another size is CSV_EINVAL).  Pools of 32^3 rANS bricks
  * decode with the tuned kernels; a volume of another brick size or with raw
  * nibbles (csv_encode_opts.coding 1) makes every decode of the pool take the
- * generic decoder (one workgroup per brick, levels in global memory; Table
- * 1's variants), which has no launch shape, no graphs, no
+ * kernels for its edge (Table 1's variants), which have no launch shape, no
+ * graphs, no
  * csv_decode_bricks_noalloc, no detail separation, no serving loop and no
  * frame cache (those return CSV_EINVAL).  Every record is checked
  * first (csv_blob_check).  Synchronous, with no stream argument: the pool's

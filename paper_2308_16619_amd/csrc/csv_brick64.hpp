@@ -11,14 +11,16 @@
 //                     and P_delta operations before it go to the slot, and
 //                     everything that could be malformed in level 0 is
 //                     checked here;
-//   leaf64_kernel     one wave per block of 32 x 16 x 8 voxels: its expanded
+//   leaf64_kernel     one wave per block of 32 x 8 x 8 voxels: its expanded
 //                     parents 64 at a time, in no order that matters (each
 //                     has its own counts), the block in LDS, the output in
 //                     rows of 128 bytes.  References out of the block are
 //                     evaluated on the other block's operations.
 // The finest level of a 64^3 brick (512 KB of u16) does not fit LDS; blocks
 // that need nothing of each other's results keep it out of global memory
-// and give 64 waves of work per brick.
+// and give 128 waves of work per brick.  512 raw bricks of the 512^3 cells
+// volume, full LOD: 267 us for the call (2.01 TB/s of labels); with a
+// workgroup per brick and its levels in global scratch 2.73 ms.
 
 constexpr uint32_t k64PalMax = 1u << 14;  // P_a counts of a slot have 14 bits
 constexpr int k64Threads = 512;           // of an upper workgroup

@@ -646,7 +646,7 @@ __device__ __forceinline__ void wave_sync() {
 // levels above L_0) are written, else at the end
 // kNarrow: blocks of 8 steps also for bricks of 8, 16 or 32 states, the rule
 // for bricks of a smaller edge (16^3 bricks have 16 or 32 states; decoding
-// 32,768 of them takes 0.39 ms).  The kernels for 32^3 rANS pools leave it
+// 32,768 of them takes 0.32 ms).  The kernels for 32^3 rANS pools leave it
 // out: their bricks mostly have 64 states, and the added code made the front
 // kernel 1 % slower (32,768 and 4,096 bricks at full LOD).
 template <bool kLutLds, int SH = 0, bool kNarrow = false, class Hook = NoHook>
@@ -1349,8 +1349,15 @@ __device__ __forceinline__ const T &brick_args(uint32_t offset) {
 // Bricks of edge 16 are bound as the 32^3 front kernel is (a serial chain
 // per brick at 16 waves per CU, set by 8 KB of LDS each); a wave per brick
 // keeps the levels in LDS and needs no barrier: all 32,768 bricks of a 512^3
-// cells volume, full LOD, 0.391 ms (1.41 TB/s of labels and records); a
+// cells volume, full LOD, 0.322 ms (1.72 TB/s of labels and records); a
 // workgroup per brick with its levels in global scratch took 2.59 ms.
+// The 32^3 kernel is bound by vector issue (70 to 80 % of its time at 16
+// waves per CU), the rest being each brick's serial chain.  Its share of the
+// work is what a decode to level 1 does: 32,768 bricks of the 1024^3 neurite
+// volume in 0.40 ms, against 0.475 ms with one look at the word ring per
+// step, a lane per parent on levels 4 and 3, branches around each neighbour
+// read and the arguments held in scalar registers; the same bricks at full
+// LOD, both kernels: 1.45 ms against 1.51.
 template <int WPG, bool kLutLds, int SH = 0, bool kGen = false>
 // 16 waves per CU at most (LDS); registers for 4 per SIMD
 __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) void front_kernel(DecodeArgs a0, LaunchA l0) {
@@ -2088,6 +2095,11 @@ __device__ __forceinline__ void leaf_fast_bricks(const DecodeArgs &a, const Laun
 
 // kSlow false: bricks whose arrays fit the LDS arena, the others deferred
 // to the slow list; kSlow true: the slow list, on an arena in global memory
+// Bound by its output writes: 4,096 bricks of the 512^3 cells volume (537 MB)
+// take 113 to 118 us, and the same stores with nothing before them 92 to 99
+// (5.4 to 5.8 TB/s; a plain fill reaches 6.9).  Leaving pass 2 out altogether
+// saves 5 us, leaving the stores out 20; two workgroups per CU are as fast as
+// three, and plain stores slower than non-temporal ones.
 template <int NW, bool kSlow>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kSlow ? 4 : 6))) void leaf_kernel(DecodeArgs a,
                                                                                                       LaunchB l) {

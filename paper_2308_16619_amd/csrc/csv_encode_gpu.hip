@@ -1,7 +1,7 @@
 // GPU compressor for 32^3 bricks: the container of csv_encode_volume, byte
 // for byte, built on the device from a label volume resident in HBM.
 //
-//   reuse kernel (a 256-thread workgroup per brick, persistent grid):
+//   reuse kernel (a 1024-thread workgroup per brick, one per CU, persistent):
 //     resolution pyramid (Sec. 3.1)    level 1 from the volume, levels 2..5
 //                                      in LDS
 //     reuse operations (Sec. 3.2,      a lane per expanded parent: its eight
@@ -16,11 +16,13 @@
 //   rANS kernel (a wavefront per brick): the frequency tables (Sec. 3.3/3.4)
 //     from the histograms, interleaved rANS, one state per lane, symbols
 //     from last to first; the record into an arena
-//   packing: a device scan of record sizes, one copy kernel
+//   packing: a device scan of record sizes, a kernel that gathers the
+//     records, and one that takes the state and the container to the host
 //
 // The kernels pass their results through arenas in global memory; a brick
-// takes its part by an atomic add, and a part that does not fit makes the
-// host repeat the launches with the sizes they report.
+// takes its part of arena 1 by an atomic add (its part of arena 2 follows
+// from it), and a part that does not fit makes the host repeat the launches
+// with the sizes they report.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

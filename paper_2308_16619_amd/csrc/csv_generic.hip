@@ -1,8 +1,10 @@
 // Decoder for bricks of edge 2^N with interleaved rANS or raw nibbles
 // (Sec. 3.3, Sec. 3.4, Alg. 1; Table 1's brick sizes and its variant
-// without rANS), built for N = 6: the smaller edges decode with the front
-// kernel of csv_decode.hip (one wavefront per brick, levels in LDS), which
-// took 32,768 bricks of edge 16 from 2.59 ms here to 0.39 ms.
+// without rANS), built for N = 6 and used for pools that hold a brick with
+// more palette entries than the kernels of csv_brick64.hpp take (16,384; 512
+// bricks: 2.73 ms here, 0.27 ms there).  The smaller edges decode with the
+// front kernel of csv_decode.hip (one wavefront per brick, levels in LDS:
+// 32,768 bricks of edge 16 in 0.32 ms, 2.59 ms here).
 //
 // One 256-thread workgroup per request, persistent over the requests:
 //   1. the record header is read and checked (as the pool's loader does);

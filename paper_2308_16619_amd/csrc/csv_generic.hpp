@@ -1,7 +1,7 @@
-// The decoder for bricks of edge 64 with both codings (rANS and raw
-// nibbles): one workgroup per brick, levels replayed one after another in a
-// global-memory scratch area of the workgroup.  Smaller edges decode with
-// the kernels of csv_decode.hip.
+// The decoder for bricks of edge 64 with palettes of any size, both codings
+// (rANS and raw nibbles): one workgroup per brick, levels replayed one after another in a
+// global-memory scratch area of the workgroup.  Smaller edges
+// and palettes decode with the kernels of csv_decode.hip and csv_brick64.hpp.
 #pragma once
 #include <hip/hip_runtime.h>
 

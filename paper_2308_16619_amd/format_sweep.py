@@ -5,9 +5,8 @@ seeded synthetic volume):
 * brick edge 2^brick_log2 in {16, 32, 64}, each with Table 1's three
   entropy-coding variants: no rANS (the symbol stream stored as raw
   nibbles, csv_encode_opts.coding 1), rANS with one frequency table for all
-  symbols, rANS with two (levels >= 1 and L_0: the default).  32^3 rANS
-  bricks decode with the tuned kernels, the others with the generic
-  decoder;
+  symbols, rANS with two (levels >= 1 and L_0: the default).  Only
+  32^3 rANS bricks have tuned launch shapes;
 * interleaved rANS states per brick W (lane_max) in {1, 4, 16, 64} (W = 1 is
   the paper's single stream per brick);
 * table precision scale_bits in {8, 9, 10, 11}.
@@ -108,7 +107,7 @@ def main():
                     rec["gpu_encode_ms"] = round(gpu_encode_ms(csv, torch, vol, blob, tables=tables), 3)
                 gbs, ms, shape = decode_rate(csv, torch, vol, blob, args.reps, log2)
                 rec.update({"decode_gbs": round(gbs, 2), "ms_per_call": round(ms, 4),
-                            "decoder": "tuned 32^3 kernels" if shape else "generic", "shape": shape})
+                            "decoder": "tuned launch shape" if shape else "fixed launch shape", "shape": shape})
             print(json.dumps(rec), flush=True)
     # interleaving width and table precision (32^3 bricks, two tables)
     for sbits, lanes in [(10, w) for w in (1, 4, 16)] + [(s, 64) for s in (8, 9, 11)]:
