@@ -741,51 +741,56 @@ __global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
 // Division by a frequency is a multiply by its 32-bit reciprocal with one
 // correction.  The chain of a step is a dozen operations (the symbols and
 // table entries of 16 steps are fetched ahead, the words gathered in LDS);
-// bound by vector issue: 82 us for the 4,096 bricks (122 us with a store per
-// word, tables unpacked in every step and a double reciprocal).
+// bound by vector issue: 71 us for the 4,096 bricks (122 us with a store per
+// word, tables unpacked in every step and a double reciprocal; 81 us with a
+// look at the kept words after every step and the tables normalised by one
+// thread each).  The few bricks of a small volume are bound by the chain: 36
+// us for 140, 46 us before the latter two.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void rans_kernel(EncArgs a) {
     // per table and symbol: the reciprocal m, f | s << 24, 2^bits - f and the
     // start c of its slots; with 2^s < f <= 2^(s + 1), v / f is
     // (v m >> 32 >> s) or one more
     __shared__ uint4 tab[32];
-    __shared__ uint32_t freq[32];
     // per wave: the packed symbols of a block of 16 steps, the last 1024 words
     __shared__ uint32_t sym_l[kWaves][128];
     __shared__ __align__(16) uint16_t word_l[kWaves][1024];
     const uint32_t t = threadIdx.x, L = lane(), w = uniform(t >> 6), bits = a.bits, M = 1u << bits;
-    if (t < 32) {  // the host compressor's normalisation of the counts
-        const uint32_t k = t >> 4, q = t & 15u;
-        const unsigned long long *h0 = glob(a.ctl)->hist[0], *h1 = glob(a.ctl)->hist[1];
-        uint64_t tot = 0;
-        for (uint32_t s = 0; s < 16; s++) tot += (a.one_table ? h0[s] + h1[s] : (k ? h1[s] : h0[s])) + 1;
-        const uint64_t c = (a.one_table ? h0[q] + h1[q] : (k ? h1[q] : h0[q])) + 1, v = c * M / tot;
-        freq[t] = v ? (uint32_t)v : 1u;
-    }
-    __syncthreads();
-    if (t < 2) {
-        uint32_t *f = freq + 16 * t, sum = 0, best = 0;
-        for (uint32_t s = 0; s < 16; s++) sum += f[s];
-        if (sum < M) {
-            for (uint32_t s = 1; s < 16; s++)
-                if (f[s] > f[best]) best = s;
-            f[best] += M - sum;
+    if (w == 0) {  // the host compressor's normalisation of the counts, 16 lanes per table
+        const uint32_t k = (L >> 4) & 1u, q = L & 15u;
+        const unsigned long long h0 = glob(a.ctl)->hist[0][q], h1 = glob(a.ctl)->hist[1][q];
+        const uint64_t c = (a.one_table ? h0 + h1 : (k ? h1 : h0)) + 1;
+        uint64_t tot = c;
+        for (int d = 1; d < 16; d *= 2) tot += __shfl_xor((unsigned long long)tot, d);
+        const uint64_t v = c * M / tot;
+        uint32_t f = v ? (uint32_t)v : 1u, sum = f;
+        for (int d = 1; d < 16; d *= 2) sum += __shfl_xor(sum, d);
+        // the first of the largest frequencies (of those above 1) takes what
+        // is missing, or gives back what is too much one by one
+        auto is_best = [&](bool on) {
+            const uint32_t key = on ? f << 4 | (15u - q) : 0u;
+            uint32_t top = key;
+            for (int d = 1; d < 16; d *= 2) top = max(top, (uint32_t)__shfl_xor(top, d));
+            return on && key == top;
+        };
+        if (is_best(true) && sum < M) f += M - sum;
+        while (__any(sum > M)) {
+            const bool best = is_best(f > 1);
+            if (sum > M) {
+                f -= best ? 1u : 0u;
+                sum--;
+            }
         }
-        for (; sum > M; sum--) {
-            best = 16;
-            for (uint32_t s = 0; s < 16; s++)
-                if (f[s] > 1 && (best == 16 || f[s] > f[best])) best = s;
-            f[best]--;
+        uint32_t c0 = f;
+        for (int d = 1; d < 16; d *= 2) {
+            const uint32_t lower = __shfl_up(c0, d, 16);
+            c0 += q >= (uint32_t)d ? lower : 0u;
         }
-    }
-    __syncthreads();
-    if (t < 32) {
-        const uint32_t f = freq[t];
-        uint32_t c = 0, s = 0;
-        for (uint32_t k = t & 16u; k < t; k++) c += freq[k];
-        while ((2u << s) < f) s++;
-        const uint64_t m = ((uint64_t)1 << (32 + s)) / f;
-        tab[t] = make_uint4(m >> 32 ? 0xFFFFFFFFu : (uint32_t)m, f | (s << 24), M - f, c);
-        if (blockIdx.x == 0) glob(a.ctl)->freq[t >> 4][t & 15] = (uint16_t)f;
+        const uint32_t sh = f > 2 ? 31u - (uint32_t)__builtin_clz(f - 1) : 0u;
+        const uint64_t m = ((uint64_t)1 << (32 + sh)) / f;
+        if (L < 32) {
+            tab[L] = make_uint4(m >> 32 ? 0xFFFFFFFFu : (uint32_t)m, f | (sh << 24), M - f, c0 - f);
+            if (blockIdx.x == 0) glob(a.ctl)->freq[k][q] = (uint16_t)f;
+        }
     }
     __syncthreads();
     // word i of a brick goes to LDS place 1023 - (i mod 1024), and each 512 of
@@ -853,7 +858,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
                     q += v - __umul24(q, e.y) >= (e.y & 0xFFFFFFu) ? 1u : 0u;
                     const uint32_t y = __umul24(q, e.z) + v + e.w;
                     x = act ? y : x;
-                    if (pushed - kept >= 512) flush();
+                    // (8 steps emit up to 512 words, behind up to 511 kept)
+                    if (k % 8 == 7 && pushed - kept >= 512) flush();
                 }
             };
             if (n % (kBlk * W)) {
