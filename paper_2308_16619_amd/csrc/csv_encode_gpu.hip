@@ -560,7 +560,7 @@ __global__ __launch_bounds__(kReuseThreads) __attribute__((amdgpu_waves_per_eu(4
 // memory, 113 us with a counter for places in arena 2).
 constexpr uint32_t kOutcomes = 2048;  // left-over children whose outcome fits LDS
 __global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
-    __shared__ __align__(8) uint8_t cop_l[kWaves][kOutcomes];
+    __shared__ __align__(8) uint8_t cop_l[kWaves][kOutcomes + 16];
     __shared__ __align__(8) uint8_t del_l[kWaves][kOutcomes + 8 * kN + 8];
     const uint32_t L = lane(), w = uniform(threadIdx.x >> 6);
     for (uint32_t id = blockIdx.x * kWaves + w; id < a.n_items; id += gridDim.x * kWaves) {
@@ -677,11 +677,17 @@ __global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
                     // the placeholders, in the order of their children
                     uint32_t left = zero_nibbles((x & 0x77777777u) ^ 0x66666666u);
                     const uint32_t c = (uint32_t)__builtin_popcount(left), inc = wave_incl_scan(c);
-                    uint32_t at = rk + inc - c;
+                    const uint32_t at = rk + inc - c;
+                    // (at most 8, read at once: the bytes behind them are not used)
+                    const auto *cw4 = reinterpret_cast<const uint32_t *>(cop + (at & ~3u));
+                    const uint32_t w0 = cw4[0], w1 = cw4[1], w2 = cw4[2];
+                    uint64_t got = (uint64_t)__builtin_amdgcn_alignbyte(w2, w1, at & 3u) << 32 |
+                                   __builtin_amdgcn_alignbyte(w1, w0, at & 3u);
                     while (left) {
                         const uint32_t b = (uint32_t)__builtin_ctz(left);
                         left &= left - 1u;
-                        x ^= (uint32_t)cop[at++] << b;
+                        x ^= ((uint32_t)got & 0xFFu) << b;
+                        got >>= 8;
                     }
                     rk += readlane(inc, 63);
                     append(x, k);
