@@ -94,3 +94,14 @@ def test_container_exits(csvlib, orc, shape):
     for _ in range(2):
         check(csvlib, orc, vol)
     check(csvlib, orc, vol[:3])
+
+
+@pytest.mark.parametrize("by,bx", [(1, 1023), (32, 32), (25, 41), (41, 100)])
+def test_sizes_scanned_per_workgroup_or_once(csvlib, orc, by, bx):
+    # one brick short of, at, one past and well past the last count of bricks
+    # whose sizes every workgroup scans itself
+    vol = np.zeros((1, 32 * by, 32 * bx), np.uint32)
+    rng = np.random.default_rng(bx)
+    for y, x in zip(rng.integers(0, 32 * by, 4000), rng.integers(0, 32 * bx, 4000)):
+        vol[0, y:y + 9, x:x + 5] = y + x
+    check(csvlib, orc, vol)
