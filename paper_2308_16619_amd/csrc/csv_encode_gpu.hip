@@ -1174,7 +1174,8 @@ struct EncCache {
         const dim3 grid(kCopyGroups), threads(256);
         if (!pieces) {
             hipLaunchKernelGGL(piece_kernel, grid, threads, 0, s, src, h_pin, (uint64_t)bytes);
-            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
+            const bool launched = hipGetLastError() == hipSuccess;
+            if (hipStreamSynchronize(s) != hipSuccess || !launched) return CSV_EHIP;
             std::memcpy(dst, h_pin, bytes);
             return CSV_OK;
         }
@@ -1333,7 +1334,9 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
             hipLaunchKernelGGL(leave_kernel, dim3(kCopyGroups), dim3(256), 0, s, a, ec->h_ctl,
                                (const uint8_t *)ec->dblob.as<uint8_t>(), rs, ec->h_pin, room);
         }
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
+        // (waits in any case: the kernels write this cache's pinned memory)
+        const bool launched = hipGetLastError() == hipSuccess;
+        if (hipStreamSynchronize(s) != hipSuccess || !launched) return CSV_EHIP;
         const EncCtl &c = *ec->h_ctl;
         if (c.top1 <= a.cap1 && c.top3 <= a.cap3) {
             there = rs + c.total < room;
