@@ -656,10 +656,14 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
     constexpr bool kHook = !std::is_same<Hook, NoHook>::value;
     const uint32_t upper = (h.c1 + 7u) & ~7u;  // whole nibble dwords
     bool fired = false;
+    // dwords that also go to lcopy: none once the hook has run, as the other
+    // wave lists references there from then on (and reads no later symbols)
+    uint32_t copied = kWDeltaDw;
     auto upper_done = [&](uint32_t decoded) {
         if constexpr (kHook) {
             if (!fired && decoded >= upper) {
                 fired = true;
+                copied = 0;
                 at_upper();
             }
         }
@@ -734,7 +738,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const uint32_t g = row_or<3>(sym << (4 * (L & 7u)));
             if ((L & 7u) == 7u) {
                 out[(i - 7) >> 3] = g;
-                if (((i - 7) >> 3) < kWDeltaDw) lcopy[(i - 7) >> 3] = g;
+                if (((i - 7) >> 3) < copied) lcopy[(i - 7) >> 3] = g;
             }
             if (cursor >= ring_lo + 512) refill();
         };
@@ -764,7 +768,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const uint32_t lo = (b.x | (b.x >> 4)) & 0x00FF00FFu, hi = (b.y | (b.y >> 4)) & 0x00FF00FFu;
             const uint32_t packed = ((lo | (lo >> 8)) & 0xFFFFu) | (((hi | (hi >> 8)) & 0xFFFFu) << 16);
             out[(s << 3) + L] = packed;
-            if ((s << 3) + L < kWDeltaDw) lcopy[(s << 3) + L] = packed;
+            if ((s << 3) + L < copied) lcopy[(s << 3) + L] = packed;
             // 8 steps take at most 512 words, so a block that starts in the
             // ring's first half stays inside it: one look per block
             if (cursor >= ring_lo + 512) refill();
@@ -812,7 +816,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const uint32_t at = ((s << lw) >> 3) + L;
             if (L < W) {
                 out[at] = packed;
-                if (at < kWDeltaDw) lcopy[at] = packed;
+                if (at < copied) lcopy[at] = packed;
             }
             if (cursor >= ring_lo + 512) refill();
             wsync();
@@ -850,7 +854,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const uint32_t g = row_or<3>(v);
             if ((L & 7) == 7 && L < W && i - 7 < n) {
                 out[(i - 7) >> 3] = g;
-                if (((i - 7) >> 3) < kWDeltaDw) lcopy[(i - 7) >> 3] = g;
+                if (((i - 7) >> 3) < copied) lcopy[(i - 7) >> 3] = g;
             }
         } else {
             const uint32_t g = W == 4 ? row_or<2>(v) : (W == 2 ? row_or<1>(v) : v);
@@ -858,7 +862,7 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
             const bool full = (((s + 1) << lw) & 7) == 0;
             if (L == W - 1 && (full || s + 1 == steps)) {
                 out[(s << lw) >> 3] = acc;
-                if (((s << lw) >> 3) < kWDeltaDw) lcopy[(s << lw) >> 3] = acc;
+                if (((s << lw) >> 3) < copied) lcopy[(s << lw) >> 3] = acc;
             }
             if (full) acc = 0;
         }
