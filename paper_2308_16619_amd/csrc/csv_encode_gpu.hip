@@ -1101,7 +1101,11 @@ struct DevBuf {
         if (p) (void)hipFree(p);
         p = nullptr;
         bytes = 0;
-        if (hipMalloc(&p, need) != hipSuccess) return false;
+        if (hipMalloc(&p, need) != hipSuccess) {
+            (void)hipGetLastError();  // (the caller goes on without it)
+            p = nullptr;
+            return false;
+        }
         bytes = need;
         return true;
     }
@@ -1156,6 +1160,15 @@ struct EncCache {
             e = nullptr;
         }
     }
+    // arenas 1 and 2 for cap1 bytes of operations and labels; if one cannot
+    // be had, neither is kept
+    bool arenas(uint64_t cap1) {
+        if (arena1.ensure(cap1) && arena2.ensure(part2(cap1))) return true;
+        arena1.release();
+        arena2.release();
+        return false;
+    }
+    uint64_t cap1() const { return std::min<uint64_t>(arena1.bytes, arena2.bytes / part2(1)); }
     // at least bytes of pinned memory
     bool pin(size_t bytes) {
         if (h_pin_bytes >= bytes) return true;
@@ -1170,7 +1183,11 @@ struct EncCache {
     int bring(uint8_t *dst, const uint8_t *src, size_t bytes, hipStream_t s) {
         bool pieces = bytes >= kPiecewise;
         for (unsigned k = 0; pieces && k < kPieces; k++)
-            if (!arrived[k] && hipEventCreateWithFlags(&arrived[k], hipEventDisableTiming) != hipSuccess) pieces = false;
+            if (!arrived[k] && hipEventCreateWithFlags(&arrived[k], hipEventDisableTiming) != hipSuccess) {
+                (void)hipGetLastError();
+                arrived[k] = nullptr;
+                pieces = false;
+            }
         const dim3 grid(kCopyGroups), threads(256);
         if (!pieces) {
             hipLaunchKernelGGL(piece_kernel, grid, threads, 0, s, src, h_pin, (uint64_t)bytes);
@@ -1267,16 +1284,14 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     EncCache *ec = cache_for(device);
     if (!ec) return CSV_ENOMEM;
     std::lock_guard<std::mutex> lk(ec->mu);  // one compression per device at a time
-    // arena 1 at first for a part of 1/12 of the labels (dense cells take
-    // 1/15), or of 1/64 where that does not fit the device
-    auto arenas = [&](uint64_t cap1) -> bool {
-        return ec->arena1.ensure(cap1) && ec->arena2.ensure(part2(ec->arena1.bytes));
-    };
     if (!ec->scratch.ensure(kScratch * grid) || !ec->wscratch.ensure(kWordsScratch * grid2 * kWaves) ||
         !ec->ctl.ensure(sizeof(EncCtl)) || !ec->meta.ensure(sizeof(BrickMeta) * (size_t)B) || !ec->sizes.ensure(4ull * B) ||
         !ec->aoff.ensure(8ull * B) || !ec->arena3.ensure(1ull << 20))
         return CSV_ENOMEM;
-    if (!arenas(std::max<uint64_t>(16ull << 20, raw / 12)) && !arenas(std::max<uint64_t>(16ull << 20, raw / 64)))
+    // arena 1 at first for a part of 1/12 of the labels (dense cells take
+    // 1/15), or of 1/64 where that does not fit the device
+    if (!ec->arenas(std::max<uint64_t>(16ull << 20, raw / 12)) &&
+        !ec->arenas(std::max<uint64_t>(16ull << 20, raw / 64)))
         return CSV_ENOMEM;
     if (!ec->dblob.ensure(rs + std::max<uint64_t>(16ull << 20, raw / 32))) return CSV_ENOMEM;
     if (!ec->h_ctl &&
@@ -1316,7 +1331,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
         a.arena1 = ec->arena1.as<uint8_t>();
         a.arena2 = ec->arena2.as<uint8_t>();
         a.arena3 = ec->arena3.as<uint8_t>();
-        a.cap1 = ec->arena1.bytes;
+        a.cap1 = ec->cap1();
         a.cap3 = ec->arena3.bytes;
         uint64_t *index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
         const uint64_t room = std::min<uint64_t>(std::min<uint64_t>(ec->h_pin_bytes, ec->dblob.bytes), kPiecewise);
@@ -1350,7 +1365,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
             if (hipGetLastError() != hipSuccess) return CSV_EHIP;
             break;
         }
-        if (pass == 2 || !arenas(c.top1) || !ec->arena3.ensure(c.top3)) return CSV_ENOMEM;
+        if (pass == 2 || !ec->arenas(c.top1) || !ec->arena3.ensure(c.top3)) return CSV_ENOMEM;
     }
     const uint64_t total = rs + ec->h_ctl->total;
     DevBuf &dblob = ec->dblob;
