@@ -1191,8 +1191,7 @@ struct EncCache {
         const dim3 grid(kCopyGroups), threads(256);
         if (!pieces) {
             hipLaunchKernelGGL(piece_kernel, grid, threads, 0, s, src, h_pin, (uint64_t)bytes);
-            const bool launched = hipGetLastError() == hipSuccess;
-            if (hipStreamSynchronize(s) != hipSuccess || !launched) return CSV_EHIP;
+            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
             std::memcpy(dst, h_pin, bytes);
             return CSV_OK;
         }
@@ -1204,10 +1203,7 @@ struct EncCache {
             if (m) hipLaunchKernelGGL(piece_kernel, grid, threads, 0, s, src + at, h_pin + at, (uint64_t)m);
             ok = hipGetLastError() == hipSuccess && hipEventRecord(arrived[k], s) == hipSuccess;
         }
-        if (!ok) {
-            (void)hipStreamSynchronize(s);
-            return CSV_EHIP;
-        }
+        if (!ok) return CSV_EHIP;
         std::atomic<unsigned> next{0};
         std::atomic<bool> failed{false};
         auto work = [&] {
@@ -1253,6 +1249,20 @@ struct DeviceGuard {
     }
 };
 
+// A call that fails waits for its launches before the buffers, which the next
+// call uses on another stream, are free again, and takes the runtime's error
+// with it (its code says what failed).
+struct InFlight {
+    hipStream_t s;
+    bool finished = false;
+    explicit InFlight(hipStream_t stream) : s(stream) {}
+    ~InFlight() {
+        if (finished) return;
+        (void)hipStreamSynchronize(s);
+        (void)hipGetLastError();
+    }
+};
+
 }  // namespace
 
 extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
@@ -1284,6 +1294,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     EncCache *ec = cache_for(device);
     if (!ec) return CSV_ENOMEM;
     std::lock_guard<std::mutex> lk(ec->mu);  // one compression per device at a time
+    InFlight flight(s);
     if (!ec->scratch.ensure(kScratch * grid) || !ec->wscratch.ensure(kWordsScratch * grid2 * kWaves) ||
         !ec->ctl.ensure(sizeof(EncCtl)) || !ec->meta.ensure(sizeof(BrickMeta) * (size_t)B) || !ec->sizes.ensure(4ull * B) ||
         !ec->aoff.ensure(8ull * B) || !ec->arena3.ensure(1ull << 20))
@@ -1349,9 +1360,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
             hipLaunchKernelGGL(leave_kernel, dim3(kCopyGroups), dim3(256), 0, s, a, ec->h_ctl,
                                (const uint8_t *)ec->dblob.as<uint8_t>(), rs, ec->h_pin, room);
         }
-        // (waits in any case: the kernels write this cache's pinned memory)
-        const bool launched = hipGetLastError() == hipSuccess;
-        if (hipStreamSynchronize(s) != hipSuccess || !launched) return CSV_EHIP;
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
         const EncCtl &c = *ec->h_ctl;
         if (c.top1 <= a.cap1 && c.top3 <= a.cap3) {
             there = rs + c.total < room;
@@ -1371,10 +1380,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     DevBuf &dblob = ec->dblob;
     if (!ec->pin(total)) return CSV_ENOMEM;
     uint8_t *out = static_cast<uint8_t *>(alloc(total, ctx));
-    if (!out) {
-        (void)hipStreamSynchronize(s);
-        return CSV_ENOMEM;
-    }
+    if (!out) return CSV_ENOMEM;
     if (there)
         std::memcpy(out, ec->h_pin, total);
     else if (const int rc = ec->bring(out, dblob.as<uint8_t>(), total, s))
@@ -1401,6 +1407,7 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     const uint64_t idx_end = csv::kHeaderBytes + 8ull * (B + 1);
     std::memset(out + idx_end, 0, rs - idx_end);  // padding before the record area
     *blob_bytes = total;
+    flight.finished = true;
     return CSV_OK;
 }
 

@@ -285,6 +285,24 @@ int main(int argc, char **argv) {
         ops = 9000;
         check(call(64) == CSV_OK, "a small call after one that did not fit");
         check(call(512) == CSV_OK, "a middle-sized call");
+    } else if (what == "every failure") {
+        // call k of the runtime fails, for every k: nothing stays in flight,
+        // and the next call succeeds
+        for (uint32_t e : {64u, 700u}) {
+            if (e == 700) extra = 400, rec = 5000;  // larger than the container's buffer at first
+            fail_at = -1;
+            calls = 0;
+            check(csv_encode_gpu_release(0) == CSV_OK && call(e) == CSV_OK, "a call");
+            const int n = calls;
+            for (int k = 0; k < n; k++) {
+                check(csv_encode_gpu_release(0) == CSV_OK, "release");
+                calls = 0;
+                fail_at = k;
+                (void)call(e);
+                fail_at = -1;
+                check(call(e) == CSV_OK, "a call after a failed one");
+            }
+        }
     } else {
         check(false, "no such scenario");
     }
