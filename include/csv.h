@@ -599,7 +599,10 @@ int csv_frame_cache_create(csv_pool *pool, uint64_t cache_bytes, uint32_t max_re
  * CSV_EINVAL (null pointers, n above max_requests), CSV_ENOMEM (with stats:
  * the frame's distinct bricks alone exceed the cache: nothing is cached,
  * every slot UINT64_MAX; without stats the same frame returns CSV_OK and
- * csv_frame_cache_last_stats reports CSV_ENOMEM), CSV_EHIP.  A cache over a
+ * csv_frame_cache_last_stats reports CSV_ENOMEM), CSV_EHIP, and those of
+ * the decode.  After a frame that failed otherwise than by its size, the
+ * next one starts from an empty cache; let it be a call, not the replay of a
+ * graph with an earlier frame.  A cache over a
  * pool that keeps level-0 detail in host memory takes its frames through
  * csv_frame_cache_frame_detail (this call returns CSV_EINVAL).
  */

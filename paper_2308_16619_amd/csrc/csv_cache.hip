@@ -118,10 +118,21 @@ __device__ __forceinline__ uint32_t take_places(uint32_t *top, uint32_t *s_cnt, 
 
 constexpr uint32_t kMarkThreads = 256;
 
-// after a frame whose launches failed part way: the running counts from zero
+// after a frame that failed part way: its number is not used again (stamps of
+// it may be there), the running counts start from zero, and so does the cache,
+// as keys may have been given blocks that were not decoded
 __global__ void reset_kernel(CacheDev c) {
-    if (threadIdx.x < kLods) c.st->run_miss[threadIdx.x] = c.st->run_uniq[threadIdx.x] = 0;
-    if (threadIdx.x == 0) c.st->run_evicted = c.st->run_want = 0;
+    const uint64_t nk = (uint64_t)c.n_bricks * kLods;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < nk; i += (uint64_t)gridDim.x * blockDim.x)
+        c.index[i] = kNone64;
+    if (blockIdx.x != 0) return;
+    FrameState *st = c.st;
+    if (threadIdx.x < kLods) st->run_miss[threadIdx.x] = st->run_uniq[threadIdx.x] = st->stack_top[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        st->run_evicted = st->run_want = 0;
+        st->top = 0;
+        st->frame++;
+    }
 }
 
 // request r: a visible, cacheable key is stamped with the frame; its first
@@ -313,7 +324,7 @@ struct csv_frame_cache {
     uint8_t *vis = nullptr;    // per request: visibility mask
     FrameState *h_st = nullptr;  // pinned copy of the frame state
     uint32_t last_n = 0;         // requests of the last frame
-    bool dirty = false;          // a frame's launches failed part way
+    bool dirty = false;          // a frame failed part way: the next one starts with reset_kernel
     // detail streaming (pools with level-0 detail in host memory)
     bool detail = false;
     uint8_t *d_det = nullptr;         // CacheDev::det
@@ -515,7 +526,12 @@ static int frame_impl(csv_frame_cache *c, const uint32_t *ids, const uint8_t *lo
     }
     const uint8_t *vis = test ? c->vis : nullptr;
     const uint32_t gr = std::max(1u, (n + 255) / 256);
-    if (c->dirty) hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(64), 0, s, d);
+    // (a reset recorded into a graph has not run yet: the next frame may come
+    // before the graph, and then needs its own)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool reset_later = c->dirty && hipStreamIsCapturing(s, &capture) == hipSuccess &&
+                             capture != hipStreamCaptureStatusNone;
+    if (c->dirty) hipLaunchKernelGGL(reset_kernel, dim3(256), dim3(256), 0, s, d);
     c->dirty = true;
     if (n)
         hipLaunchKernelGGL(mark_kernel, dim3((n + kMarkThreads - 1) / kMarkThreads), dim3(kMarkThreads), 0, s, d, ids,
@@ -524,7 +540,6 @@ static int frame_impl(csv_frame_cache *c, const uint32_t *ids, const uint8_t *lo
     hipLaunchKernelGGL(evict_kernel, dim3((uint32_t)std::min<uint64_t>((nk + 1023) / 1024, 1024)), dim3(1024), 0, s, d);
     hipLaunchKernelGGL(assign_kernel, dim3(1), dim3(1024), 0, s, d);
     if (hipGetLastError() != hipSuccess) return CSV_EHIP;
-    c->dirty = false;
     c->last_n = n;
     int rc = CSV_OK;
     FrameState st{};
@@ -560,6 +575,7 @@ static int frame_impl(csv_frame_cache *c, const uint32_t *ids, const uint8_t *lo
         if (dstats) dstats->fallbacks = st.n_want;
     }
     if (hipGetLastError() != hipSuccess && !rc) rc = CSV_EHIP;
+    if (!rc) c->dirty = reset_later;
     if (stats) {
         fill_stats(c, st, stats);
         if (!rc && st.error) rc = CSV_ENOMEM;
