@@ -2929,9 +2929,11 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     if (slow && (!B->arenas || B->arena_groups < grid_g)) {
         if (!B->owned || capturing(s)) return CSV_EBUSY;  // fixed buffers cannot grow
         uint32_t groups = slow_groups(cu);
-        if (over_budget(pool, (uint64_t)groups * kArenaBytes)) {
+        // (the arenas there are make room for the new ones)
+        auto too_many = [&] { return over_budget(pool, (uint64_t)(groups - B->arena_groups) * kArenaBytes); };
+        if (too_many()) {
             groups = grid_g;  // raw nibbles: no more than this batch needs
-            if (!gen || over_budget(pool, (uint64_t)groups * kArenaBytes)) return CSV_ENOMEM;
+            if (!gen || too_many()) return CSV_ENOMEM;
         }
         if (B->arenas && hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
         const int rc = B->reserve_arenas(groups);
