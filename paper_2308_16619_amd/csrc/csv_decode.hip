@@ -2644,12 +2644,9 @@ int stream_bufs(csv_pool *pool, hipStream_t s, uint32_t n, LaunchBufs **out) {
         if (cap) return CSV_EBUSY;  // buffers cannot be re-sized inside a capture
         if (b->slots && hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
         const uint64_t now = b->slots ? LaunchBufs::sized(b->cap_n, b->slot_dw) : 0;
-        uint64_t want = LaunchBufs::sized(std::max(n, 1024u), dw);
-        uint32_t least = 1024u;
-        if (pool->generic && want > now && over_budget(pool, want - now)) {  // no more than this batch needs
-            want = LaunchBufs::sized(n, dw);
-            least = 1u;
-        }
+        // raw nibbles in a budget: no more than this batch needs
+        const uint32_t least = pool->generic && pool->hbm_budget ? 1u : 1024u;
+        const uint64_t want = LaunchBufs::sized(std::max(n, least), dw);
         if (want > now && over_budget(pool, want - now)) return CSV_ENOMEM;
         const int rc = b->reserve(n, dw, least);
         if (rc) return rc;
@@ -2925,16 +2922,16 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const bool slow = pool->any_big_palette || pool->max_fast_bytes > arena_b(groups_b);
     // buffers the library allocates get one arena per global-arena workgroup; a view of
     // memory it does not allocate brings its own, fewer ones
-    const uint32_t grid_g = std::min(B->owned ? slow_groups(cu) : B->arena_groups, n);
+    uint32_t grid_g = std::min(B->owned ? slow_groups(cu) : B->arena_groups, n);
+    // raw nibbles in a budget: arenas for this batch only, and in a capture
+    // those there are
+    const bool tight = gen && pool->hbm_budget;
+    if (tight && B->arenas && capturing(s)) grid_g = std::min(grid_g, B->arena_groups);
     if (slow && (!B->arenas || B->arena_groups < grid_g)) {
         if (!B->owned || capturing(s)) return CSV_EBUSY;  // fixed buffers cannot grow
-        uint32_t groups = slow_groups(cu);
+        const uint32_t groups = tight ? grid_g : slow_groups(cu);
         // (the arenas there are make room for the new ones)
-        auto too_many = [&] { return over_budget(pool, (uint64_t)(groups - B->arena_groups) * kArenaBytes); };
-        if (too_many()) {
-            groups = grid_g;  // raw nibbles: no more than this batch needs
-            if (!gen || too_many()) return CSV_ENOMEM;
-        }
+        if (over_budget(pool, (uint64_t)(groups - B->arena_groups) * kArenaBytes)) return CSV_ENOMEM;
         if (B->arenas && hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
         const int rc = B->reserve_arenas(groups);
         if (rc) return rc;
@@ -3083,15 +3080,17 @@ int launch(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_t lo
     chunks = std::min(chunks, n / kMinChunk);
     if (pool && pool->generic) {
         chunks = 1;  // (no launch shape)
-        if (pool->brick_log2 == (uint32_t)kLog2 && !plain && !fixed && !words_out && n > kRawChunk / 4 && ids &&
+        const bool cap = capturing(s);
+        if (pool->brick_log2 == (uint32_t)kLog2 && !plain && !fixed && !words_out && (n > kRawChunk / 4 || cap) && ids &&
             out && (!lods || out_off) && (lods || lod_scalar <= (uint32_t)kLog2)) {
             // 32^3 raw nibbles: slots for at most kRawChunk requests; a
             // stream capture, where they cannot grow, uses those there are
+            // (few of them only for a batch that an unlimited pool has slots for)
             uint32_t per = kRawChunk;
-            if (capturing(s)) {
+            if (cap) {
                 std::lock_guard<std::mutex> lk(pool->mu);
                 for (auto &e : pool->bufs)
-                    if (e.stream == s && e.cap_n >= kRawChunk / 4) per = std::min(per, e.cap_n);
+                    if (e.stream == s && e.cap_n && (e.cap_n >= kRawChunk / 4 || n <= 1024u)) per = std::min(per, e.cap_n);
             }
             const uint64_t G = 32u >> (lods ? 0u : lod_scalar), cnt = lods ? 0 : G * G * G;
             int rc = CSV_OK;

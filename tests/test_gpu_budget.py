@@ -27,13 +27,18 @@ def decode(pool, n, n_bricks, edge=32):
     return out.cpu().numpy().view(np.uint32)
 
 
+def raw_blob(csv, seed):
+    """Raw 32^3 bricks, one with a large palette."""
+    vol = synth.cells(n=64, grid=8, seed=seed)
+    vol[:32, :32, :32] = np.random.default_rng(seed).integers(1, 3000, (32, 32, 32)).astype(np.uint32)
+    return csv.encode_volume(vol, coding=1)
+
+
 def test_batches_that_grow_within_a_budget(orc):
     # raw 32^3 bricks: the budget holds the slots and 12 arenas
     torch = torch_cuda()
     import paper_2308_16619_amd as csv
-    vol = synth.cells(n=64, grid=8, seed=4)
-    vol[:32, :32, :32] = np.random.default_rng(4).integers(1, 3000, (32, 32, 32)).astype(np.uint32)
-    blob = csv.encode_volume(vol, coding=1)
+    blob = raw_blob(csv, 4)
     pool = pool_of(csv, blob)
     before = pool.info()["device_bytes"]
     decode(pool, 1, 8)
@@ -44,3 +49,48 @@ def test_batches_that_grow_within_a_budget(orc):
     want = orc.decode_bricks(blob, np.arange(12) % 8, np.zeros(12, np.uint8))
     for n in (8, 9, 12):
         np.testing.assert_array_equal(decode(pool, n, 8), want[:n * 32768])
+
+
+def test_small_batches_leave_the_budget_to_others(orc):
+    # a budget of what an unlimited pool takes for a stream: small batches on
+    # several streams and a second volume fit
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blob = raw_blob(csv, 5)
+    pool = pool_of(csv, blob)
+    decode(pool, 1, 8)
+    pool = pool_of(csv, blob, pool.info()["device_bytes"] + ARENA // 4)
+    want = orc.decode_bricks(blob, np.arange(4), np.zeros(4, np.uint8))
+    for s in [torch.cuda.Stream() for _ in range(3)]:
+        with torch.cuda.stream(s):
+            np.testing.assert_array_equal(decode(pool, 4, 8), want)
+    assert pool.add_volume(blob) == 8
+
+
+@pytest.mark.parametrize("budget", [0, 1 << 30])
+def test_captured_after_a_smaller_batch(orc, budget):
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blob = raw_blob(csv, 6)
+    pool = pool_of(csv, blob, budget)
+    want = orc.decode_bricks(blob, np.arange(8), np.zeros(8, np.uint8)).reshape(8, -1)
+    n = 50
+    ids = torch.zeros(n, dtype=torch.int32, device="cuda")
+    out = torch.empty((n, 32768), dtype=torch.int32, device="cuda")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        pool.decode(ids[:3], out)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("[gpu-test] captured", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        pool.decode(ids, out, stream=s)
+    rng = np.random.default_rng(6)
+    for _ in range(3):
+        now = rng.integers(0, 8, n).astype(np.int32)
+        ids.copy_(torch.from_numpy(now))
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert pool.last_error() == (0, 0)
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want[now])
