@@ -193,8 +193,9 @@ __host__ __device__ constexpr uint64_t part2(uint64_t off1) { return 3 * off1; }
 struct EncArgs {
     const uint32_t *vol;
     uint32_t nx, ny, nz, nbx, nby;
-    uint32_t n_items;          // bricks
-    uint32_t sample_stride;    // the frequency tables count every sample_stride-th brick
+    uint32_t first, step;      // the bricks: first, first + step, ..
+    uint32_t n_items;          // how many
+    uint32_t sample_stride;    // the frequency tables count every sample_stride-th brick (0: none of these)
     uint32_t bits, lane_k, lane_max, one_table;
     EncCtl *ctl;
     BrickMeta *meta;
@@ -310,7 +311,8 @@ __global__ __launch_bounds__(kReuseThreads) __attribute__((amdgpu_waves_per_eu(4
     // this thread's voxels: 4 in x of row (t >> 3) & 31 in the planes t >> 8, + 4, ..
     const uint32_t vx = 4 * (t & 7u), vy = (t >> 3) & 31u, vz = t >> 8;
     uint4 pre[8];
-    auto fetch = [&](uint32_t id) {
+    auto fetch = [&](uint32_t item) {
+        const uint32_t id = a.first + item * a.step;
         const uint64_t x = (uint64_t)(id % a.nbx) * 32 + vx, y = (uint64_t)((id / a.nbx) % a.nby) * 32 + vy;
         const uint64_t z0 = (id / ((uint64_t)a.nbx * a.nby)) * 32;
         const uint32_t *v = glob(a.vol) + x + row * y + plane * (z0 + vz);
@@ -713,7 +715,7 @@ __global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
             m->P = P;
         }
         // the sampled bricks' symbols (the frequency tables, Sec. 3.4)
-        if (id % a.sample_stride == 0) {
+        if (a.sample_stride && (a.first + id * a.step) % a.sample_stride == 0) {
             own_stores();
             const uint32_t leaf = n - D[0] - 8 * E[0];
             for (uint32_t tb = 0; tb < 2; tb++) {
@@ -1087,8 +1089,10 @@ __global__ __launch_bounds__(256) void piece_kernel(const uint8_t *src, uint8_t 
     copy_out(src, dst, bytes);
 }
 
-__global__ __launch_bounds__(256) void begin_kernel(EncCtl *ctl) {
-    if (threadIdx.x < sizeof(EncCtl) / 4) reinterpret_cast<uint32_t *>(ctl)[threadIdx.x] = 0;
+// keep_hist: all but the histograms
+__global__ __launch_bounds__(256) void begin_kernel(EncCtl *ctl, bool keep_hist) {
+    const uint32_t from = keep_hist ? sizeof(EncCtl::hist) / 4 : 0u;
+    if (threadIdx.x >= from && threadIdx.x < sizeof(EncCtl) / 4) reinterpret_cast<uint32_t *>(ctl)[threadIdx.x] = 0;
 }
 
 // a device buffer that grows on demand
@@ -1139,7 +1143,7 @@ struct EncCache {
     uint8_t *h_pin = nullptr;  // pinned staging of the container on its way to host memory
     size_t h_pin_bytes = 0;
     hipEvent_t arrived[kPieces] = {};  // the pieces of a large container
-    void release() {
+    void release_device() {
         scratch.release();
         wscratch.release();
         ctl.release();
@@ -1150,6 +1154,9 @@ struct EncCache {
         arena2.release();
         arena3.release();
         dblob.release();
+    }
+    void release() {
+        release_device();
         if (h_ctl) (void)hipHostFree(h_ctl);
         h_ctl = nullptr;
         if (h_pin) (void)hipHostFree(h_pin);
@@ -1263,6 +1270,183 @@ struct InFlight {
     }
 };
 
+// The most that a brick can ask for: all of its 4,681 parents expanded, a
+// palette entry for each child; a record of two words per child and delta
+constexpr uint64_t kMostOps = 4ull * (kNodes + kMaxChildren) + kPad1;
+constexpr uint64_t kMostRecord = 4ull * (csv::record_header_words(kN) + kMaxChildren + 1 + 64) + 2ull * kMaxSym + 4;
+// Bricks per CU of a batch where the device has no room for all at once, at
+// most (1.28 MB each)
+constexpr uint32_t kBatchPerCu = 16;
+
+// The kernels of a compression on stream s with the buffers of ec; a: the
+// volume and the options, then the bricks and buffers of the launches
+struct Compression {
+    EncCache *ec;
+    hipStream_t s;
+    uint32_t cu;
+    EncArgs a;
+    bool there = false;  // the last run's container is in the pinned buffer
+    uint64_t bytes = 0;  // ... its bytes
+
+    // reuse kernel: a workgroup per CU
+    uint32_t grid(uint32_t n) const { return std::min(n, cu); }
+    uint32_t grid2(uint32_t n) const {
+        return (uint32_t)std::min<uint64_t>(((uint64_t)n + kWaves - 1) / kWaves, (uint64_t)cu * 4);
+    }
+    // what n bricks need apart from the arenas and the container
+    bool room(uint32_t n) {
+        return ec->scratch.ensure(kScratch * grid(n)) && ec->wscratch.ensure(kWordsScratch * grid2(n) * kWaves) &&
+               ec->ctl.ensure(sizeof(EncCtl)) && ec->meta.ensure(sizeof(BrickMeta) * (size_t)n) &&
+               ec->sizes.ensure(4ull * n) && ec->aoff.ensure(8ull * n);
+    }
+    void bind() {
+        a.ctl = ec->ctl.as<EncCtl>();
+        a.meta = ec->meta.as<BrickMeta>();
+        a.scratch = ec->scratch.as<uint8_t>();
+        a.wscratch = ec->wscratch.as<uint8_t>();
+        a.sizes = ec->sizes.as<uint32_t>();
+        a.aoff = ec->aoff.as<uint64_t>();
+        a.arena1 = ec->arena1.as<uint8_t>();
+        a.arena2 = ec->arena2.as<uint8_t>();
+        a.arena3 = ec->arena3.as<uint8_t>();
+        a.cap1 = ec->cap1();
+        a.cap3 = ec->arena3.bytes;
+    }
+    void symbols(bool keep_hist) {
+        hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(256), 0, s, a.ctl, keep_hist);
+        hipLaunchKernelGGL(reuse_kernel, dim3(grid(a.n_items)), dim3(kReuseThreads), sizeof(ReuseLds), s, a);
+        hipLaunchKernelGGL(palette_kernel, dim3(grid2(a.n_items)), dim3(kThreads), 0, s, a);
+    }
+    void gather(uint64_t rs) {
+        uint64_t *index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
+        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a, index);
+        hipLaunchKernelGGL(pack_kernel, dim3(std::min<uint32_t>(a.n_items, cu * 8)), dim3(256), 0, s, a,
+                           (const uint64_t *)index, ec->dblob.as<uint8_t>() + rs, ec->dblob.bytes - rs);
+    }
+    // The container of the a.n_items bricks (its header is not written),
+    // there or in ec->dblob.  CSV_ENOMEM: the device's memory is short.  All
+    // launches in one go, repeated with larger arenas if one was short
+    // (arena 3's demand is only known once arena 1 held).
+    int run(bool keep_hist) {
+        const uint32_t n = a.n_items;
+        const uint64_t rs = csv::record_area_offset(n);
+        for (int pass = 0;; pass++) {
+            bind();
+            const uint64_t cap = std::min<uint64_t>(std::min<uint64_t>(ec->h_pin_bytes, ec->dblob.bytes), kPiecewise);
+            symbols(keep_hist);
+            hipLaunchKernelGGL(rans_kernel, dim3(grid2(n)), dim3(kThreads), 0, s, a);
+            if (n <= kFinishMax) {
+                hipLaunchKernelGGL(finish_kernel, dim3(std::min<uint32_t>(n, cu * 8)), dim3(256), 0, s, a, ec->h_ctl,
+                                   ec->dblob.as<uint8_t>(), (uint64_t)ec->dblob.bytes, rs, ec->h_pin, cap);
+            } else {
+                gather(rs);
+                hipLaunchKernelGGL(leave_kernel, dim3(kCopyGroups), dim3(256), 0, s, a, ec->h_ctl,
+                                   (const uint8_t *)ec->dblob.as<uint8_t>(), rs, ec->h_pin, cap);
+            }
+            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
+            const EncCtl &c = *ec->h_ctl;
+            if (c.top1 <= a.cap1 && c.top3 <= a.cap3) {
+                bytes = rs + c.total;
+                there = bytes < cap;
+                if (bytes <= ec->dblob.bytes) return CSV_OK;
+                // the records did not fit the container's buffer
+                if (!ec->dblob.ensure(bytes)) return CSV_ENOMEM;
+                gather(rs);
+                return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
+            }
+            if (pass == 2 || !ec->arenas(c.top1) || !ec->arena3.ensure(c.top3)) return CSV_ENOMEM;
+        }
+    }
+    // the last run's container, to host memory
+    int take(uint8_t *to) {
+        if (!there) return ec->bring(to, ec->dblob.as<uint8_t>(), bytes, s);
+        std::memcpy(to, ec->h_pin, bytes);
+        return CSV_OK;
+    }
+};
+
+// containers of batches in host memory (the header of each unused)
+struct Batches {
+    struct Piece {
+        Piece *next;
+        uint32_t n;
+        uint64_t bytes;
+        uint8_t *at() { return reinterpret_cast<uint8_t *>(this + 1); }
+    };
+    Piece *head = nullptr, **tail = &head;
+    uint64_t records = 0;
+    ~Batches() {
+        for (Piece *p = head; p;) {
+            Piece *q = p->next;
+            std::free(p);
+            p = q;
+        }
+    }
+    uint8_t *add(uint32_t n, uint64_t bytes) {
+        Piece *p = static_cast<Piece *>(std::malloc(sizeof(Piece) + bytes));
+        if (!p) return nullptr;
+        p->next = nullptr;
+        p->n = n;
+        p->bytes = bytes;
+        *tail = p;
+        tail = &p->next;
+        records += bytes - csv::record_area_offset(n);
+        return p->at();
+    }
+    // the index and the records of the B bricks
+    void join(uint8_t *out, uint32_t B) {
+        uint8_t *to = out + csv::record_area_offset(B);
+        uint64_t *index = reinterpret_cast<uint64_t *>(out + csv::kHeaderBytes), at = 0;
+        for (Piece *p = head; p; p = p->next) {
+            const uint64_t rs = csv::record_area_offset(p->n), m = p->bytes - rs;
+            const uint64_t *from = reinterpret_cast<const uint64_t *>(p->at() + csv::kHeaderBytes);
+            for (uint32_t i = 0; i < p->n; i++) *index++ = at + from[i];
+            std::memcpy(to + at, p->at() + rs, m);
+            at += m;
+        }
+        *index = at;
+    }
+};
+
+// A compression in batches of bricks, for volumes that the device has no room
+// for at once: the symbols of the sampled bricks first, for the frequency
+// tables, then batch after batch, each of as many bricks as there is room for
+// whatever they ask for (so that no launch has to be repeated).  All 4,096
+// bricks of the 512^3 cells volume at once need 0.9 GB besides the container.
+int in_batches(Compression &c, uint32_t B, uint32_t stride, Batches &out) {
+    EncCache *ec = c.ec;
+    uint32_t nb = (uint32_t)std::min<uint64_t>(B, (uint64_t)c.cu * kBatchPerCu);
+    for (;; nb = (nb + 1) / 2) {
+        ec->release_device();
+        if (c.room(nb) && ec->arenas(kMostOps * nb) && ec->arena3.ensure(kMostRecord * nb) &&
+            ec->dblob.ensure(csv::record_area_offset(nb) + kMostRecord * nb))
+            break;
+        if (nb == 1) return CSV_ENOMEM;
+    }
+    c.bind();
+    c.a.step = stride;
+    c.a.sample_stride = 1;
+    const uint32_t samples = (uint32_t)(((uint64_t)B + stride - 1) / stride);
+    for (uint64_t i = 0; i < samples; i += nb) {
+        c.a.first = (uint32_t)(i * stride);
+        c.a.n_items = (uint32_t)std::min<uint64_t>(nb, samples - i);
+        c.symbols(i > 0);
+    }
+    c.a.step = 1;
+    c.a.sample_stride = 0;
+    for (uint64_t at = 0; at < B; at += nb) {
+        c.a.first = (uint32_t)at;
+        c.a.n_items = (uint32_t)std::min<uint64_t>(nb, B - at);
+        int rc = c.run(true);
+        if (rc) return rc;
+        uint8_t *to = out.add(c.a.n_items, c.bytes);
+        if (!to || (!c.there && !ec->pin(c.bytes))) return CSV_ENOMEM;
+        rc = c.take(to);
+        if (rc) return rc;
+    }
+    return CSV_OK;
+}
+
 }  // namespace
 
 extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, uint32_t ny, uint32_t nz,
@@ -1287,24 +1471,12 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     int cu = 0;
     if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cu < 1) cu = 1;
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(B64, (uint64_t)cu);  // reuse kernel: a workgroup per CU
-    const uint32_t grid2 = (uint32_t)std::min<uint64_t>((B64 + kWaves - 1) / kWaves, (uint64_t)cu * 4);
     const uint64_t raw = (uint64_t)nx * ny * nz * 4;
     const uint64_t rs = csv::record_area_offset(B);
     EncCache *ec = cache_for(device);
     if (!ec) return CSV_ENOMEM;
     std::lock_guard<std::mutex> lk(ec->mu);  // one compression per device at a time
     InFlight flight(s);
-    if (!ec->scratch.ensure(kScratch * grid) || !ec->wscratch.ensure(kWordsScratch * grid2 * kWaves) ||
-        !ec->ctl.ensure(sizeof(EncCtl)) || !ec->meta.ensure(sizeof(BrickMeta) * (size_t)B) || !ec->sizes.ensure(4ull * B) ||
-        !ec->aoff.ensure(8ull * B) || !ec->arena3.ensure(1ull << 20))
-        return CSV_ENOMEM;
-    // arena 1 at first for a part of 1/12 of the labels (dense cells take
-    // 1/15), or of 1/64 where that does not fit the device
-    if (!ec->arenas(std::max<uint64_t>(16ull << 20, raw / 12)) &&
-        !ec->arenas(std::max<uint64_t>(16ull << 20, raw / 64)))
-        return CSV_ENOMEM;
-    if (!ec->dblob.ensure(rs + std::max<uint64_t>(16ull << 20, raw / 32))) return CSV_ENOMEM;
     if (!ec->h_ctl &&
         hipHostMalloc(reinterpret_cast<void **>(&ec->h_ctl), sizeof(EncCtl), hipHostMallocDefault) != hipSuccess)
         return CSV_ENOMEM;
@@ -1314,7 +1486,11 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(reuse_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(ReuseLds));
     });
-    EncArgs a;
+    Compression c;
+    c.ec = ec;
+    c.s = s;
+    c.cu = (uint32_t)cu;
+    EncArgs &a = c.a;
     std::memset(&a, 0, sizeof(a));
     a.vol = labels;
     a.nx = nx;
@@ -1322,69 +1498,31 @@ extern "C" int csv_encode_volume_gpu_alloc(const uint32_t *labels, uint32_t nx, 
     a.nz = nz;
     a.nbx = nbx;
     a.nby = nby;
+    a.step = 1;
     a.n_items = B;
     a.sample_stride = stride;
     a.bits = o.scale_bits;
     a.lane_k = o.lane_k;
     a.lane_max = o.lane_max;
     a.one_table = o.tables == 1 ? 1u : 0u;
-    a.ctl = ec->ctl.as<EncCtl>();
-    a.meta = ec->meta.as<BrickMeta>();
-    a.scratch = ec->scratch.as<uint8_t>();
-    a.wscratch = ec->wscratch.as<uint8_t>();
-    a.sizes = ec->sizes.as<uint32_t>();
-    a.aoff = ec->aoff.as<uint64_t>();
-    // all launches in one go; repeated with larger arenas if one was short
-    // (arena 3's demand is only known once arena 1 held)
-    const uint32_t grid_p = std::min<uint32_t>(B, (uint32_t)cu * 8);
-    bool there = false;  // the container is in the pinned buffer
-    for (int pass = 0;; pass++) {
-        a.arena1 = ec->arena1.as<uint8_t>();
-        a.arena2 = ec->arena2.as<uint8_t>();
-        a.arena3 = ec->arena3.as<uint8_t>();
-        a.cap1 = ec->cap1();
-        a.cap3 = ec->arena3.bytes;
-        uint64_t *index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
-        const uint64_t room = std::min<uint64_t>(std::min<uint64_t>(ec->h_pin_bytes, ec->dblob.bytes), kPiecewise);
-        hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(256), 0, s, a.ctl);
-        hipLaunchKernelGGL(reuse_kernel, dim3(grid), dim3(kReuseThreads), sizeof(ReuseLds), s, a);
-        hipLaunchKernelGGL(palette_kernel, dim3(grid2), dim3(kThreads), 0, s, a);
-        hipLaunchKernelGGL(rans_kernel, dim3(grid2), dim3(kThreads), 0, s, a);
-        if (B <= kFinishMax) {
-            hipLaunchKernelGGL(finish_kernel, dim3(grid_p), dim3(256), 0, s, a, ec->h_ctl, ec->dblob.as<uint8_t>(),
-                               (uint64_t)ec->dblob.bytes, rs, ec->h_pin, room);
-        } else {
-            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a, index);
-            hipLaunchKernelGGL(pack_kernel, dim3(grid_p), dim3(256), 0, s, a, (const uint64_t *)index,
-                               ec->dblob.as<uint8_t>() + rs, ec->dblob.bytes - rs);
-            hipLaunchKernelGGL(leave_kernel, dim3(kCopyGroups), dim3(256), 0, s, a, ec->h_ctl,
-                               (const uint8_t *)ec->dblob.as<uint8_t>(), rs, ec->h_pin, room);
-        }
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return CSV_EHIP;
-        const EncCtl &c = *ec->h_ctl;
-        if (c.top1 <= a.cap1 && c.top3 <= a.cap3) {
-            there = rs + c.total < room;
-            if (rs + c.total <= ec->dblob.bytes) break;
-            // the records did not fit the container's buffer
-            if (!ec->dblob.ensure(rs + c.total)) return CSV_ENOMEM;
-            index = reinterpret_cast<uint64_t *>(ec->dblob.as<uint8_t>() + csv::kHeaderBytes);
-            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, a, index);
-            hipLaunchKernelGGL(pack_kernel, dim3(grid_p), dim3(256), 0, s, a, (const uint64_t *)index,
-                               ec->dblob.as<uint8_t>() + rs, ec->dblob.bytes - rs);
-            if (hipGetLastError() != hipSuccess) return CSV_EHIP;
-            break;
-        }
-        if (pass == 2 || !ec->arenas(c.top1) || !ec->arena3.ensure(c.top3)) return CSV_ENOMEM;
-    }
-    const uint64_t total = rs + ec->h_ctl->total;
-    DevBuf &dblob = ec->dblob;
-    if (!ec->pin(total)) return CSV_ENOMEM;
+    // arena 1 at first for a part of 1/12 of the labels (dense cells take
+    // 1/15), or of 1/64 where that does not fit the device
+    const bool fits = c.room(B) && ec->arena3.ensure(1ull << 20) &&
+                      (ec->arenas(std::max<uint64_t>(16ull << 20, raw / 12)) ||
+                       ec->arenas(std::max<uint64_t>(16ull << 20, raw / 64))) &&
+                      ec->dblob.ensure(rs + std::max<uint64_t>(16ull << 20, raw / 32));
+    int rc = fits ? c.run(false) : CSV_ENOMEM;
+    Batches batches;
+    const bool parts = rc == CSV_ENOMEM;
+    if (parts) rc = in_batches(c, B, stride, batches);
+    if (rc) return rc;
+    const uint64_t total = parts ? rs + batches.records : c.bytes;
+    if (!parts && !ec->pin(total)) return CSV_ENOMEM;
     uint8_t *out = static_cast<uint8_t *>(alloc(total, ctx));
     if (!out) return CSV_ENOMEM;
-    if (there)
-        std::memcpy(out, ec->h_pin, total);
-    else if (const int rc = ec->bring(out, dblob.as<uint8_t>(), total, s))
-        return rc;
+    if (parts) batches.join(out, B);
+    else rc = c.take(out);
+    if (rc) return rc;
     csv::VolumeHeader h;
     std::memset(&h, 0, sizeof(h));
     h.magic = csv::kMagic;

@@ -20,6 +20,7 @@ hipError_t last = hipSuccess;
 int calls = 0, fail_at = -1;              // calls that can fail; the one that does
 uint64_t ops = 9000, extra = 0;           // bytes of arenas 1 and 3 per brick
 uint32_t rec = 64;                        // ... of a record, at least
+uint64_t samples = 0;                     // bricks that the frequency tables count
 dim3 grid, block;
 std::mutex mu;
 
@@ -79,7 +80,8 @@ std::function<void()> effect(const std::string &k, void **args, uint32_t groups)
     auto is = [&](const char *s) { return k.find(s) != std::string::npos; };
     if (is("begin_kernel")) {
         EncCtl *c = arg<EncCtl *>(args, 0);
-        return [c] { std::memset(c, 0, sizeof(*c)); };
+        const size_t keep = arg<bool>(args, 1) ? sizeof(c->hist) : 0;
+        return [c, keep] { std::memset((char *)c + keep, 0, sizeof(*c) - keep); };
     }
     if (is("piece_kernel")) {
         auto src = arg<const uint8_t *>(args, 0);
@@ -98,17 +100,22 @@ std::function<void()> effect(const std::string &k, void **args, uint32_t groups)
             check(sizeof(BrickMeta) * (size_t)a.n_items <= room(a.meta), "bricks' states");
             a.ctl->top1 += ops * a.n_items;
         };
-    if (is("palette_kernel")) return [a] { a.ctl->hist[0][0] += a.n_items; };
+    if (is("palette_kernel"))
+        return [a] {
+            for (uint32_t i = 0; i < a.n_items; i++)
+                if (a.sample_stride && (a.first + i * a.step) % a.sample_stride == 0) a.ctl->hist[0][0]++;
+        };
     if (is("rans_kernel"))
         return [a, groups] {
             check(kWordsScratch * kWaves * groups <= room(a.wscratch), "rANS kernel's scratch");
             check(a.cap3 <= room(a.arena3), "arena 3");
+            check(fail_at >= 0 || a.ctl->hist[0][0] == samples, "the sampled bricks, each once");
             check(4ull * a.n_items <= room(a.sizes) && 8ull * a.n_items <= room(a.aoff), "records' places");
             if (a.ctl->top1 > a.cap1) return;  // (some bricks have no operations)
             a.ctl->top3 += extra * a.n_items;
             for (uint32_t i = 0; i < a.n_items; i++) {
-                a.sizes[i] = record_bytes(i);
-                a.aoff[i] = i;
+                a.sizes[i] = record_bytes(a.first + i * a.step);
+                a.aoff[i] = a.first + i * a.step;
             }
         };
     if (is("scan_kernel")) {
@@ -244,11 +251,12 @@ static int call(uint32_t edge) {
     static const uint32_t label = 0;  // (never read: the kernels do not run)
     uint8_t *blob = nullptr;
     size_t n = 0;
+    const uint32_t e = (edge + 31) / 32, B = e * e * e;
+    samples = (B + 511) / 512;
     const int rc = csv_encode_volume_gpu(&label, edge, edge, edge, nullptr, 0, nullptr, &blob, &n);
     check(queue.empty(), "the call returned with kernels in flight");
     check((rc == CSV_OK) == (blob != nullptr), "a container if and only if the call succeeds");
     if (rc == CSV_OK) {
-        const uint32_t e = (edge + 31) / 32, B = e * e * e;
         const uint64_t rs = csv::record_area_offset(B);
         auto index = reinterpret_cast<const uint64_t *>(blob + csv::kHeaderBytes);
         uint64_t at = 0;
@@ -288,7 +296,8 @@ int main(int argc, char **argv) {
     } else if (what == "every failure") {
         // call k of the runtime fails, for every k: nothing stays in flight,
         // and the next call succeeds
-        for (uint32_t e : {64u, 700u}) {
+        for (uint32_t e : {64u, 260u, 700u}) {
+            limit = e == 260 ? 150 * MiB : ~(size_t)0;  // (in batches)
             if (e == 700) extra = 400, rec = 5000;  // larger than the container's buffer at first
             fail_at = -1;
             calls = 0;
@@ -303,6 +312,28 @@ int main(int argc, char **argv) {
                 check(call(e) == CSV_OK, "a call after a failed one");
             }
         }
+    } else if (what == "batches") {
+        // noise: the most that bricks can ask for
+        ops = kMostOps;
+        extra = rec = 160000;
+        for (size_t m : {3000, 800, 300, 100, 40}) {
+            check(csv_encode_gpu_release(0) == CSV_OK, "release");
+            limit = m * MiB;
+            check(call(256) == CSV_OK, "noise in little memory");
+        }
+        check(call(64) == CSV_OK && call(256) == CSV_OK, "calls after it");
+        limit = 2 * MiB;  // a brick at a time
+        check(csv_encode_gpu_release(0) == CSV_OK && call(128) == CSV_OK, "noise, brick by brick");
+        limit = MiB / 2;
+        check(csv_encode_gpu_release(0) == CSV_OK && call(64) == CSV_ENOMEM, "no room for a brick");
+        limit = ~(size_t)0;
+        check(call(256) == CSV_OK, "a call with enough memory");
+        // more than three batches of sampled bricks, the last one ragged
+        ops = 3000;
+        extra = 0;
+        rec = 64;
+        limit = 4 * MiB;
+        check(csv_encode_gpu_release(0) == CSV_OK && call(700) == CSV_OK, "many sampled bricks");
     } else {
         check(false, "no such scenario");
     }

@@ -25,7 +25,8 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["plain", "smaller arenas", "small after too large", "every failure"])
+@pytest.mark.parametrize("scenario", ["plain", "smaller arenas", "small after too large", "every failure",
+                                      "batches"])
 def test_host_code_of_the_gpu_compressor(driver, scenario):
     r = subprocess.run([driver, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr

@@ -105,3 +105,33 @@ def test_sizes_scanned_per_workgroup_or_once(csvlib, orc, by, bx):
     for y, x in zip(rng.integers(0, 32 * by, 4000), rng.integers(0, 32 * bx, 4000)):
         vol[0, y:y + 9, x:x + 5] = y + x
     check(csvlib, orc, vol)
+
+
+@pytest.mark.parametrize("left,sample_stride", [(110, 0), (48, 3)])
+def test_little_device_memory(csvlib, orc, left, sample_stride):
+    # in batches of bricks, as the device has no room for all of them at once
+    torch = torch_cuda()
+    vol = synth.cells(n=192, grid=14, seed=31)
+    vol[:96] = np.random.default_rng(31).integers(1, 1 << 30, (96, 192, 192)).astype(np.uint32)
+    opts = {"scale_bits": 10, "lane_k": 64, "lane_max": 64, "sample_stride": sample_stride}
+    want = orc.encode_volume(vol, **opts)
+    dev = torch.from_numpy(vol.view(np.int32)).cuda()
+    assert csvlib.encode_volume_gpu(dev, **opts) == want
+    csvlib.encode_gpu_release(0)
+    torch.cuda.empty_cache()
+    fill = []
+    while len(fill) < 8 and torch.cuda.mem_get_info()[0] >> 20 > left + 16:
+        fill.append(torch.empty(torch.cuda.mem_get_info()[0] - (left << 20), dtype=torch.uint8, device="cuda"))
+    now = torch.cuda.mem_get_info()[0] >> 20
+    print("[gpu-test] %d MiB left" % now, flush=True)
+    try:
+        if now <= left + 64:
+            assert csvlib.encode_volume_gpu(dev, **opts) == want
+            assert csvlib.encode_volume_gpu(dev[:33, :40, :50].contiguous(), **opts) == orc.encode_volume(
+                np.ascontiguousarray(vol[:33, :40, :50]), **opts)
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+        csvlib.encode_gpu_release(0)
+    assert now <= left + 64
+    assert csvlib.encode_volume_gpu(dev, **opts) == want
