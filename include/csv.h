@@ -97,11 +97,16 @@ void csv_free(void *p);
  * runs on `stream` (NULL: the null stream) and the call returns when the
  * blob is in host memory (*blob, release with csv_free).  Only 32^3 bricks
  * (opts->brick_log2 5) and rANS coding (opts->coding 0); opts->threads is
- * ignored.  The call keeps its device
- * buffers (2.5 MiB per CU, arenas of together a third of the labels' bytes,
- * or more where a volume's operations need it, and the container) and a
- * pinned host buffer of the container's
- * size for later calls on the same device, until csv_encode_gpu_release;
+ * ignored.  The call keeps its device buffers for later calls on the same
+ * device: scratch of the kernels (0.17 MB per brick, at most per CU, and 0.15
+ * MB per brick, at most for 16 per CU), arenas of together a third of the
+ * labels' bytes (64 MiB at least; four times the operations' and labels'
+ * bytes where that is more, for noise five times the labels' bytes) and the
+ * container (16 MiB plus the index at least, or a 32nd of the labels' bytes).
+ * Where the device has no room for these, the volume is compressed in batches
+ * of as many bricks as there is room for, 1.6 MB each: slower, with the same
+ * container.  A pinned host buffer of the container's (or batch's) size, 1
+ * MiB at least, is kept as well, all until csv_encode_gpu_release;
  * calls on one device run one at a time.  Errors: CSV_EINVAL (null
  * pointers, zero dims, options out of range, a bad device), CSV_ERANGE
  * (2^32 or more bricks), CSV_ENOMEM, CSV_EHIP.
