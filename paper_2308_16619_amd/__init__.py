@@ -109,6 +109,9 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libcsv.so is not built: run paper_2308_16619_amd/build.py")
         L = ctypes.CDLL(LIB_PATH)
+        # (csv_encode_volume_gpu_alloc came within version 4)
+        if any(not hasattr(L, f) for f in ("csv_abi_version", "csv_encode_volume_gpu_alloc")) or L.csv_abi_version() != 4:
+            raise RuntimeError("libcsv.so ABI mismatch")
         vp, u32, u64, i32 = ctypes.c_void_p, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int
         L.csv_abi_version.restype = u32
         L.csv_strerror.restype = ctypes.c_char_p
@@ -176,8 +179,6 @@ def lib():
         L.csv_frame_cache_read.argtypes = [vp, u64, u64, vp]
         L.csv_frame_cache_last_stats.argtypes = [vp, ctypes.POINTER(FrameStats)]
         L.csv_frame_cache_destroy.argtypes = [vp]
-        if L.csv_abi_version() != 4:
-            raise RuntimeError("libcsv.so ABI mismatch")
         _lib = L
     return _lib
 
