@@ -94,3 +94,70 @@ def test_captured_after_a_smaller_batch(orc, budget):
         torch.cuda.synchronize()
         assert pool.last_error() == (0, 0)
         np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want[now])
+
+
+def volume64(seed):
+    vol = synth.cells(n=128, grid=9, seed=seed)
+    vol[:20, :20, :20] = np.random.default_rng(seed).integers(1, 1 << 30, (20, 20, 20)).astype(np.uint32)
+    vol[:64, 64:, :64] = 5
+    return vol
+
+
+def workgroup_bytes(blob, n_bricks):
+    """What a 64^3 request needs where a workgroup decodes it in memory: a
+    byte per symbol, five bytes per node, four per parent of the finest level."""
+    rs = (128 + 8 * (n_bricks + 1) + 15) & ~15
+    c0 = max(int(np.frombuffer(blob, np.uint32, 4, rs + int(i))[3]) for i in np.frombuffer(blob, np.uint64, n_bricks, 128))
+    nodes = sum(8 ** k for k in range(7))
+    up = lambda v: (v + 255) & ~255  # noqa: E731
+    return up(c0 + 16) + up(4 * nodes) + up(nodes) + up(4 * 8 ** 5)
+
+
+@pytest.mark.parametrize("coding", [0, 1])
+@pytest.mark.parametrize("n", [1, 5])
+def test_edge64_within_a_budget(orc, coding, n):
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(7), brick_log2=6, coding=coding)
+    base = pool_of(csv, blob).info()["device_bytes"]
+    want = orc.decode_bricks(blob, np.arange(n), np.zeros(n, np.uint8))
+    pool = pool_of(csv, blob, base + 64 + n * workgroup_bytes(blob, 8))
+    np.testing.assert_array_equal(decode(pool, n, 8, 64), want)
+    # a budget below one request's slot
+    pool = pool_of(csv, blob, base + (100 << 10))
+    with pytest.raises(csv.CsvError) as e:
+        decode(pool, n, 8, 64)
+    assert e.value.code == csv.CSV_ENOMEM
+
+
+@pytest.mark.parametrize("coding", [0, 1])
+def test_edge64_captured(orc, coding):
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(8), brick_log2=6, coding=coding)
+    pool = pool_of(csv, blob)
+    want = orc.decode_bricks(blob, np.arange(8), np.zeros(8, np.uint8)).reshape(8, -1)
+    n = 12
+    ids = torch.zeros(n, dtype=torch.int32, device="cuda")
+    out = torch.empty((n, 64 ** 3), dtype=torch.int32, device="cuda")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        pool.decode(ids, out)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("[gpu-test] captured", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        pool.decode(ids, out, stream=s)
+    rng = np.random.default_rng(8)
+    for _ in range(3):
+        now = rng.integers(0, 8, n).astype(np.int32)
+        ids.copy_(torch.from_numpy(now))
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert pool.last_error() == (0, 0)
+        np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want[now])
+    fresh = pool_of(csv, blob)
+    with pytest.raises(csv.CsvError) as e:  # no slots on this stream, and they cannot be made in a capture
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=s):
+            fresh.decode(ids, out, stream=s)
+    assert e.value.code == csv.CSV_EBUSY
