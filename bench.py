@@ -45,7 +45,7 @@ def log(msg):
 def decoder_hash():
     """sha256 prefix of the decoder's sources (kernels and the table format)."""
     h = hashlib.sha256()
-    for f in ("csv_decode.hip", "csv_format.hpp"):
+    for f in ("csv_decode.hip", "csv_brick64.hpp", "csv_format.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2308_16619_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
