@@ -210,7 +210,7 @@ __global__ __launch_bounds__(64 * kWavesGen) void entropy64_kernel(DecodeArgs a,
             h.c0 = g.c[1];
             h.c1 = 0;
             uint32_t words = 0;
-            ok = entropy_decode<kLutLds, -1>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
+            ok = entropy_decode<kLutLds, -1, true>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
                                              reinterpret_cast<uint32_t *>(slot + l.nib_off),
                                              reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
             wsync();

@@ -644,9 +644,10 @@ __device__ __forceinline__ void wave_sync() {
 // at_upper (with the paired front kernel) is called once, in wave-uniform
 // control flow, as soon as the nibble dwords of the first c_1 symbols (the
 // levels above L_0) are written, else at the end
-// kNarrow: blocks of 8 steps also for bricks of 8, 16 or 32 states, the rule
-// for bricks of a smaller edge (16^3 bricks have 16 or 32 states; decoding
-// 32,768 of them takes 0.32 ms).  The kernels for 32^3 rANS pools leave it
+// kNarrow: blocks of 8 steps also for bricks of 1 to 32 states, the rule
+// for bricks of another edge (16^3 bricks have 16 or 32 states; decoding
+// 32,768 of them takes 0.32 ms.  8^3 bricks have up to 8: 16 of them take 24
+// us, and 44 step by step).  The kernels for 32^3 rANS pools leave it
 // out: their bricks mostly have 64 states, and the added code made the front
 // kernel 1 % slower (32,768 and 4,096 bricks at full LOD).
 template <bool kLutLds, int SH = 0, bool kNarrow = false, class Hook = NoHook>
@@ -787,8 +788,8 @@ __device__ __forceinline__ bool entropy_decode(const DecodeArgs &a, const Hdr &h
         // words past the end of the stream came from stale ring entries
         bad = cursor > h.nw;
         if (bad) s = steps;
-    } else if (kNarrow && W >= 8) {
-        // 8, 16 or 32 states: the same blocks of 8 steps, lanes from W on left out of the ballot.
+    } else if (kNarrow) {
+        // 1 to 32 states: the same blocks of 8 steps, lanes from W on left out of the ballot.
         // What those lanes write behind a step's W symbol bytes is
         // overwritten by the next step (the last step's ends below byte
         // 7 * 32 + 64 of the 512).
