@@ -2,8 +2,9 @@
 // rANS or raw nibbles; part of csv_decode.hip, whose helpers it uses.  A
 // decode is up to three launches:
 //   entropy64_kernel  (pools with rANS volumes) one wave per brick: the
-//                     symbols as packed nibbles in the request's slot; raw
-//                     bricks are read where they lie in the record;
+//                     symbols as packed nibbles in the request's slot (few
+//                     requests or symbols: a wave of upper64_kernel instead);
+//                     raw bricks are read where they lie in the record;
 //   upper64_kernel    a workgroup per brick: levels 5 .. max(t, 1) in LDS
 //                     (u16 palette indices, Morton order), one lane per
 //                     parent; t >= 1: the output.  t = 0: level 1, its
@@ -172,6 +173,35 @@ __device__ __forceinline__ bool short_delta(uint32_t ipb, uint32_t pam, uint32_t
     return bad;
 }
 
+// The symbols of request g as packed nibbles in its slot, by one wave with wl
+// (kWaveLds bytes) of LDS; false on a malformed stream
+template <bool kLutLds>
+__device__ __forceinline__ bool entropy64(const DecodeArgs &a, const Launch64 &l, const Hdr64 &g, uint8_t *slot,
+                                          const uint32_t *slut, uint8_t *wl) {
+    const uint32_t n = g.t == 0   ? g.c[0]
+                       : g.t == 1 ? g.c[1]
+                       : g.t == 2 ? g.c[2]
+                       : g.t == 3 ? g.c[3]
+                       : g.t == 4 ? g.c[4]
+                                  : g.c[5];
+    if (n + 16 > 8 * l.nib_dw) return false;
+    Hdr h;
+    h.rec = g.rec;
+    h.sfx = nullptr;
+    h.pdw = 0xFFFFFFFFu;
+    h.P = g.P;
+    h.W = g.W;
+    h.nw = g.nw;
+    h.vol = g.vol;
+    h.t = g.t - 1u;  // (levels of a 64^3 brick are one above those of Hdr)
+    h.c0 = g.c[1];
+    h.c1 = 0;
+    uint32_t words = 0;
+    return entropy_decode<kLutLds, -1, true>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
+                                             reinterpret_cast<uint32_t *>(slot + l.nib_off),
+                                             reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
+}
+
 // One wave per rANS request; a serial chain of c_t / 64 steps (a brick of
 // the 512^3 cells volume has 100,000 symbols), so a launch of 512 bricks is
 // bound by that chain's latency, not by the machine.
@@ -190,34 +220,16 @@ __global__ __launch_bounds__(64 * kWavesGen) void entropy64_kernel(DecodeArgs a,
         const ReqKind kind = load_request64(a, rq, g, dst, count, fill);
         if (kind != kReqDecode || g.raw) continue;
         uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
-        const uint32_t n = g.t == 0   ? g.c[0]
-                           : g.t == 1 ? g.c[1]
-                           : g.t == 2 ? g.c[2]
-                           : g.t == 3 ? g.c[3]
-                           : g.t == 4 ? g.c[4]
-                                      : g.c[5];
-        bool ok = n + 16 <= 8 * l.nib_dw;
-        if (ok) {
-            Hdr h;
-            h.rec = g.rec;
-            h.sfx = nullptr;
-            h.pdw = 0xFFFFFFFFu;
-            h.P = g.P;
-            h.W = g.W;
-            h.nw = g.nw;
-            h.vol = g.vol;
-            h.t = g.t - 1u;  // (levels of a 64^3 brick are one above those of Hdr)
-            h.c0 = g.c[1];
-            h.c1 = 0;
-            uint32_t words = 0;
-            ok = entropy_decode<kLutLds, -1, true>(a, h, slut, reinterpret_cast<uint32_t *>(wl),
-                                             reinterpret_cast<uint32_t *>(slot + l.nib_off),
-                                             reinterpret_cast<uint32_t *>(wl + kWPal), n, words);
-            wsync();
-        }
+        const bool ok = entropy64<kLutLds>(a, l, g, slot, slut, wl);
+        wsync();
         if (lane() == 0) reinterpret_cast<Head64 *>(slot + k64Head)->bad = ok ? 0u : 1u;
     }
 }
+
+// Who decodes the symbols before upper64_kernel replays them: a launch of
+// entropy64_kernel, or the workgroup's own first wave, with the tables in LDS
+// (in the place of level 1, which comes later) or in global memory
+enum class Symbols64 { kLaunch, kOwnLds, kOwnGlobal };
 
 // LDS of an upper workgroup: levels 2..5 and the root (u16), level 1, the
 // expansion bits of levels 1..5 and of the root (64-bit words), expanded
@@ -226,6 +238,7 @@ __device__ constexpr uint32_t k64Lv[7] = {0, 0, 0, 4096, 4608, 4672, 4680};
 __device__ constexpr uint32_t k64Bm[7] = {0, 0, 512, 576, 584, 585, 586};  // words of level m
 constexpr uint32_t kU64L1 = 2 * 4688, kU64Bm = kU64L1 + 65536, kU64Pre = kU64Bm + 8 * 588, kU64Sm = kU64Pre + 1024,
                    kU64Lds = kU64Sm + 96;
+static_assert(kLutLdsCap + kWaveLds <= 65536, "tables and a decoding wave in the place of level 1");
 
 // What bounds it: latency (a chain of six levels with a few barriers and
 // dependent loads each, at the two workgroups per CU that 80 KB of LDS
@@ -233,6 +246,7 @@ constexpr uint32_t kU64L1 = 2 * 4688, kU64Bm = kU64L1 + 65536, kU64Pre = kU64Bm 
 // time).  512 bricks of the 512^3 cells volume take 82 us; with a lane per
 // parent instead of per expanded parent, the counts of level 0 scanned 64 at
 // a time and deltas read child by child it was 118 us.
+template <Symbols64 kSym>
 __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4))) void upper64_kernel(DecodeArgs a,
                                                                                                    Launch64 l) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -255,7 +269,7 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
         __syncthreads();  // LDS of the request before
         if (tid == 0) {
             head->leaf = 0;
-            *bad = (kind == kReqDecode && !h.raw) ? head->bad : 0u;
+            *bad = (kSym == Symbols64::kLaunch && kind == kReqDecode && !h.raw) ? head->bad : 0u;
             bmw[k64Bm[6]] = 1;
             bmw[k64Bm[5]] = 0;  // (8 of the word's bits are nodes)
             lv[k64Lv[6]] = 0;
@@ -279,6 +293,16 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
         }
         uint32_t ipl = 0;
         bool ok = true;
+        if constexpr (kSym != Symbols64::kLaunch) {
+            constexpr bool kLds = kSym == Symbols64::kOwnLds;
+            uint32_t *slut = reinterpret_cast<uint32_t *>(smem + kU64L1);
+            if (!h.raw) {
+                if (kLds)
+                    for (uint32_t e = tid; e < l.lut_lds_words; e += k64Threads) slut[e] = a.luts[e];
+                __syncthreads();
+                if (w == 0 && !entropy64<kLds>(a, l, h, slot, slut, smem + kU64L1 + kLutLdsCap) && L == 0) *bad = 1;
+            }
+        }
         __syncthreads();
         if (*bad) ok = false;
         // node of rank r among the expanded nodes whose bits are pb and

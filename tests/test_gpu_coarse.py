@@ -1,0 +1,93 @@
+"""GPU: requests of coarse levels of detail and small batches, where a decode
+makes fewer launches."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def volume64(seed):
+    """128^3: cells, a patch of many labels, a uniform 64^3 brick."""
+    vol = synth.cells(n=128, grid=9, seed=seed)
+    vol[:20, :20, :20] = np.random.default_rng(seed).integers(1, 1 << 30, (20, 20, 20)).astype(np.uint32)
+    vol[:64, 64:, :64] = 5
+    return vol
+
+
+def decode_lods(csv, pool, ids, lods, status=False):
+    torch = torch_cuda()
+    off, tot = csv.output_offsets(lods, 6)
+    out = torch.full((tot,), -1, dtype=torch.int32, device="cuda")
+    st = torch.zeros(ids.size, dtype=torch.int32, device="cuda") if status else None
+    pool.decode(torch.from_numpy(ids.view(np.int32)).cuda(), out, lods=torch.from_numpy(lods).cuda(),
+                out_offsets=torch.from_numpy(off.view(np.int64)).cuda(), **({"status": st} if status else {}))
+    torch.cuda.synchronize()
+    return out.cpu().numpy().view(np.uint32), off, st
+
+
+@pytest.mark.parametrize("n", [1, 512, 513, 1100])
+@pytest.mark.parametrize("lane_max,tables", [(64, 1), (2, 1), (64, 3)])
+def test_edge64_symbols_decoded_by_either_kernel(orc, n, lane_max, tables):
+    # up to two requests per CU the upper kernel decodes the symbols, beyond
+    # that a launch of its own; three volumes' tables do not fit LDS
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(31), brick_log2=6, lane_max=lane_max, scale_bits=11)
+    pool = csv.Pool()
+    for _ in range(tables):
+        pool.add_volume(blob)
+    rng = np.random.default_rng(n)
+    ids = rng.integers(0, 8 * tables, n).astype(np.uint32)
+    lods = np.where(np.arange(n) % 100 == 0, 0, rng.integers(1, 7, n)).astype(np.uint8)
+    print("[gpu-test] edge 64, %d requests, %d states, %d volumes" % (n, lane_max, tables), flush=True)
+    got, off, _ = decode_lods(csv, pool, ids, lods)
+    assert pool.last_error() == (0, 0)
+    want = {(i, t): orc.decode_brick(blob, i, t).ravel() for i in range(8) for t in range(7)}
+    for i, t, o in zip(ids, lods, off):
+        w = want[int(i) % 8, int(t)]
+        np.testing.assert_array_equal(got[int(o):int(o) + w.size], w)
+
+
+@pytest.mark.parametrize("n", [3, 700])
+@pytest.mark.parametrize("lod", [3, 4, 5])
+def test_edge64_one_coarse_level(orc, n, lod):
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blobs = [csv.encode_volume(volume64(32 + c), brick_log2=6, coding=c) for c in (0, 1)]
+    pool = csv.Pool()
+    for b in blobs:
+        pool.add_volume(b)
+    ids = torch.arange(n, dtype=torch.int32, device="cuda") % 16
+    out = torch.full((n, (64 >> lod) ** 3), -1, dtype=torch.int32, device="cuda")
+    print("[gpu-test] edge 64, %d requests of level %d" % (n, lod), flush=True)
+    pool.decode(ids, out, lod=lod)
+    torch.cuda.synchronize()
+    assert pool.last_error() == (0, 0)
+    want = np.concatenate([orc.decode_bricks(b, np.arange(8), [lod] * 8).reshape(8, -1) for b in blobs])
+    np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want[np.arange(n) % 16])
+
+
+@pytest.mark.parametrize("n", [5, 600])
+def test_edge64_malformed_states(orc, n):
+    # a changed state of brick 1: found by whichever kernel decodes the symbols
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(33), brick_log2=6)
+    rs = (128 + 8 * 9 + 15) & ~15
+    at = rs + int(np.frombuffer(blob, np.uint64, 9, 128)[1])
+    P = int(np.frombuffer(blob, np.uint32, 1, at)[0])
+    bad = bytearray(blob)
+    bad[at + 4 * (9 + P) + 1] ^= 0x5A
+    pool = csv.Pool()
+    pool.add_volume(bytes(bad))
+    ids = (np.arange(n) % 5).astype(np.uint32)
+    lods = np.where(np.arange(n) < 5, 0, 3).astype(np.uint8)
+    print("[gpu-test] edge 64, malformed state among %d requests" % n, flush=True)
+    got, off, st = decode_lods(csv, pool, ids, lods, status=True)
+    st = st.cpu().numpy()
+    assert st[1] == csv.CSV_ECORRUPT and pool.last_error()[0] == csv.CSV_ECORRUPT
+    np.testing.assert_array_equal(got[int(off[1]):int(off[2])], 0)
+    for k in (0, 2, 3, 4):
+        assert st[k] == 0
+        np.testing.assert_array_equal(got[int(off[k]):int(off[k]) + 64 ** 3], orc.decode_brick(blob, int(ids[k]), 0).ravel())
