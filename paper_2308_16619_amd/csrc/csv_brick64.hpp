@@ -1,10 +1,12 @@
 // Decoder for 64^3 bricks with palettes of fewer than k64PalMax entries,
-// rANS or raw nibbles; part of csv_decode.hip, whose helpers it uses.  A
-// decode is up to three launches:
+// rANS or raw nibbles; part of csv_decode.hip, whose helpers it uses.  The
+// launches of a decode:
 //   entropy64_kernel  (pools with rANS volumes) one wave per brick: the
 //                     symbols as packed nibbles in the request's slot (few
 //                     requests or symbols: a wave of upper64_kernel instead);
 //                     raw bricks are read where they lie in the record;
+//   front_kernel      (of csv_decode.hip; many requests of t >= 2) a wave per
+//                     brick, which is a 32^3 brick of level t - 1 then;
 //   upper64_kernel    a workgroup per brick: levels 5 .. max(t, 1) in LDS
 //                     (u16 palette indices, Morton order), one lane per
 //                     parent; t >= 1: the output.  t = 0: level 1, its
@@ -40,13 +42,24 @@ struct Head64 {
 };
 static_assert(sizeof(Head64) <= 256, "slot layout");
 
+// nibble dwords of a wave's slot for levels 5 .. 2 (585 parents at most, 16
+// symbols each), and the 16 that entropy_decode may write past them
+constexpr uint32_t k64CoarseDw = 585 * 16 / 8 + 14;
+static_assert(k64CoarseDw % 4 == 0, "levels behind it");
+static_assert(k64Info >= kWavesGen * (4 * k64CoarseDw + kSlotLv), "a request's slot holds those of a front workgroup");
+
 struct Launch64 {
     uint8_t *slots;
     uint64_t slot_bytes;
     uint32_t nib_off;        // nibbles in a slot
     uint32_t nib_dw;         // dwords they may take
     uint32_t lut_lds_words;  // decode-table words in LDS (entropy kernel; 0: read from global memory)
+    uint32_t front;          // 1: the front kernel decodes requests of levels 2 and coarser
 };
+
+__device__ __forceinline__ bool front_takes(const DecodeArgs &a, const Launch64 &l, uint32_t rq) {
+    return l.front && a.lods && ld_s_u8(a.lods + rq) >= 2;
+}
 
 struct Hdr64 {
     const uint32_t *rec;
@@ -215,6 +228,7 @@ __global__ __launch_bounds__(64 * kWavesGen) void entropy64_kernel(DecodeArgs a,
     const uint32_t wave = uniform(threadIdx.x >> 6);
     uint8_t *wl = smem + align16(4 * l.lut_lds_words) + wave * kWaveLds;
     for (uint32_t rq = blockIdx.x * kWavesGen + wave; rq < a.n; rq += gridDim.x * kWavesGen) {
+        if (front_takes(a, l, rq)) continue;
         Hdr64 g;
         uint32_t *dst, count, fill;
         const ReqKind kind = load_request64(a, rq, g, dst, count, fill);
@@ -261,11 +275,15 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
     constexpr uint32_t kMark = 65533u;
     using V = Vec8<uint16_t>;
     for (uint32_t rq = blockIdx.x; rq < a.n; rq += gridDim.x) {
+        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+        Head64 *head = reinterpret_cast<Head64 *>(slot + k64Head);
+        if (front_takes(a, l, rq)) {
+            if (tid == 0) head->leaf = 0;
+            continue;
+        }
         Hdr64 h;
         uint32_t *dst, count, fill;
         const ReqKind kind = load_request64(a, rq, h, dst, count, fill);
-        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
-        Head64 *head = reinterpret_cast<Head64 *>(slot + k64Head);
         __syncthreads();  // LDS of the request before
         if (tid == 0) {
             head->leaf = 0;
@@ -675,6 +693,11 @@ __device__ __forceinline__ uint32_t eval64(const Leaf64 &f, uint32_t q, uint32_t
     }
 }
 
+// kRuns: workgroups' blocks that one workgroup takes in turn.  With levels by
+// request most workgroups may find nothing to do, and their start is bound by
+// the rate at which they are handed out (12 us for those of 1,024 requests);
+// with one level each block's own workgroup balances better.
+template <uint32_t kRuns>
 __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_eu(7))) void leaf64_kernel(DecodeArgs a,
                                                                                                            Launch64 l) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -686,7 +709,7 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     uint8_t *list = wl + kV64List;
     uint32_t *delta = reinterpret_cast<uint32_t *>(wl + kV64Delta);
     uint16_t *refs = reinterpret_cast<uint16_t *>(wl + kV64Ref);
-    constexpr uint32_t kMark = 65533u, kGroups = k64Blocks / k64LeafWaves;  // workgroups per brick
+    constexpr uint32_t kMark = 65533u, kGroups = k64Blocks / k64LeafWaves / kRuns;  // workgroups per brick
     // workgroups go to the 8 XCDs in turn: those of a brick on the XCD of its
     // upper workgroup, whose L2 holds the slot
     const uint32_t g = blockIdx.x >> 3, rq = (g / kGroups) * 8 + (blockIdx.x & 7u);
@@ -696,7 +719,7 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     if (!ld_s(&head->leaf)) return;
     const uint32_t P = ld_s(&head->P);
     const uint32_t *pal = rec_at(ld_s(&head->pal));
-    uint32_t *dst = reinterpret_cast<uint32_t *>(ld_s(&head->dst));
+    uint32_t *const brick = reinterpret_cast<uint32_t *>(ld_s(&head->dst));
     Leaf64 f;
     f.l1 = reinterpret_cast<const uint16_t *>(slot);
     f.bits = reinterpret_cast<const uint64_t *>(slot + k64Bits);
@@ -709,123 +732,125 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     const bool plds = P <= k64PalLds;
     if (plds)
         for (uint32_t e = threadIdx.x; e < P; e += 64 * k64LeafWaves) spal[e] = pal[e];
-    // the block's first parent, and its Morton index
-    const uint32_t blk = (g % kGroups) * k64LeafWaves + w;
-    const uint32_t PX = 16 * (blk & 1u), PY = 4 * ((blk >> 1) & 7u), PZ = 4 * (blk >> 4);
-    const uint32_t Q0 = spread5(PX) | (spread5(PY) << 1) | (spread5(PZ) << 2);
-    const uint32_t lx = coord2(L), ly = coord2(L >> 1), lz = coord2(L >> 2);
-    // every voxel its parent's value; the expanded parents listed
-    uint32_t E = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < k64Words; j++) {
-        const uint32_t q0 = Q0 + 64 * (j & 1u) + 512 * (j >> 1), word = q0 >> 6;
-        const uint64_t b = ld_s(f.bits + word);
-        const uint32_t pv = f.l1[q0 + L] * 0x00010001u;
-        const uint32_t d = v64_dw(8 * j + 2 * lx, 2 * ly, 2 * lz);  // (the rows y and y + 1 share it)
-        D32[d] = pv;
-        D32[d + 16] = pv;
-        D32[d + kV64Plane] = pv;
-        D32[d + kV64Plane + 16] = pv;
-        if ((b >> L) & 1u) list[E + mbcnt(b)] = (uint8_t)(64 * j + L);
-        if (L == 0) delta[j] = ld_s_u16(f.pre + word) - E;
-        E += (uint32_t)__popcll(b);
-    }
-    __syncthreads();  // the palette, for every wave
-    // the children of the expanded parents; those that refer to a same-level
-    // node are listed
-    struct Ops {
-        uint32_t idx, wd, in, pv, nb[3];
-    };
-    // what a lane needs of the expanded parent at place 64 c + L, loaded
-    // while the chunk before is replayed
-    auto load = [&](uint32_t c) -> Ops {
-        Ops o;
-        const uint32_t pos = min(64 * c + L, E - 1);
-        o.idx = list[pos];
-        const uint32_t j = o.idx >> 6, q = Q0 + (o.idx & 63u) + 64 * (j & 1u) + 512 * (j >> 1), r = pos + delta[j];
-        o.wd = nib8(f.nib, f.ops0 + 8 * r);
-        o.in = f.info[r];
-        o.pv = f.l1[q];
-#pragma unroll
-        for (int x = 0; x < 3; x++) o.nb[x] = f.l1[morton_inc(q, 0x1249u << x)];  // (on a high face: any value)
-        return o;
-    };
-    uint32_t nref = 0;
-    const uint32_t chunks = (E + 63) / 64;
-    Ops next{};
-    if (chunks) next = load(0);
-    for (uint32_t c = 0; c < chunks; c++) {
-        const Ops o = next;
-        if (c + 1 < chunks) next = load(c + 1);
-        uint32_t open = 0, v0 = 0;
-        if (64 * c + L < E) {
-            const uint32_t j = o.idx >> 6, i = o.idx & 63u;
-            const uint32_t bx = 4 * j + coord2(i), by = coord2(i >> 1), bz = coord2(i >> 2);
-            const uint32_t y = o.wd & 0x77777777u;
-            const uint32_t pam = zero_nibbles(y ^ 0x66666666u), pdm = zero_nibbles(y ^ 0x55555555u);
-            const uint32_t dl = pdm ? nib8(f.nib, f.seg + (o.in >> 14)) : 0u;
-            const uint4 v = replay_children_u16(o.wd, o.pv, o.nb, f.ipl + (o.in & (k64PalMax - 1u)), pam, pdm, dl);
-            const uint32_t d = v64_dw(2 * bx, 2 * by, 2 * bz);
-            D32[d] = v.x;
-            D32[d + 16] = v.y;
-            D32[d + kV64Plane] = v.z;
-            D32[d + kV64Plane + 16] = v.w;
-            open = ref_children(o.wd, 7u);
-            v0 = 2 * bx + 64 * by + 512 * bz;  // x + 32 y + 256 z
+    for (uint32_t run = 0; run < kRuns; run++) {
+        // the block's first parent, and its Morton index
+        const uint32_t blk = ((g % kGroups) * kRuns + run) * k64LeafWaves + w;
+        const uint32_t PX = 16 * (blk & 1u), PY = 4 * ((blk >> 1) & 7u), PZ = 4 * (blk >> 4);
+        const uint32_t Q0 = spread5(PX) | (spread5(PY) << 1) | (spread5(PZ) << 2);
+        const uint32_t lx = coord2(L), ly = coord2(L >> 1), lz = coord2(L >> 2);
+        // every voxel its parent's value; the expanded parents listed
+        uint32_t E = 0;
+    #pragma unroll
+        for (uint32_t j = 0; j < k64Words; j++) {
+            const uint32_t q0 = Q0 + 64 * (j & 1u) + 512 * (j >> 1), word = q0 >> 6;
+            const uint64_t b = ld_s(f.bits + word);
+            const uint32_t pv = f.l1[q0 + L] * 0x00010001u;
+            const uint32_t d = v64_dw(8 * j + 2 * lx, 2 * ly, 2 * lz);  // (the rows y and y + 1 share it)
+            D32[d] = pv;
+            D32[d + 16] = pv;
+            D32[d + kV64Plane] = pv;
+            D32[d + kV64Plane + 16] = pv;
+            if ((b >> L) & 1u) list[E + mbcnt(b)] = (uint8_t)(64 * j + L);
+            if (L == 0) delta[j] = ld_s_u16(f.pre + word) - E;
+            E += (uint32_t)__popcll(b);
         }
-        for (uint64_t m; (m = __ballot(open != 0)) != 0;) {
-            const uint32_t k = (uint32_t)__builtin_ctz(open) >> 2, to = nref + mbcnt(m);
-            if (open && to < kV64RefCap) refs[to] = (uint16_t)(v0 + (k & 1u) + 16 * (k & 2u) + 64 * (k & 4u));
-            open &= open - 1u;
-            nref += (uint32_t)__popcll(m);
-        }
-    }
-    wsync();
-    // a voxel's value: references followed inside the block, and out of it on
-    // the other block's operations (concurrent chases see a reference or its
-    // value, both of which lead to the value)
-    auto at = [&](uint32_t x, uint32_t y, uint32_t z) -> uint32_t { return 2 * v64_dw(x, y, z) + (x & 1u); };
-    auto chase = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t v) -> uint32_t {
-        while (v >= kMark) {
-            const uint32_t ax = v - kMark, c = ax == 0 ? x : ax == 1 ? y : z;
-            if (c == 0) {
-                const uint32_t q = spread5(PX + (x >> 1)) | (spread5(PY + (y >> 1)) << 1) | (spread5(PZ + (z >> 1)) << 2);
-                return eval64(f, morton_dec(q, 0x1249u << ax), (x & 1u) | ((y & 1u) << 1) | ((z & 1u) << 2) | (1u << ax));
+        __syncthreads();  // the palette, for every wave
+        // the children of the expanded parents; those that refer to a same-level
+        // node are listed
+        struct Ops {
+            uint32_t idx, wd, in, pv, nb[3];
+        };
+        // what a lane needs of the expanded parent at place 64 c + L, loaded
+        // while the chunk before is replayed
+        auto load = [&](uint32_t c) -> Ops {
+            Ops o;
+            const uint32_t pos = min(64 * c + L, E - 1);
+            o.idx = list[pos];
+            const uint32_t j = o.idx >> 6, q = Q0 + (o.idx & 63u) + 64 * (j & 1u) + 512 * (j >> 1), r = pos + delta[j];
+            o.wd = nib8(f.nib, f.ops0 + 8 * r);
+            o.in = f.info[r];
+            o.pv = f.l1[q];
+    #pragma unroll
+            for (int x = 0; x < 3; x++) o.nb[x] = f.l1[morton_inc(q, 0x1249u << x)];  // (on a high face: any value)
+            return o;
+        };
+        uint32_t nref = 0;
+        const uint32_t chunks = (E + 63) / 64;
+        Ops next{};
+        if (chunks) next = load(0);
+        for (uint32_t c = 0; c < chunks; c++) {
+            const Ops o = next;
+            if (c + 1 < chunks) next = load(c + 1);
+            uint32_t open = 0, v0 = 0;
+            if (64 * c + L < E) {
+                const uint32_t j = o.idx >> 6, i = o.idx & 63u;
+                const uint32_t bx = 4 * j + coord2(i), by = coord2(i >> 1), bz = coord2(i >> 2);
+                const uint32_t y = o.wd & 0x77777777u;
+                const uint32_t pam = zero_nibbles(y ^ 0x66666666u), pdm = zero_nibbles(y ^ 0x55555555u);
+                const uint32_t dl = pdm ? nib8(f.nib, f.seg + (o.in >> 14)) : 0u;
+                const uint4 v = replay_children_u16(o.wd, o.pv, o.nb, f.ipl + (o.in & (k64PalMax - 1u)), pam, pdm, dl);
+                const uint32_t d = v64_dw(2 * bx, 2 * by, 2 * bz);
+                D32[d] = v.x;
+                D32[d + 16] = v.y;
+                D32[d + kV64Plane] = v.z;
+                D32[d + kV64Plane + 16] = v.w;
+                open = ref_children(o.wd, 7u);
+                v0 = 2 * bx + 64 * by + 512 * bz;  // x + 32 y + 256 z
             }
-            x -= ax == 0 ? 1u : 0u;
-            y -= ax == 1 ? 1u : 0u;
-            z -= ax == 2 ? 1u : 0u;
-            v = D[at(x, y, z)];
-        }
-        return v;
-    };
-    const bool listed = nref <= kV64RefCap;
-    for (uint32_t e = L; listed && e < nref; e += 64) {
-        const uint32_t v = refs[e], x = v & 31u, y = (v >> 5) & 7u, z = v >> 8, p = at(x, y, z);
-        D[p] = (uint16_t)chase(x, y, z, D[p]);
-    }
-    wsync();
-    // the block through the palette: 8 rows of 32 voxels per store
-    const uint32_t x = 4 * (L & 7u), y = L >> 3;
-    dst += 2 * PX + 128 * PY + 8192 * PZ + x + 64 * y;
-    auto rows = [&](auto al16, auto p, auto refs_left) {
-#pragma unroll 2
-        for (uint32_t z = 0; z < 8; z++) {
-            uint2 v = *reinterpret_cast<const uint2 *>(D32 + v64_dw(x, y, z));
-            if constexpr (decltype(refs_left)::value) {  // more references than the list holds
-                v.x = chase(x, y, z, v.x & 0xFFFFu) | (chase(x + 1, y, z, v.x >> 16) << 16);
-                v.y = chase(x + 2, y, z, v.y & 0xFFFFu) | (chase(x + 3, y, z, v.y >> 16) << 16);
+            for (uint64_t m; (m = __ballot(open != 0)) != 0;) {
+                const uint32_t k = (uint32_t)__builtin_ctz(open) >> 2, to = nref + mbcnt(m);
+                if (open && to < kV64RefCap) refs[to] = (uint16_t)(v0 + (k & 1u) + 16 * (k & 2u) + 64 * (k & 4u));
+                open &= open - 1u;
+                nref += (uint32_t)__popcll(m);
             }
-            store4<decltype(al16)::value>(dst + 4096 * z, make_uint4(p(half_x4<0>(v.x)), p(half_x4<1>(v.x)),
-                                                                     p(half_x4<0>(v.y)), p(half_x4<1>(v.y))));
         }
-    };
-    const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
-    const uint8_t *sp = smem, *gp = reinterpret_cast<const uint8_t *>(pal);
-    auto in_lds = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(sp + o); };
-    auto in_mem = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(gp + o); };
-    if (plds && al && listed) rows(std::true_type{}, in_lds, std::false_type{});
-    else if (al && listed) rows(std::true_type{}, in_mem, std::false_type{});
-    else if (al) rows(std::true_type{}, in_mem, std::true_type{});
-    else rows(std::false_type{}, in_mem, std::true_type{});
+        wsync();
+        // a voxel's value: references followed inside the block, and out of it on
+        // the other block's operations (concurrent chases see a reference or its
+        // value, both of which lead to the value)
+        auto at = [&](uint32_t x, uint32_t y, uint32_t z) -> uint32_t { return 2 * v64_dw(x, y, z) + (x & 1u); };
+        auto chase = [&](uint32_t x, uint32_t y, uint32_t z, uint32_t v) -> uint32_t {
+            while (v >= kMark) {
+                const uint32_t ax = v - kMark, c = ax == 0 ? x : ax == 1 ? y : z;
+                if (c == 0) {
+                    const uint32_t q = spread5(PX + (x >> 1)) | (spread5(PY + (y >> 1)) << 1) | (spread5(PZ + (z >> 1)) << 2);
+                    return eval64(f, morton_dec(q, 0x1249u << ax), (x & 1u) | ((y & 1u) << 1) | ((z & 1u) << 2) | (1u << ax));
+                }
+                x -= ax == 0 ? 1u : 0u;
+                y -= ax == 1 ? 1u : 0u;
+                z -= ax == 2 ? 1u : 0u;
+                v = D[at(x, y, z)];
+            }
+            return v;
+        };
+        const bool listed = nref <= kV64RefCap;
+        for (uint32_t e = L; listed && e < nref; e += 64) {
+            const uint32_t v = refs[e], x = v & 31u, y = (v >> 5) & 7u, z = v >> 8, p = at(x, y, z);
+            D[p] = (uint16_t)chase(x, y, z, D[p]);
+        }
+        wsync();
+        // the block through the palette: 8 rows of 32 voxels per store
+        const uint32_t x = 4 * (L & 7u), y = L >> 3;
+        uint32_t *dst = brick + 2 * PX + 128 * PY + 8192 * PZ + x + 64 * y;
+        auto rows = [&](auto al16, auto p, auto refs_left) {
+    #pragma unroll 2
+            for (uint32_t z = 0; z < 8; z++) {
+                uint2 v = *reinterpret_cast<const uint2 *>(D32 + v64_dw(x, y, z));
+                if constexpr (decltype(refs_left)::value) {  // more references than the list holds
+                    v.x = chase(x, y, z, v.x & 0xFFFFu) | (chase(x + 1, y, z, v.x >> 16) << 16);
+                    v.y = chase(x + 2, y, z, v.y & 0xFFFFu) | (chase(x + 3, y, z, v.y >> 16) << 16);
+                }
+                store4<decltype(al16)::value>(dst + 4096 * z, make_uint4(p(half_x4<0>(v.x)), p(half_x4<1>(v.x)),
+                                                                         p(half_x4<0>(v.y)), p(half_x4<1>(v.y))));
+            }
+        };
+        const bool al = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+        const uint8_t *sp = smem, *gp = reinterpret_cast<const uint8_t *>(pal);
+        auto in_lds = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(sp + o); };
+        auto in_mem = [&](uint32_t o) -> uint32_t { return *reinterpret_cast<const uint32_t *>(gp + o); };
+        if (plds && al && listed) rows(std::true_type{}, in_lds, std::false_type{});
+        else if (al && listed) rows(std::true_type{}, in_mem, std::false_type{});
+        else if (al) rows(std::true_type{}, in_mem, std::true_type{});
+        else rows(std::false_type{}, in_mem, std::true_type{});
+    }
 }

@@ -323,8 +323,9 @@ enum ReqKind { kReqBadLod, kReqBadId, kReqCorrupt, kReqFill, kReqDecode };
 
 // A brick of edge 32 >> SH has the levels SH .. 5 of a 32^3 brick: its level
 // t is level t + SH here, in Hdr::t, in Hdr::c() and in every function of
-// the replay, and its finest level is level SH.  (SH = -1, edge 64: the
-// entropy decode only, with c0 the symbols before the finest segment.)
+// the replay, and its finest level is level SH.  (SH = -1, edge 64: levels
+// 2..6 of the brick as levels 1..5, with c0 the symbols before its finest
+// segment; the finer levels take the kernels of csv_brick64.hpp.)
 template <int SH>
 constexpr uint32_t header_words() { return csv::record_header_words(kLog2 - SH); }
 
@@ -360,7 +361,8 @@ __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq
     h.W = ld_s(h.rec + 1);
     h.nw = ld_s(h.rec + 2);
     // the counts of levels finer than the brick's finest one (SH) are that one's
-    h.c0 = ld_s(h.rec + 3);
+    const uint32_t every = ld_s(h.rec + 3);
+    h.c0 = SH < 0 ? ld_s(h.rec + 4) : every;
     h.c1 = h.c2 = h.c3 = h.c4 = h.c0;
     if constexpr (SH < 1) h.c1 = ld_s(h.rec + 4 - SH);
     if constexpr (SH < 2) h.c2 = ld_s(h.rec + 5 - SH);
@@ -377,14 +379,14 @@ __device__ __forceinline__ ReqKind load_request(const DecodeArgs &a, uint32_t rq
     }
     const uint32_t hdr = header_words<SH>();
     // the record holds its words up to pdw dwords (the rest is staged)
-    bool ok = h.P >= 1 && h.W <= 64 && (h.W & (h.W - 1)) == 0 && ((h.c0 > 0) == (h.W > 0) || (kGen && h.raw)) &&
-              h.c0 <= kMaxSym &&
+    bool ok = h.P >= 1 && h.W <= 64 && (h.W & (h.W - 1)) == 0 && ((every > 0) == (h.W > 0) || (kGen && h.raw)) &&
+              (SH < 0 || every <= kMaxSym) &&
               4ull * ((uint64_t)hdr + h.P + h.W) + std::min<uint64_t>(2ull * h.nw, 4ull * h.pdw) <= size;
-    if constexpr (kGen) ok = ok && (!h.raw || (h.W == 0 && h.nw == (h.c0 + 3) / 4));
-    ok = ok && h.c0 >= h.c1 && h.c1 >= h.c2 && h.c2 >= h.c3 && h.c3 >= h.c4;
-    if (ok) ok = (h.c0 == 0) ? (h.P == 1) : (h.P >= 2);
+    if constexpr (kGen) ok = ok && (!h.raw || (h.W == 0 && h.nw == (every + 3) / 4));
+    ok = ok && every >= h.c0 && h.c0 >= h.c1 && h.c1 >= h.c2 && h.c2 >= h.c3 && h.c3 >= h.c4;
+    if (ok) ok = (every == 0) ? (h.P == 1) : (h.P >= 2);
     if (!ok) return kReqCorrupt;
-    if (h.t == (uint32_t)kLog2 || h.c0 == 0) {  // coarsest level or uniform brick: palette[0]
+    if (h.t == (uint32_t)kLog2 || every == 0) {  // coarsest level or uniform brick: palette[0]
         fill = ld_s(h.rec + hdr);
         return kReqFill;
     }
@@ -1306,7 +1308,7 @@ __device__ __forceinline__ bool front_replay(const Hdr &h, const LaunchA &l, con
     uint16_t *lst = reinterpret_cast<uint16_t *>(wl + kWLst);
     uint32_t E1 = 0, ipl = 0;
     if (!upper_replay<IdxT, kG, SH>(h, nib, lv, bm, lst, reinterpret_cast<uint32_t *>(wl + kWPal), E1, ipl)) return false;
-    if (SH > 0 || h.t >= 1) {
+    if (SH != 0 || h.t >= 1) {
         const uint32_t *pal = h.rec + hdr;
         if (!kG) {  // stage the palette next to the levels
             uint32_t *sp = reinterpret_cast<uint32_t *>(wl + kWPal);
@@ -1398,6 +1400,8 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         if (req >= n_req) break;
         const uint32_t rq = l.order ? ld_s(l.order + req) : req;
         phase_mark(rq, 0);
+        // (full-LOD and level-1 requests of 64^3 bricks: not here)
+        if (SH < 0 && a.lods && ld_s_u8(a.lods + rq) < 2) continue;
         Hdr h;
         uint32_t *dst, count, fill;
         const ReqKind kind = load_request<SH, kGen>(a, rq, h, dst, count, fill);
@@ -1417,7 +1421,7 @@ __global__ __launch_bounds__(WPG * 64) __attribute__((amdgpu_waves_per_eu(4))) v
         }
         if (h.up && L == 0) fail(a, rq, CSV_EDETAIL, h.id);
         const uint32_t n = h.c(h.t);
-        uint8_t *slot = glob(l.slots) + (size_t)(SH > 0 ? wid : rq) * l.slot_bytes;
+        uint8_t *slot = glob(l.slots) + (size_t)(SH != 0 ? wid : rq) * l.slot_bytes;
         uint32_t *nib = reinterpret_cast<uint32_t *>(slot);
         if (n + 16 > 8 * l.slot_dw) {  // the slots are sized for the pool's largest brick
             if (L == 0) fail(a, rq, CSV_EINVAL, h.id);
@@ -2792,24 +2796,44 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
             (void)set_lds_attr(upper64_kernel<Symbols64::kLaunch>);
             (void)set_lds_attr(upper64_kernel<Symbols64::kOwnLds>);
             (void)set_lds_attr(upper64_kernel<Symbols64::kOwnGlobal>);
-            (void)set_lds_attr(leaf64_kernel);
+            (void)set_lds_attr(leaf64_kernel<1>);
+            (void)set_lds_attr(leaf64_kernel<4>);
         });
         // slots for 4 requests per CU at most (0.2 to 0.5 MB each)
         const uint32_t per = plain ? 1u : std::min(n, 4u * cu);
-        const int rc = generic_bufs(pool, s, l.slot_bytes * per, &G);
+        LaunchA la{};
+        la.lut_lds_words = !lods && lod_scalar >= 5 ? 0u : lut_lds_words(pool);
+        la.slot_dw = k64CoarseDw;
+        la.slot_bytes = 4 * k64CoarseDw + kSlotLv;
+        const uint32_t lds_a = align16(4 * la.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
+        const uint32_t waves = cu * std::max(1u, kLdsBytes / lds_a) * kWavesGen;
+        const int rc = generic_bufs(pool, s, std::max(l.slot_bytes * per, (uint64_t)la.slot_bytes * std::min(per, waves)), &G);
         if (rc) return rc;
-        l.slots = G->gen;
+        l.slots = la.slots = G->gen;
         const uint64_t g = 64u >> (lods ? 0u : lod_scalar), cnt = lods ? 0 : g * g * g;
+        auto args = [&](uint32_t at, uint32_t m) {
+            return decode_args(pool, ids + at, lods ? lods + at : nullptr, lod_scalar, out_off ? out_off + at : nullptr, m,
+                               out_off ? out : out + at * cnt, req_err ? req_err + at : nullptr, rq_base + at);
+        };
+        // Requests of levels 2 and coarser take the front kernel where there
+        // are more of them than upper workgroups fit at once: 16 of its waves
+        // on a CU work on a brick each, of theirs 8.  5,000 requests of level
+        // 3: 35 us, 175 by workgroups; 256: 22 us, 18 by workgroups.
+        const bool front = n > 2 * cu && (lods || lod_scalar >= 2);
+        if (front) {
+            const uint32_t most = (uint32_t)std::min<uint64_t>(waves, G->gen_bytes / la.slot_bytes) / kWavesGen;
+            for (uint32_t at = 0, m = plain ? 1u : n; at < n; at += m)
+                launch_gen<-1>(args(at, m), la, std::max(1u, std::min(most, (m + kWavesGen - 1) / kWavesGen)), lds_a, s);
+            if (!lods) return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
+        }
+        l.front = front ? 1u : 0u;
         for (uint32_t at = 0; at < n; at += per) {
             const uint32_t m = std::min(per, n - at);
-            const DecodeArgs a = decode_args(pool, ids + at, lods ? lods + at : nullptr, lod_scalar,
-                                             out_off ? out_off + at : nullptr, m, out_off ? out : out + at * cnt,
-                                             req_err ? req_err + at : nullptr, rq_base + at);
-            // Few requests (a workgroup each) or few symbols (levels 4 and 5):
-            // the upper kernel decodes them itself.  One launch less: 16
-            // requests of level 5 take 9 us, 300 take 10.3 (12.7 and 14.5
-            // with the launch).
-            const bool coarse = !lods && lod_scalar >= 4, own = rans && (m <= 2 * cu || coarse);
+            const DecodeArgs a = args(at, m);
+            // Few requests (a workgroup each): the upper kernel decodes their
+            // symbols itself.  One launch less: 16 requests of level 5 take 9
+            // us, 300 take 10.3 (12.7 and 14.5 with the launch).
+            const bool own = rans && m <= 2 * cu;
             if (rans && !own) {
                 const uint32_t ge = (m + kWavesGen - 1) / kWavesGen;
                 if (l.lut_lds_words)
@@ -2820,12 +2844,16 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
             const dim3 gu(std::min(m, 2 * cu)), tu(k64Threads);
             if (!own)
                 hipLaunchKernelGGL(upper64_kernel<Symbols64::kLaunch>, gu, tu, kU64Lds, s, a, l);
-            else if (l.lut_lds_words && !coarse)
+            else if (l.lut_lds_words)
                 hipLaunchKernelGGL(upper64_kernel<Symbols64::kOwnLds>, gu, tu, kU64Lds, s, a, l);
             else
                 hipLaunchKernelGGL(upper64_kernel<Symbols64::kOwnGlobal>, gu, tu, kU64Lds, s, a, l);
-            if (lods || lod_scalar == 0)
-                hipLaunchKernelGGL(leaf64_kernel, dim3(((m + 7) / 8) * 8 * (k64Blocks / k64LeafWaves)), dim3(64 * k64LeafWaves), lds_l, s, a, l);
+            // levels by request: most may have nothing for the leaf kernel
+            const uint32_t bricks = ((m + 7) / 8) * 8, groups = k64Blocks / k64LeafWaves;
+            if (lods && m > cu / 2)
+                hipLaunchKernelGGL(leaf64_kernel<4>, dim3(bricks * groups / 4), dim3(64 * k64LeafWaves), lds_l, s, a, l);
+            else if (lods || lod_scalar == 0)
+                hipLaunchKernelGGL(leaf64_kernel<1>, dim3(bricks * groups), dim3(64 * k64LeafWaves), lds_l, s, a, l);
         }
         return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
     }

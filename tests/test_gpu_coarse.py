@@ -51,11 +51,13 @@ def test_edge64_symbols_decoded_by_either_kernel(orc, n, lane_max, tables):
 
 
 @pytest.mark.parametrize("n", [3, 700])
-@pytest.mark.parametrize("lod", [3, 4, 5])
-def test_edge64_one_coarse_level(orc, n, lod):
+@pytest.mark.parametrize("labels", [100, 1 << 31])
+@pytest.mark.parametrize("lod", [2, 3, 4, 5])
+def test_edge64_one_coarse_level(orc, n, lod, labels):
+    # by workgroups, and, many of them, by the front kernel (u8 or u16 indices)
     torch = torch_cuda()
     import paper_2308_16619_amd as csv
-    blobs = [csv.encode_volume(volume64(32 + c), brick_log2=6, coding=c) for c in (0, 1)]
+    blobs = [csv.encode_volume(volume64(32 + c) % labels, brick_log2=6, coding=c) for c in (0, 1)]
     pool = csv.Pool()
     for b in blobs:
         pool.add_volume(b)
@@ -91,3 +93,37 @@ def test_edge64_malformed_states(orc, n):
     for k in (0, 2, 3, 4):
         assert st[k] == 0
         np.testing.assert_array_equal(got[int(off[k]):int(off[k]) + 64 ** 3], orc.decode_brick(blob, int(ids[k]), 0).ravel())
+
+
+@pytest.mark.parametrize("plain", [False, True])
+def test_edge64_requests_out_of_range_among_many(orc, plain):
+    # each is found once, by the kernel that serves its level
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(36), brick_log2=6)
+    pool = csv.Pool()
+    pool.add_volume(blob)
+    n = 600
+    rng = np.random.default_rng(36)
+    ids = rng.integers(0, 8, n).astype(np.uint32)
+    lods = rng.integers(1, 7, n).astype(np.uint8)
+    ids[[200, 300]] = [8, 1 << 31]
+    lods[[200, 300]] = [1, 4]
+    off, tot = csv.output_offsets(lods, 6)
+    lods[[100, 599]] = [7, 255]
+    out = torch.full((tot,), -1, dtype=torch.int32, device="cuda")
+    st = torch.zeros(n, dtype=torch.int32, device="cuda")
+    print("[gpu-test] edge 64, requests out of range, plain %s" % plain, flush=True)
+    d = [torch.from_numpy(ids.view(np.int32)).cuda(), out]
+    kw = {"lods": torch.from_numpy(lods).cuda(), "out_offsets": torch.from_numpy(off.view(np.int64)).cuda()}
+    pool.decode(*d, **kw, **({"plain": True} if plain else {"status": st}))
+    torch.cuda.synchronize()
+    code, who = pool.last_error()
+    assert code == csv.CSV_ERANGE and who in (100, 200, 300, 599)
+    bad = np.isin(np.arange(n), (100, 200, 300, 599))
+    if not plain:
+        np.testing.assert_array_equal(st.cpu().numpy(), np.where(bad, csv.CSV_ERANGE, 0))
+    got = out.cpu().numpy().view(np.uint32)
+    for i in np.nonzero(~bad)[0]:
+        w = orc.decode_brick(blob, int(ids[i]), int(lods[i])).ravel()
+        np.testing.assert_array_equal(got[int(off[i]):int(off[i]) + w.size], w)
