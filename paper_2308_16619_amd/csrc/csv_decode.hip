@@ -2540,6 +2540,14 @@ uint32_t lut_lds_words(const csv_pool *p) {
     const uint32_t lw = (uint32_t)p->luts.size();
     return (4 * lw <= kLutLdsCap) ? lw : 0u;
 }
+// ... of pools with other brick edges or raw nibbles: none where no volume has
+// rANS symbols, and few: for requests of at most 16 symbols (the copy of 8 KB
+// takes 1.5 us at the start of a workgroup)
+uint32_t gen_lut_words(const csv_pool *p, bool few) {
+    for (uint8_t raw : p->vol_raw)
+        if (!raw && !few) return lut_lds_words(p);
+    return 0u;
+}
 // nibble dwords per request: a multiple of 4, so every request's nibbles start 16-byte aligned
 uint32_t slot_dw(const csv_pool *p) { return ((p->max_c0 + 7) / 8 + 8 + 3) & ~3u; }
 constexpr uint32_t kSmallB = (sizeof(SmallB) + 15u) & ~15u;
@@ -2747,11 +2755,13 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
     if (pool->brick_log2 < (uint32_t)kLog2) {
         const uint32_t sh = (uint32_t)kLog2 - pool->brick_log2;
         LaunchA la{};
-        la.lut_lds_words = lut_lds_words(pool);
+        la.lut_lds_words = gen_lut_words(pool, !lods && lod_scalar + sh >= 4);
         la.slot_dw = slot_dw(pool);
         la.slot_bytes = (4 * la.slot_dw + 2 * (4680u - kLvOffH[sh]) + 15u) & ~15u;
         const uint32_t lds = align16(4 * la.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
-        const uint32_t most = cu * std::max(1u, kLdsBytes / lds);
+        // (as many workgroups as fit with the tables, whether or not they are
+        // copied: the scratch that a stream has serves every level)
+        const uint32_t most = cu * std::max(1u, kLdsBytes / (align16(4 * lut_lds_words(pool)) + (uint32_t)kWavesGen * kWaveLds));
         // from half of the waves that fit on, scratch for all of them, so
         // that it does not grow with larger batches
         const uint32_t grid = plain ? 1u : std::min(most, (n + kWavesGen - 1) / kWavesGen);
@@ -2802,11 +2812,12 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
         // slots for 4 requests per CU at most (0.2 to 0.5 MB each)
         const uint32_t per = plain ? 1u : std::min(n, 4u * cu);
         LaunchA la{};
-        la.lut_lds_words = !lods && lod_scalar >= 5 ? 0u : lut_lds_words(pool);
+        la.lut_lds_words = gen_lut_words(pool, !lods && lod_scalar >= 5);
         la.slot_dw = k64CoarseDw;
         la.slot_bytes = 4 * k64CoarseDw + kSlotLv;
         const uint32_t lds_a = align16(4 * la.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
-        const uint32_t waves = cu * std::max(1u, kLdsBytes / lds_a) * kWavesGen;
+        // (16 waves per CU at most, by registers)
+        const uint32_t waves = cu * std::max(1u, std::min(kLdsBytes / lds_a, 16u / kWavesGen)) * kWavesGen;
         const int rc = generic_bufs(pool, s, std::max(l.slot_bytes * per, (uint64_t)la.slot_bytes * std::min(per, waves)), &G);
         if (rc) return rc;
         l.slots = la.slots = G->gen;
@@ -2989,7 +3000,7 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
         B->dirty = false;
     }
     LaunchA la;
-    la.lut_lds_words = lut_lds_words(pool);
+    la.lut_lds_words = gen ? gen_lut_words(pool, !lods && lod_scalar >= 4) : lut_lds_words(pool);
     la.queue = queue ? ctr : nullptr;
     la.order = nullptr;
     la.slots = B->slots;
@@ -3025,7 +3036,7 @@ int launch_one(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint32_
     const uint32_t per_wg = waves_a == 2 ? 1u : (uint32_t)waves_a;
     const uint32_t lds_a = align16(4 * la.lut_lds_words) +
                            (waves_a == 2 ? kPairDecLds + kWaveLds : (uint32_t)waves_a * kWaveLds);
-    const uint32_t fit_a = std::max(1u, std::min(kLdsBytes / lds_a, 32u / (uint32_t)waves_a));
+    const uint32_t fit_a = std::max(1u, std::min(kLdsBytes / lds_a, (gen ? 16u : 32u) / (uint32_t)waves_a));
     const uint32_t grid_a = std::max(1u, std::min(cu * fit_a, (n + per_wg - 1) / per_wg));
     const uint32_t bricks_a = grid_a * per_wg;
     const uint32_t grid_b = std::min(cu * groups_b, n);
