@@ -1,10 +1,10 @@
 """GPU: requests of coarse levels of detail and small batches, where a decode
-makes fewer launches."""
+makes fewer launches or its later kernels find nothing to do."""
 import numpy as np
 import pytest
 
 import synth
-from gpu_util import torch_cuda
+from gpu_util import gpu_decode, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -127,3 +127,25 @@ def test_edge64_requests_out_of_range_among_many(orc, plain):
     for i in np.nonzero(~bad)[0]:
         w = orc.decode_brick(blob, int(ids[i]), int(lods[i])).ravel()
         np.testing.assert_array_equal(got[int(off[i]):int(off[i]) + w.size], w)
+
+
+@pytest.mark.parametrize("coding", [0, 1])
+@pytest.mark.parametrize("shape", [(2, 3, 0), (8, 3, 0), (8, 3, 1)])
+def test_no_request_for_the_leaf_kernels_and_then_some(orc, coding, shape):
+    # coarse levels by request leave the counters as full-LOD requests need them
+    import paper_2308_16619_amd as csv
+    vol = synth.cells(n=96, grid=9, seed=34)
+    vol[:32, :32, :32] = np.random.default_rng(34).integers(1, 3000, (32, 32, 32)).astype(np.uint32)
+    blob = csv.encode_volume(vol, coding=coding)
+    pool = csv.Pool()
+    pool.add_volume(blob)
+    if coding == 0:
+        pool.set_shape(shape)
+    rng = np.random.default_rng(35)
+    for k, levels in enumerate([(1, 2, 3, 4, 5), (0,), (5,), (4, 5), (0, 1, 2), (3,), (0,)]):
+        n = 200 + k
+        ids = rng.integers(0, 27, n).astype(np.uint32)
+        lods = rng.choice(levels, n).astype(np.uint8)
+        print("[gpu-test] coding %d, shape %s, levels %s" % (coding, shape, levels), flush=True)
+        got, _ = gpu_decode(pool, ids, lods)
+        np.testing.assert_array_equal(got, orc.decode_bricks(blob, ids, lods))
