@@ -256,7 +256,7 @@ static_assert(kLutLdsCap + kWaveLds <= 65536, "tables and a decoding wave in the
 
 // What bounds it: latency (a chain of six levels with a few barriers and
 // dependent loads each, at the two workgroups per CU that 80 KB of LDS
-// allow) and vector issue (6.6 k wave-instructions per wave, half of the
+// allow) and vector issue (6.6 k wave-instructions per wave, 60 % of the
 // time).  512 bricks of the 512^3 cells volume take 82 us; with a lane per
 // parent instead of per expanded parent, the counts of level 0 scanned 64 at
 // a time and deltas read child by child it was 118 us.

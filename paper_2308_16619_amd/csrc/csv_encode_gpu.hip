@@ -294,7 +294,7 @@ __device__ __forceinline__ uint32_t vox_at(uint32_t x, uint32_t y, uint32_t z) {
 // workgroup per CU: the brick's 128 KB of labels are read once, into
 // registers while the brick before is worked on, and kept in LDS for the
 // operations, which look at every expanded node's eight children and twelve
-// neighbours.  Bound by vector issue (20 k wave-instructions per brick, 43 %
+// neighbours.  Bound by vector issue (20 k wave-instructions per brick, 49 %
 // of the time) and the steps of few waves between barriers; 307 us for the
 // 512^3 cells volume (1.75 TB/s of labels).  Reading the labels again from
 // memory, with six smaller workgroups per CU, exceeded the L2 and took 625
@@ -559,9 +559,10 @@ __global__ __launch_bounds__(kReuseThreads) __attribute__((amdgpu_waves_per_eu(4
 // children and the place of each one's label among the last 17 entries; the
 // first child without a place is appended, which moves the places behind it
 // by one (or to 0), and those before it are final.  A brick of the 512^3
-// cells volume has about 300 left-over children and 100 appends; 60 us for
-// its 4,096 bricks (155 us with a step per child and outcomes in global
-// memory, 113 us with a counter for places in arena 2).
+// cells volume of the performance cases has about 300 left-over children and
+// 100 appends; 60 us for its 4,096 bricks (155 us with a step per child and
+// outcomes in global memory, 113 us with a counter for places in arena 2); 51
+// us for those of the benchmark's 512^3 cells.
 constexpr uint32_t kOutcomes = 2048;  // left-over children whose outcome fits LDS
 __global__ __launch_bounds__(kThreads) void palette_kernel(EncArgs a) {
     __shared__ __align__(8) uint8_t cop_l[kWaves][kOutcomes + 16];
