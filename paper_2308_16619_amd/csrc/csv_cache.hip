@@ -529,7 +529,7 @@ static int frame_impl(csv_frame_cache *c, const uint32_t *ids, const uint8_t *lo
     // (a reset recorded into a graph has not run yet: the next frame may come
     // before the graph, and then needs its own)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool reset_later = c->dirty && hipStreamIsCapturing(s, &capture) == hipSuccess &&
+    const bool reset_later = c->dirty && s && hipStreamIsCapturing(s, &capture) == hipSuccess &&
                              capture != hipStreamCaptureStatusNone;
     if (c->dirty) hipLaunchKernelGGL(reset_kernel, dim3(256), dim3(256), 0, s, d);
     c->dirty = true;
