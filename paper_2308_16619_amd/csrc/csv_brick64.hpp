@@ -7,6 +7,8 @@
 //                     raw bricks are read where they lie in the record;
 //   front_kernel      (of csv_decode.hip; many requests of t >= 2) a wave per
 //                     brick, which is a 32^3 brick of level t - 1 then;
+//   split64_kernel    (levels by request, more requests than slots) a list of
+//                     those of levels 0 and 1, for the kernels below;
 //   upper64_kernel    a workgroup per brick: levels 5 .. max(t, 1) in LDS
 //                     (u16 palette indices, Morton order), one lane per
 //                     parent; t >= 1: the output.  t = 0: level 1, its
@@ -54,11 +56,38 @@ struct Launch64 {
     uint32_t nib_off;        // nibbles in a slot
     uint32_t nib_dw;         // dwords they may take
     uint32_t lut_lds_words;  // decode-table words in LDS (entropy kernel; 0: read from global memory)
-    uint32_t front;          // 1: the front kernel decodes requests of levels 2 and coarser
+    // levels by request in more than one chunk: the requests of levels 0 and 1
+    // (nullptr: requests 0 .. n - 1), how many there are, the chunk's first one
+    const uint32_t *list, *count;
+    uint32_t base;
 };
 
-__device__ __forceinline__ bool front_takes(const DecodeArgs &a, const Launch64 &l, uint32_t rq) {
-    return l.front && a.lods && ld_s_u8(a.lods + rq) >= 2;
+// requests of a launch, and the i-th of them
+__device__ __forceinline__ uint32_t requests64(const DecodeArgs &a, const Launch64 &l) {
+    if (!l.list) return a.n;
+    const uint32_t c = ld_s(l.count);
+    return c > l.base ? min(a.n, c - l.base) : 0u;
+}
+__device__ __forceinline__ uint32_t request64(const Launch64 &l, uint32_t i) {
+    return l.list ? ld_s(l.list + l.base + i) : i;
+}
+
+// Lists the requests of levels 0 and 1 (list, *count from zero), in no order:
+// a counter step per workgroup.  Without it a chunk of a batch with mostly
+// coarser levels holds few of these, and every chunk takes as long as one
+// full-LOD brick: 200,000 requests, one in 200 at full LOD, 57 ms.
+__global__ __launch_bounds__(256) void split64_kernel(const uint8_t *lods, uint32_t n, uint32_t *list, uint32_t *count) {
+    __shared__ uint32_t part[4], first;
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x, w = threadIdx.x >> 6;
+    const uint64_t m = __ballot(i < n && lods[i] < 2);
+    if (lane() == 0) part[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) first = atomicAdd(count, part[0] + part[1] + part[2] + part[3]);
+    __syncthreads();
+    uint32_t at = first;
+#pragma unroll
+    for (uint32_t v = 0; v < 4; v++) at += v < w ? part[v] : 0u;
+    if ((m >> lane()) & 1u) list[at + mbcnt(m)] = i;
 }
 
 struct Hdr64 {
@@ -227,13 +256,13 @@ __global__ __launch_bounds__(64 * kWavesGen) void entropy64_kernel(DecodeArgs a,
     __syncthreads();
     const uint32_t wave = uniform(threadIdx.x >> 6);
     uint8_t *wl = smem + align16(4 * l.lut_lds_words) + wave * kWaveLds;
-    for (uint32_t rq = blockIdx.x * kWavesGen + wave; rq < a.n; rq += gridDim.x * kWavesGen) {
-        if (front_takes(a, l, rq)) continue;
+    const uint32_t n = requests64(a, l);
+    for (uint32_t i = blockIdx.x * kWavesGen + wave; i < n; i += gridDim.x * kWavesGen) {
         Hdr64 g;
         uint32_t *dst, count, fill;
-        const ReqKind kind = load_request64(a, rq, g, dst, count, fill);
+        const ReqKind kind = load_request64(a, request64(l, i), g, dst, count, fill);
         if (kind != kReqDecode || g.raw) continue;
-        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+        uint8_t *slot = glob(l.slots) + (size_t)i * l.slot_bytes;
         const bool ok = entropy64<kLutLds>(a, l, g, slot, slut, wl);
         wsync();
         if (lane() == 0) reinterpret_cast<Head64 *>(slot + k64Head)->bad = ok ? 0u : 1u;
@@ -274,13 +303,11 @@ __global__ __launch_bounds__(k64Threads) __attribute__((amdgpu_waves_per_eu(4)))
     const uint32_t tid = threadIdx.x, L = lane(), w = uniform(tid >> 6), hdr = csv::record_header_words(6);
     constexpr uint32_t kMark = 65533u;
     using V = Vec8<uint16_t>;
-    for (uint32_t rq = blockIdx.x; rq < a.n; rq += gridDim.x) {
-        uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+    const uint32_t n = requests64(a, l);
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const uint32_t rq = request64(l, i);
+        uint8_t *slot = glob(l.slots) + (size_t)i * l.slot_bytes;
         Head64 *head = reinterpret_cast<Head64 *>(slot + k64Head);
-        if (front_takes(a, l, rq)) {
-            if (tid == 0) head->leaf = 0;
-            continue;
-        }
         Hdr64 h;
         uint32_t *dst, count, fill;
         const ReqKind kind = load_request64(a, rq, h, dst, count, fill);
@@ -693,10 +720,10 @@ __device__ __forceinline__ uint32_t eval64(const Leaf64 &f, uint32_t q, uint32_t
     }
 }
 
-// kRuns: workgroups' blocks that one workgroup takes in turn.  With levels by
-// request most workgroups may find nothing to do, and their start is bound by
-// the rate at which they are handed out (12 us for those of 1,024 requests);
-// with one level each block's own workgroup balances better.
+// kRuns: workgroups' blocks that one workgroup takes in turn: 8 for the later
+// chunks of a batch with levels by request, which mostly find nothing to do and
+// are then bound by the rate at which workgroups are handed out (12 us for
+// those of 1,024 requests); else 1, which balances better.
 template <uint32_t kRuns>
 __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_eu(7))) void leaf64_kernel(DecodeArgs a,
                                                                                                            Launch64 l) {
@@ -712,9 +739,9 @@ __global__ __launch_bounds__(64 * k64LeafWaves) __attribute__((amdgpu_waves_per_
     constexpr uint32_t kMark = 65533u, kGroups = k64Blocks / k64LeafWaves / kRuns;  // workgroups per brick
     // workgroups go to the 8 XCDs in turn: those of a brick on the XCD of its
     // upper workgroup, whose L2 holds the slot
-    const uint32_t g = blockIdx.x >> 3, rq = (g / kGroups) * 8 + (blockIdx.x & 7u);
-    if (rq >= a.n) return;
-    const uint8_t *slot = glob(l.slots) + (size_t)rq * l.slot_bytes;
+    const uint32_t g = blockIdx.x >> 3, i = (g / kGroups) * 8 + (blockIdx.x & 7u);
+    if (i >= requests64(a, l)) return;
+    const uint8_t *slot = glob(l.slots) + (size_t)i * l.slot_bytes;
     const Head64 *head = reinterpret_cast<const Head64 *>(slot + k64Head);
     if (!ld_s(&head->leaf)) return;
     const uint32_t P = ld_s(&head->P);

@@ -1359,7 +1359,7 @@ __device__ __forceinline__ const T &brick_args(uint32_t offset) {
 // keeps the levels in LDS and needs no barrier: all 32,768 bricks of a 512^3
 // cells volume, full LOD, 0.322 ms (1.72 TB/s of labels and records); a
 // workgroup per brick with its levels in global scratch took 2.59 ms.
-// The 32^3 kernel is bound by vector issue (70 to 80 % of its time at 16
+// The 32^3 kernel is bound by vector issue (69 % of its time at 16
 // waves per CU), the rest being each brick's serial chain.  Its share of the
 // work is what a decode to level 1 does: 32,768 bricks of the 1024^3 neurite
 // volume in 0.40 ms, against 0.475 ms with one look at the word ring per
@@ -2633,7 +2633,11 @@ int generic_bufs(csv_pool *pool, hipStream_t s, uint64_t bytes, LaunchBufs **out
         (void)hipFree(b->gen);
         b->gen = nullptr;
         b->gen_bytes = 0;
-        if (hipMalloc(reinterpret_cast<void **>(&b->gen), bytes) != hipSuccess) return CSV_ENOMEM;
+        if (hipMalloc(reinterpret_cast<void **>(&b->gen), bytes) != hipSuccess) {
+            (void)hipGetLastError();  // (a caller may go on with less)
+            b->gen = nullptr;
+            return CSV_ENOMEM;
+        }
         b->gen_bytes = bytes;
     }
     *out = b;
@@ -2814,7 +2818,7 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
             (void)set_lds_attr(upper64_kernel<Symbols64::kOwnLds>);
             (void)set_lds_attr(upper64_kernel<Symbols64::kOwnGlobal>);
             (void)set_lds_attr(leaf64_kernel<1>);
-            (void)set_lds_attr(leaf64_kernel<4>);
+            (void)set_lds_attr(leaf64_kernel<8>);
         });
         // slots for 4 requests per CU at most (0.2 to 0.5 MB each)
         const uint32_t per = plain ? 1u : std::min(n, 4u * cu);
@@ -2825,8 +2829,17 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
         const uint32_t lds_a = align16(4 * la.lut_lds_words) + (uint32_t)kWavesGen * kWaveLds;
         // (16 waves per CU at most, by registers)
         const uint32_t waves = cu * std::max(1u, std::min(kLdsBytes / lds_a, 16u / kWavesGen)) * kWavesGen;
-        const int rc = generic_bufs(pool, s, std::max(l.slot_bytes * per, (uint64_t)la.slot_bytes * std::min(per, waves)), &G);
-        if (rc) return rc;
+        const uint64_t slots = (std::max(l.slot_bytes * per, (uint64_t)la.slot_bytes * std::min(per, waves)) + 255u) & ~255ull;
+        // Levels by request in more than one chunk: those of levels 0 and 1
+        // are listed and fill the first chunks, where there is room for the list
+        // (of a power of two, so that it seldom grows).  20,000 requests, 1 in
+        // 63 at full LOD: 0.95 ms, and 6.65 in chunks of all levels.
+        bool split = lods && !plain && n > per;
+        if (split) split = generic_bufs(pool, s, slots + 256 + (4ull << (32 - __builtin_clz(n))), &G) == CSV_OK;
+        if (!split) {
+            const int rc = generic_bufs(pool, s, slots, &G);
+            if (rc) return rc;
+        }
         l.slots = la.slots = G->gen;
         const uint64_t g = 64u >> (lods ? 0u : lod_scalar), cnt = lods ? 0 : g * g * g;
         auto args = [&](uint32_t at, uint32_t m) {
@@ -2837,17 +2850,23 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
         // are more of them than upper workgroups fit at once: 16 of its waves
         // on a CU work on a brick each, of theirs 8.  5,000 requests of level
         // 3: 35 us, 175 by workgroups; 256: 22 us, 18 by workgroups.
-        const bool front = n > 2 * cu && (lods || lod_scalar >= 2);
-        if (front) {
-            const uint32_t most = (uint32_t)std::min<uint64_t>(waves, G->gen_bytes / la.slot_bytes) / kWavesGen;
+        if (split || (!lods && lod_scalar >= 2 && n > 2 * cu)) {
+            const uint32_t most = (uint32_t)std::min<uint64_t>(waves, slots / la.slot_bytes) / kWavesGen;
             for (uint32_t at = 0, m = plain ? 1u : n; at < n; at += m)
                 launch_gen<-1>(args(at, m), la, std::max(1u, std::min(most, (m + kWavesGen - 1) / kWavesGen)), lds_a, s);
             if (!lods) return hipGetLastError() == hipSuccess ? CSV_OK : CSV_EHIP;
         }
-        l.front = front ? 1u : 0u;
+        if (split) {
+            uint32_t *count = reinterpret_cast<uint32_t *>(G->gen + slots), *list = count + 64;
+            hipLaunchKernelGGL(zero_words, dim3(1), dim3(256), 0, s, count, 1u);
+            hipLaunchKernelGGL(split64_kernel, dim3((n + 255) / 256), dim3(256), 0, s, lods, n, list, count);
+            l.list = list;
+            l.count = count;
+        }
         for (uint32_t at = 0; at < n; at += per) {
             const uint32_t m = std::min(per, n - at);
-            const DecodeArgs a = args(at, m);
+            DecodeArgs a = args(split ? 0 : at, m);
+            l.base = at;
             // Few requests (a workgroup each): the upper kernel decodes their
             // symbols itself.  One launch less: 16 requests of level 5 take 9
             // us, 300 take 10.3 (12.7 and 14.5 with the launch).
@@ -2866,10 +2885,9 @@ int launch_edges(csv_pool *pool, const uint32_t *ids, const uint8_t *lods, uint3
                 hipLaunchKernelGGL(upper64_kernel<Symbols64::kOwnLds>, gu, tu, kU64Lds, s, a, l);
             else
                 hipLaunchKernelGGL(upper64_kernel<Symbols64::kOwnGlobal>, gu, tu, kU64Lds, s, a, l);
-            // levels by request: most may have nothing for the leaf kernel
             const uint32_t bricks = ((m + 7) / 8) * 8, groups = k64Blocks / k64LeafWaves;
-            if (lods && m > cu / 2)
-                hipLaunchKernelGGL(leaf64_kernel<4>, dim3(bricks * groups / 4), dim3(64 * k64LeafWaves), lds_l, s, a, l);
+            if (split && at >= 8 * per)
+                hipLaunchKernelGGL(leaf64_kernel<8>, dim3(bricks * groups / 8), dim3(64 * k64LeafWaves), lds_l, s, a, l);
             else if (lods || lod_scalar == 0)
                 hipLaunchKernelGGL(leaf64_kernel<1>, dim3(bricks * groups), dim3(64 * k64LeafWaves), lds_l, s, a, l);
         }

@@ -1396,16 +1396,20 @@ struct Batches {
     }
     // the index and the records of the B bricks
     void join(uint8_t *out, uint32_t B) {
-        uint8_t *to = out + csv::record_area_offset(B);
-        uint64_t *index = reinterpret_cast<uint64_t *>(out + csv::kHeaderBytes), at = 0;
+        uint8_t *to = out + csv::record_area_offset(B), *index = out + csv::kHeaderBytes;
+        uint64_t at = 0;
+        auto put = [&](uint64_t v) {  // (the caller's memory may have any alignment)
+            std::memcpy(index, &v, 8);
+            index += 8;
+        };
         for (Piece *p = head; p; p = p->next) {
             const uint64_t rs = csv::record_area_offset(p->n), m = p->bytes - rs;
             const uint64_t *from = reinterpret_cast<const uint64_t *>(p->at() + csv::kHeaderBytes);
-            for (uint32_t i = 0; i < p->n; i++) *index++ = at + from[i];
+            for (uint32_t i = 0; i < p->n; i++) put(at + from[i]);
             std::memcpy(to + at, p->at() + rs, m);
             at += m;
         }
-        *index = at;
+        put(at);
     }
 };
 

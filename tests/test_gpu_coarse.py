@@ -95,15 +95,14 @@ def test_edge64_malformed_states(orc, n):
         np.testing.assert_array_equal(got[int(off[k]):int(off[k]) + 64 ** 3], orc.decode_brick(blob, int(ids[k]), 0).ravel())
 
 
-@pytest.mark.parametrize("plain", [False, True])
-def test_edge64_requests_out_of_range_among_many(orc, plain):
+@pytest.mark.parametrize("n,plain", [(600, False), (600, True), (1500, False)])
+def test_edge64_requests_out_of_range_among_many(orc, n, plain):
     # each is found once, by the kernel that serves its level
     torch = torch_cuda()
     import paper_2308_16619_amd as csv
     blob = csv.encode_volume(volume64(36), brick_log2=6)
     pool = csv.Pool()
     pool.add_volume(blob)
-    n = 600
     rng = np.random.default_rng(36)
     ids = rng.integers(0, 8, n).astype(np.uint32)
     lods = rng.integers(1, 7, n).astype(np.uint8)
@@ -127,6 +126,64 @@ def test_edge64_requests_out_of_range_among_many(orc, plain):
     for i in np.nonzero(~bad)[0]:
         w = orc.decode_brick(blob, int(ids[i]), int(lods[i])).ravel()
         np.testing.assert_array_equal(got[int(off[i]):int(off[i]) + w.size], w)
+
+
+@pytest.mark.parametrize("n", [1025, 9300])
+def test_edge64_levels_0_and_1_listed_from_many_requests(orc, n):
+    # more requests than slots: none, some and only such levels (in chunks up
+    # to the ninth, whose leaf workgroups take 8 runs)
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(37), brick_log2=6)
+    pool = csv.Pool()
+    pool.add_volume(blob)
+    rng = np.random.default_rng(n)
+    want = {(i, t): orc.decode_brick(blob, i, t).ravel() for i in range(8) for t in range(7)}
+    for levels, p in (((3, 4, 5, 6), None), ((0, 1, 2, 5), (0.01, 0.3, 0.3, 0.39)), ((1,), None), ((0, 1), (0.005, 0.995))):
+        ids = rng.integers(0, 8, n).astype(np.uint32)
+        lods = rng.choice(levels, n, p=p).astype(np.uint8)
+        lods[-1] = levels[0]
+        print("[gpu-test] edge 64, %d requests of levels %s" % (n, levels), flush=True)
+        got, off, _ = decode_lods(csv, pool, ids, lods)
+        assert pool.last_error() == (0, 0)
+        for i, t, o in zip(ids, lods, off):
+            w = want[int(i), int(t)]
+            assert np.array_equal(got[int(o):int(o) + w.size], w), (i, t, o)
+
+
+def test_edge64_captured_with_more_requests_than_the_list_holds(orc):
+    # the list cannot grow in a capture: chunks of all levels then
+    torch = torch_cuda()
+    import paper_2308_16619_amd as csv
+    blob = csv.encode_volume(volume64(38), brick_log2=6)
+    pool = csv.Pool()
+    pool.add_volume(blob)
+    n = 2100
+    want = {(i, t): orc.decode_brick(blob, i, t).ravel() for i in range(8) for t in range(7)}
+    rng = np.random.default_rng(38)
+    lods = np.where(np.arange(n) % 300 == 0, 0, rng.integers(2, 7, n)).astype(np.uint8)
+    off, tot = csv.output_offsets(lods, 6)
+    ids = torch.zeros(n, dtype=torch.int32, device="cuda")
+    d_lods, d_off = torch.from_numpy(lods).cuda(), torch.from_numpy(off.view(np.int64)).cuda()
+    out = torch.empty(tot, dtype=torch.int32, device="cuda")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        pool.decode(ids[:1100], out, lods=d_lods[:1100], out_offsets=d_off[:1100], stream=s)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("[gpu-test] captured", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        pool.decode(ids, out, lods=d_lods, out_offsets=d_off, stream=s)
+    for _ in range(3):
+        now = rng.integers(0, 8, n).astype(np.int32)
+        ids.copy_(torch.from_numpy(now))
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert pool.last_error() == (0, 0)
+        got = out.cpu().numpy().view(np.uint32)
+        for i, t, o in zip(now, lods, off):
+            w = want[int(i), int(t)]
+            assert np.array_equal(got[int(o):int(o) + w.size], w), (i, t, o)
 
 
 @pytest.mark.parametrize("coding", [0, 1])
