@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 # what the same counters read for a plain 256 MiB device copy; see
 # profiles/decode_neurite1024_hbm_traffic.md.  Valid only for the decoder
 # source the counters were taken on (at the launch shape named here).
-TRAFFIC = {"decoder_sha256_16": "23f4b9d0a8342557", "shape": (8, 3, 0, 0, 4), "bytes": 5093642559}
+TRAFFIC = {"decoder_sha256_16": "ea0b23de6d524c28", "shape": (8, 3, 0, 0, 4), "bytes": 5093618947}
 PAPER_GBS = {"cells": 9.9, "fiber": 10.4, "cortex": 9.3}  # Table 3, RTX 3070 Ti (context only)
 
 
